@@ -30,8 +30,8 @@ PEAK_HBM_GBPS = 8000.0
 # WRITE_SIZE passes (calibrated against a plain copy: FETCH_SIZE x 2.0,
 # WRITE_SIZE x 1.0), valid only for that workload and the kernel source they
 # were taken on.
-POSTERIOR_TRAFFIC = {"source_sha1": "2390c5c7a554f5900a4d3815ba24f2cb7a60f96a",
-                     "bytes": {"f32": 14046269, "f64": 17451049}}
+POSTERIOR_TRAFFIC = {"source_sha1": "ef5e773c14f76314f5e55f711ff9a40664992717",
+                     "bytes": {"f32": 14749296, "f64": 17462993}}
 
 
 def posterior_traffic(args):
@@ -229,10 +229,12 @@ def main():
 
     # Algorithmic work of the fused posterior per candidate and objective: the
     # triangular product (m^2 flops) and K* with the mean (m (3d + 10) flops;
-    # the m square roots and m exponentials are not counted).  On gfx950 the
-    # fp32 matrix instructions and the vector ALU share one datapath (measured:
-    # they do not overlap), so both draw on the same 157.3 TFLOP/s (78.6 in
-    # fp64, for the matrix instructions and the vector ALU alike).
+    # the m square roots and m exponentials are not counted).  The peak is the
+    # rate of the precision that the results have: 157.3 TFLOP/s in fp32, 78.6
+    # in fp64, for the matrix instructions and the vector ALU alike.  The fp32
+    # kernel's product runs as six bf16 products of exact three-part splits
+    # (fp32 results at fp32 accuracy), so its share of the fp32 peak could
+    # exceed one.
     flops_trsm = m * m
     flops_per_unit = flops_trsm + m * (3 * w["d"] + 10)
     peak = PEAK_FP64_MFMA_TFLOPS if args.dtype == "f64" else PEAK_FP32_MFMA_TFLOPS
@@ -268,7 +270,8 @@ def main():
         },
         "roofline": {
             "bound": "mfma",
-            "kernel": f"posterior_{args.dtype}_kernel (K*, mean, L^-1 K*^T on {args.dtype[1:]}-bit MFMA, variance)",
+            "kernel": f"posterior_{args.dtype}_kernel (K*, mean, L^-1 K*^T on "
+                      f"{'fp64' if args.dtype == 'f64' else 'bf16 (exact three-part split)'} MFMA, variance)",
             "achieved": achieved,
             "peak": peak,
             "unit": "TFLOP/s",

@@ -137,79 +137,100 @@ int upload_async(void* dst, const void* src, size_t bytes, int slot, void* strea
   return SCOOT_OK;
 }
 
+namespace {
+// The handle's fields but its buffer.
+GPDevice describe(const FitHost& f, const double* warp_a, const double* warp_b, scoot_dtype dt) {
+  GPDevice g;
+  g.dt = dt;
+  g.m = f.m;
+  g.d = f.d;
+  g.m_pad = f.m_pad;
+  g.nb = f.nb;
+  g.s2 = f.s2;
+  g.tau2 = f.tau2;
+  g.c = f.c;
+  for (int k = 0; k < SCOOT_MAX_DIM; ++k) {
+    g.scale64[k] = k < f.d ? f.scale[k] : 0.0;
+    g.scale32[k] = (float)g.scale64[k];
+  }
+  for (int i = 0; i < 3; ++i) {
+    g.coef64[i] = f.coef[i];
+    g.coef32[i] = (float)f.coef[i];
+  }
+  g.warp = warp_a != nullptr;
+  for (int k = 0; k < SCOOT_MAX_DIM; ++k) {
+    g.warp_a[k] = g.warp && k < f.d ? warp_a[k] : 1.0;
+    g.warp_b[k] = g.warp && k < f.d ? warp_b[k] : 1.0;
+  }
+  return g;
+}
+
+// The device buffer: [L^-1 packed][observations][alpha][alpha as float], each
+// part 256-byte aligned.
+size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+struct GPLayout {
+  size_t xs, alpha, alpha32, bytes;
+  GPLayout(size_t linv_bytes, size_t xs_bytes, int m_pad) {
+    xs = align256(linv_bytes);
+    alpha = xs + align256(xs_bytes);
+    alpha32 = alpha + align256((size_t)m_pad * 8);
+    bytes = alpha32 + align256((size_t)m_pad * 4);
+  }
+  void place(GPDevice& g) const {
+    unsigned char* p = (unsigned char*)g.buf;
+    g.linv = p;
+    g.xs = p + xs;
+    g.alpha = (const double*)(p + alpha);
+    g.alpha32 = (const float*)(p + alpha32);
+  }
+};
+
+int make_handle(const GPDevice& g, scoot_gp* out) {
+  scoot_gp h = new (std::nothrow) scoot_gp_t;
+  if (!h) {
+    hipFree(g.buf);
+    return fail(SCOOT_ERR_NO_MEMORY, "gp fit: host allocation failed");
+  }
+  h->dev = g;
+  hipGetDevice(&h->device);
+  *out = h;
+  return SCOOT_OK;
+}
+}  // namespace
+
 int gp_from_fit(const FitHost& f, const double* warp_a, const double* warp_b, scoot_dtype dt, scoot_gp* out) {
   const int m = f.m, d = f.d;
-  const double signal_var = f.s2, noise_var = f.tau2, prior_mean = f.c;
   try {
-    GPDevice g;
-    g.dt = dt;
-    g.m = m;
-    g.d = d;
-    g.m_pad = f.m_pad;
-    g.nb = f.nb;
-    g.s2 = signal_var;
-    g.tau2 = noise_var;
-    g.c = prior_mean;
-    for (int k = 0; k < SCOOT_MAX_DIM; ++k) {
-      g.scale64[k] = k < d ? f.scale[k] : 0.0;
-      g.scale32[k] = (float)g.scale64[k];
-    }
-    for (int i = 0; i < 3; ++i) {
-      g.coef64[i] = f.coef[i];
-      g.coef32[i] = (float)f.coef[i];
-    }
-    g.warp = warp_a != nullptr;
-    for (int k = 0; k < SCOOT_MAX_DIM; ++k) {
-      g.warp_a[k] = g.warp && k < d ? warp_a[k] : 1.0;
-      g.warp_b[k] = g.warp && k < d ? warp_b[k] : 1.0;
-    }
-
-    // Host image of the device buffer: [L^-1 packed][scaled observations][alpha][alpha as float].
-    std::vector<unsigned char> img;
-    size_t linv_bytes, xs_bytes;
-    const size_t esz = dt == SCOOT_F32 ? 4 : 8;
+    GPDevice g = describe(f, warp_a, warp_b, dt);
     std::vector<float> l32;
-    std::vector<double> l64;
+    std::vector<double> l64, xs;
+    // fp32: the augmented observation rows of the distance chain; fp64: scaled
+    // rows of kXsStride doubles, which carry alpha_i in column d where there is
+    // one, so the kernel reads an observation and its weight with the same loads
     if (dt == SCOOT_F32) {
       pack_linv_f32(f, l32);
-      linv_bytes = l32.size() * 4;
+      pack_obs_f32(f, xs);
     } else {
       pack_linv_f64(f, l64);
-      linv_bytes = l64.size() * 8;
-    }
-    linv_bytes = (linv_bytes + 255) / 256 * 256;
-    // fp32: the augmented observation rows of the cross-term chain (double);
-    // fp64: scaled rows of kXsStride doubles
-    std::vector<double> q32;
-    if (dt == SCOOT_F32) pack_obs_f32(f, q32);
-    xs_bytes = dt == SCOOT_F32 ? (q32.size() * 8 + 255) / 256 * 256
-                               : ((size_t)f.m_pad * kXsStride * esz + 255) / 256 * 256;
-    const size_t alpha_bytes = (size_t)f.m_pad * 8;
-    const size_t alpha32_bytes = ((size_t)f.m_pad * 4 + 255) / 256 * 256;
-    img.assign(linv_bytes + xs_bytes + alpha_bytes + alpha32_bytes, 0);
-    if (dt == SCOOT_F32) std::memcpy(img.data(), l32.data(), l32.size() * 4);
-    else std::memcpy(img.data(), l64.data(), l64.size() * 8);
-    // fp64 rows with a spare column carry alpha_i in column d, so the kernel
-    // reads an observation and its weight with the same loads.
-    if (dt == SCOOT_F32) {
-      std::memcpy(img.data() + linv_bytes, q32.data(), q32.size() * 8);
-    } else {
+      xs.assign((size_t)f.m_pad * kXsStride, 0.0);
       for (int i = 0; i < f.m_pad; ++i)
         for (int k = 0; k < kXsStride; ++k) {
-          double v = 0.0;
+          double& v = xs[(size_t)i * kXsStride + k];
           if (k < d) v = i < m ? f.Xw[(size_t)i * d + k] * f.scale[k] : kPadCoord;
           else if (k == d && i < m) v = f.alpha[i];
-          std::memcpy(img.data() + linv_bytes + ((size_t)i * kXsStride + k) * 8, &v, 8);
         }
     }
-    std::vector<double> apad(f.m_pad, 0.0);
-    std::memcpy(apad.data(), f.alpha.data(), sizeof(double) * m);
-    std::memcpy(img.data() + linv_bytes + xs_bytes, apad.data(), alpha_bytes);
-    for (int i = 0; i < f.m_pad; ++i) {
-      float av = (float)apad[i];
-      std::memcpy(img.data() + linv_bytes + xs_bytes + alpha_bytes + (size_t)i * 4, &av, 4);
+    const void* linv = dt == SCOOT_F32 ? (const void*)l32.data() : (const void*)l64.data();
+    const size_t linv_bytes = dt == SCOOT_F32 ? l32.size() * 4 : l64.size() * 8;
+    const GPLayout L(linv_bytes, xs.size() * 8, f.m_pad);
+    std::vector<unsigned char> img(L.bytes, 0);
+    std::memcpy(img.data(), linv, linv_bytes);
+    std::memcpy(img.data() + L.xs, xs.data(), xs.size() * 8);
+    std::memcpy(img.data() + L.alpha, f.alpha.data(), sizeof(double) * m);
+    for (int i = 0; i < m; ++i) {
+      const float av = (float)f.alpha[i];
+      std::memcpy(img.data() + L.alpha32 + (size_t)i * 4, &av, 4);
     }
-
     hipError_t e = hipMalloc(&g.buf, img.size());
     if (e != hipSuccess) return fail(SCOOT_ERR_NO_MEMORY, "gp fit: device allocation failed");
     e = hipMemcpy(g.buf, img.data(), img.size(), hipMemcpyHostToDevice);
@@ -217,15 +238,34 @@ int gp_from_fit(const FitHost& f, const double* warp_a, const double* warp_b, sc
       hipFree(g.buf);
       return fail(SCOOT_ERR_DEVICE, std::string("gp fit: upload: ") + hipGetErrorString(e));
     }
-    g.linv = g.buf;
-    g.xs = (unsigned char*)g.buf + linv_bytes;
-    g.alpha = (const double*)((unsigned char*)g.buf + linv_bytes + xs_bytes);
-    g.alpha32 = (const float*)((unsigned char*)g.buf + linv_bytes + xs_bytes + alpha_bytes);
-    scoot_gp h = new scoot_gp_t;
-    h->dev = g;
-    hipGetDevice(&h->device);
-    *out = h;
-    return SCOOT_OK;
+    L.place(g);
+    return make_handle(g, out);
+  } catch (const std::bad_alloc&) {
+    return fail(SCOOT_ERR_NO_MEMORY, "gp fit: host allocation failed");
+  }
+}
+
+int gp_from_factor(const FitHost& f, const double* warp_a, const double* warp_b, const double* Xi, int nbf,
+                   const double* alpha, void* stream, scoot_gp* out) {
+  try {
+    GPDevice g = describe(f, warp_a, warp_b, SCOOT_F32);
+    std::vector<double> xs;
+    pack_obs_f32(f, xs);
+    const GPLayout L((size_t)post_units((f.m + 15) / 16, f.nb) * 3 * 64 * 16, xs.size() * 8, f.m_pad);
+    if (hipMalloc(&g.buf, L.bytes) != hipSuccess)
+      return fail(SCOOT_ERR_NO_MEMORY, "gp fit: device allocation failed");
+    L.place(g);
+    int rc = launch_pack_f32(Xi, nbf, alpha, f.m, f.nb, g.buf, (double*)g.alpha, (float*)g.alpha32, stream);
+    if (rc == SCOOT_OK) {
+      hipError_t e = hipMemcpyAsync((void*)g.xs, xs.data(), xs.size() * 8, hipMemcpyHostToDevice, (hipStream_t)stream);
+      if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
+      if (e != hipSuccess) rc = fail(SCOOT_ERR_DEVICE, std::string("gp fit: upload: ") + hipGetErrorString(e));
+    }
+    if (rc != SCOOT_OK) {
+      hipFree(g.buf);
+      return rc;
+    }
+    return make_handle(g, out);
   } catch (const std::bad_alloc&) {
     return fail(SCOOT_ERR_NO_MEMORY, "gp fit: host allocation failed");
   }

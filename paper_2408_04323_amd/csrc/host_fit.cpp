@@ -132,29 +132,44 @@ int fit_host(const double* X, const double* y, int m, int d, scoot_kernel kernel
   return SCOOT_OK;
 }
 
-// fp32 layout, for v_mfma_f32_16x16x4f32: 16 x 16 blocks (J <= I), the
-// block's contraction index ordered k = 4g + s (g = lane / 16, s the step),
-// so at step s lane l holds Linv[16I + l % 16][16J + 4 (l / 16) + s] and a
-// lane reads the four steps of a block as one 16-byte load:
-//   float index = (blk * 64 + l) * 4 + s.
-// Blocks are ordered the way the kernel's waves consume them: plan entry
-// after plan entry (plan_rows16 with the kernel's wave count), J = 0..I.
+// fp32 layout, for v_mfma_f32_32x32x16_bf16: units of 32 rows x 16 columns,
+// observation block j = 0 .. ceil(m / 16) - 1 outermost, then row blocks P =
+// nb - 1 down to j / 2.  Every entry is the sum of three bfloat16 values
+// (rounded to nearest, each the next one's remainder: 24 bits and more of the
+// double), a part per 1 KiB: lane l holds L^-1[32P + l % 32][16j + 8 (l / 32) + i],
+// i = 0..7, as four words of two,
+//   word index = ((unit * 3 + part) * 64 + l) * 4 + i / 2, the low half first.
 void pack_linv_f32(const FitHost& f, std::vector<float>& out) {
-  const int nb = f.m_pad / kBlk16, m = f.m;
-  const RowPlan16 plan = plan_rows16(nb, posterior_waves(f.nb));
-  out.assign((size_t)nb * (nb + 1) / 2 * 4 * 64, 0.0f);
-  size_t blk = 0;
-  for (int e = 0; e < 8; ++e)
-    for (int q = 0; q < plan.nrows[e] && q < kMaxRows16; ++q) {
-      const int I = plan16_row(plan, e, q);
-      for (int J = 0; J <= I; ++J, ++blk)
-        for (int l = 0; l < 64; ++l)
-          for (int s = 0; s < 4; ++s) {
-            const int row = 16 * I + (l % 16), col = 16 * J + 4 * (l / 16) + s;
-            const double v = (row < m && col < m) ? f.Linv[(size_t)row * m + col] : 0.0;
-            out[(blk * 64 + l) * 4 + s] = (float)v;
-          }
+  const int nb = f.nb, m = f.m, nj = (m + 15) / 16;
+  out.assign((size_t)post_units(nj, nb) * 3 * 64 * 4, 0.0f);
+  unsigned char* units = reinterpret_cast<unsigned char*>(out.data());
+  // a row block's units are its own, so row blocks run in parallel
+  parallel_chunks(nb, [&](int P) {
+    for (int j = 0, unit = 0; j < nj && j / 2 <= P; unit += nb - j / 2, ++j) {
+      unsigned char* at = units + (size_t)(unit + nb - 1 - P) * 3 * 64 * 16;
+      for (int row = 32 * P; row < std::min(32 * P + 32, m); ++row)
+        for (int half = 0; half < 2; ++half) {
+          const int c0 = 16 * j + 8 * half, cols = std::min(8, row + 1 - c0);
+          if (cols <= 0) continue;
+          double v[8] = {};
+          std::memcpy(v, &f.Linv[(size_t)row * m + c0], sizeof(double) * cols);
+          uint16_t h[3][8];
+          for (int part = 0; part < 3; ++part)
+            for (int i = 0; i < 8; ++i) {
+              const float x = (float)v[i];
+              uint32_t b;
+              std::memcpy(&b, &x, 4);
+              b = (b + 0x7fffu + ((b >> 16) & 1u)) & 0xffff0000u;  // to nearest even
+              float back;
+              std::memcpy(&back, &b, 4);
+              v[i] -= (double)back;
+              h[part][i] = (uint16_t)(b >> 16);
+            }
+          for (int part = 0; part < 3; ++part)
+            std::memcpy(at + part * 1024 + (row % 32 + 32 * half) * 16, h[part], 16);
+        }
     }
+  });
 }
 
 // The fp32 kernel's observation operand: per 16-observation block J and step
@@ -164,7 +179,7 @@ void pack_linv_f32(const FitHost& f, std::vector<float>& out) {
 // candidates' rows (xs, 1, |xs|^2) the chain yields -|xs - Xs_i|^2:
 //   double index = (J * S + s) * 64 + l,  S = ceil((d + 2) / 4).
 // That instruction leaves output row t = g + 4r in register r of lanes
-// 16g .. 16g + 15 (measured), while the float triangle wants observation
+// 16g .. 16g + 15 (measured), while the product wants observation
 // 16J + 4g + r there, so A-operand row t carries observation
 // 16J + 4 (t % 4) + t / 4.  Padding rows (i >= m) carry -1e30 in the norm's
 // place: their covariance underflows to exactly 0.

@@ -32,6 +32,14 @@ constexpr double kPadCoord = 1.0e4;    // scaled coordinate of padding rows: k(x
 // so it gets 8 waves; otherwise two 4-wave workgroups share a CU.
 inline int posterior_waves(int nb) { return nb > 9 ? 8 : 4; }
 
+// Units (32 rows x 16 columns) of the fp32 posterior's stream of L^-1: at
+// observation block j the row blocks j / 2 .. nb32 - 1.
+inline int post_units(int nj, int nb32) {
+  int u = 0;
+  for (int j = 0; j < nj; ++j) u += nb32 - j / 2;
+  return u;
+}
+
 // Which 16-row blocks of V each wave of the posterior owns (both
 // precisions).  Row block I costs I + 1 blocks of the triangle.  Plan entry p
 // goes to wave p of a 4-wave workgroup; with 8 waves the two entries p and
@@ -202,6 +210,11 @@ int fit_setup(const double* X, const double* y, int m, int d, scoot_kernel kerne
               const double* warp_a, const double* warp_b, double s2, double tau2, double c, FitHost& out);
 // The device GP handle of a fit (its Linv and alpha filled): packing and upload.
 int gp_from_fit(const FitHost& f, const double* warp_a, const double* warp_b, scoot_dtype dt, scoot_gp* out);
+// The same for fp32 from a factorization on the device: Xi = L^-1 as nbf x nbf
+// row-major 16 x 16 blocks (J <= I used), alpha (16 nbf), both made on
+// `stream` before; f without Linv and alpha.  Returns when the handle is ready.
+int gp_from_factor(const FitHost& f, const double* warp_a, const double* warp_b, const double* Xi, int nbf,
+                   const double* alpha, void* stream, scoot_gp* out);
 // mle_fit_device, then the GP at the optimum with L^-1 and alpha from the
 // search's own device factorization (no host refit).
 int mle_fit_device_gp(const double* X, const double* y, int m, int d, scoot_kernel kernel, const double* warp_a,
@@ -350,6 +363,10 @@ int launch_posterior(const GPDevice& g, const float* Xc, int64_t n, void* mu, vo
                      const double* ei_c /* nullable: fused EI with c = best + xi */, void* ei,
                      void* stream, float* v_out = nullptr, bool xc_warped = false,
                      int64_t v_ld = 0 /* row stride of v_out; 0: n */);
+// The units of pack_linv_f32 and alpha's two copies (m_pad entries), from a
+// factorization's L^-1 blocks on the device.
+int launch_pack_f32(const double* Xi, int nbf, const double* alpha, int m, int nb32, void* linv, double* alpha64,
+                    float* alpha32, void* stream);
 int launch_warp_pool(const GPDevice& g, const float* Xc, int64_t n, float* out, void* stream);
 int launch_ei(const void* mu, const void* sigma, int64_t n, scoot_dtype dt, double c, void* ei,
               void* stream);

@@ -924,10 +924,8 @@ class DeviceNll {
     }
     return true;
   }
-  // K, the factor and L^-1 at theta, then L^-1 (m x m row-major, lower) and
-  // alpha to the host; false when K is not positive definite or on a device
-  // failure (kept in error()).
-  bool inverse(const double* theta, std::vector<double>& Linv, std::vector<double>& alpha) {
+  // K, the factor, L^-1 and alpha at theta, launched.
+  bool launch_factor(const double* theta) {
     if (rc_ != SCOOT_OK) return false;
     std::memcpy(a_.theta, theta, sizeof(double) * P_);
     (void)hipGetLastError();  // clear an earlier, unrelated error
@@ -941,16 +939,31 @@ class DeviceNll {
       rc_ = fail(SCOOT_ERR_DEVICE, std::string("gp fit: launch failed: ") + hipGetErrorString(launched));
       return false;
     }
+    return true;
+  }
+  // After a synchronisation: false when K is not positive definite or on a
+  // device failure (kept in error()).
+  bool factored() {
+    if (host_[0] == 2.0) {
+      rc_ = fail(SCOOT_ERR_DEVICE, "gp fit: the factorization's wait for its diagonal block ran out");
+      return false;
+    }
+    return host_[0] == 1.0;
+  }
+  const double* Xi() const { return a_.Xi; }
+  const double* alpha() const { return a_.alpha; }
+  int blocks() const { return nb_; }
+  hipStream_t stream() const { return s_; }
+  // launch_factor, then L^-1 (m x m row-major, lower) and alpha to the host;
+  // false when K is not positive definite or on a device failure.
+  bool inverse(const double* theta, std::vector<double>& Linv, std::vector<double>& alpha) {
+    if (!launch_factor(theta)) return false;
     if (hipStreamSynchronize(s_) != hipSuccess) {
       rc_ = fail(SCOOT_ERR_DEVICE, std::string("gp fit: device factorization failed: ") +
                                        hipGetErrorString(hipGetLastError()));
       return false;
     }
-    if (host_[0] == 2.0) {
-      rc_ = fail(SCOOT_ERR_DEVICE, "gp fit: the factorization's wait for its diagonal block ran out");
-      return false;
-    }
-    if (host_[0] != 1.0) return false;
+    if (!factored()) return false;
     std::vector<double> xi((size_t)nb_ * nb_ * 256), al((size_t)nb_ * 16);
     if (hipMemcpyAsync(xi.data(), a_.Xi, xi.size() * sizeof(double), hipMemcpyDeviceToHost, s_) != hipSuccess ||
         hipMemcpyAsync(al.data(), a_.alpha, al.size() * sizeof(double), hipMemcpyDeviceToHost, s_) != hipSuccess ||
@@ -1036,7 +1049,7 @@ int mle_fit_device(const double* X, const double* y, int m, int d, scoot_kernel 
 }
 
 namespace {
-// The GP at theta from a factorization on dev: the host part of a fit, then
+// The GP at theta from a factorization on dev: the host part of a fit, with
 // L^-1 and alpha from the device.
 int gp_from_device(DeviceNll& dev, const double* X, const double* y, int m, int d, scoot_kernel kernel,
                    const double* warp_a, const double* warp_b, double c, bool learn_warp, const double* theta,
@@ -1056,9 +1069,25 @@ int gp_from_device(DeviceNll& dev, const double* X, const double* y, int m, int 
   FitHost f;
   int rc = fit_setup(X, y, m, d, kernel, ls, pa, pb, std::exp(theta[d]), std::exp(theta[d + 1]), c, f);
   if (rc != SCOOT_OK) return rc;
-  if (!dev.inverse(theta, f.Linv, f.alpha))
+  auto failed = [&]() {
     return dev.error() != SCOOT_OK ? dev.error()
                                    : fail(SCOOT_ERR_NOT_PD, "gp fit: K + tau^2 I is not positive definite");
+  };
+  if (dt == SCOOT_F32) {
+    // fp32: packed on the device; the factorization's status is read after the
+    // one synchronisation, and a handle made from a failed one is dropped
+    if (!dev.launch_factor(theta)) return failed();
+    scoot_gp gp = nullptr;
+    rc = gp_from_factor(f, pa, pb, dev.Xi(), dev.blocks(), dev.alpha(), dev.stream(), &gp);
+    if (rc != SCOOT_OK) return rc;
+    if (!dev.factored()) {
+      scoot_gp_destroy(gp);
+      return failed();
+    }
+    *out = gp;
+    return SCOOT_OK;
+  }
+  if (!dev.inverse(theta, f.Linv, f.alpha)) return failed();
   return gp_from_fit(f, pa, pb, dt, out);
 }
 }  // namespace

@@ -51,322 +51,367 @@ __device__ inline double partial_expectation_d(double c, double mu, double sd) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32.  Everything runs on 16 x 16 MFMA tiles; a candidate tile is 64
-// candidates, four column tiles ct of 16.  Lane l has g = l / 16 and
-// c = l % 16.
+// fp32.  A workgroup of RS waves owns a tile of 64 candidates; wave r owns the
+// row blocks (32 rows) of V that fall to it, for all 64.
 //
-// Phase 1, squared distances on the fp64 matrix cores: with augmented rows
+// Squared distances on the fp64 matrix cores: with augmented rows
 // A_i = (2 X_i, -|X_i|^2, -1) for the observations and B_x = (x, 1, |x|^2)
 // for the candidates (scaled coordinates, fp64), A_i . B_x = -|x - X_i|^2, so
-// one v_mfma_f64_16x16x4f64 chain over ceil((d + 2) / 4) steps gives -u^2
+// one v_mfma_f64_16x16x4f64 chain over S = ceil((d + 2) / 4) steps gives -u^2
 // for 16 observations x 16 candidates, exact to double rounding (no
 // cancellation that float could see).  The observations are packed so that
-// output lane l, register r holds observation 16J + 4g + r of candidate c
-// (the instruction's own order is row g + 4r there): the lane turns its four values
-// into K* in float (sqrt, exp2, the polynomial), folds alpha into the mean,
-// and stores them as one float4 -- which is exactly the B operand the
-// triangular product reads.
+// lane l = 16g + c, register r holds observation 16j + 4g + r of candidate c
+// (the instruction's own order is row g + 4r there); the lane turns its four
+// values into K* in float (sqrt, exp2, the polynomial) and folds alpha into
+// the mean.
 //
-// Phase 2, V = L^-1 K*^T on v_mfma_f32_16x16x4f32 over 16 x 16 blocks of the
-// triangle (executed work (nb16 + 1) / nb16 of the triangle's, against
-// (nb32 + 1) / nb32 for 32 x 32 blocks).  The contraction index of a block is
-// ordered k = 4g + s (s the MFMA step), so at step s lane l holds
-// L^-1[16I + c][16J + 4g + s] and K*[16J + 4g + s][candidate c] -- the
-// float4 phase 1 stored.  Output lane l, register r holds row 16I + 4g + r of
-// candidate c.
+// The product V = L^-1 K*^T runs on the bf16 matrix cores without giving up
+// fp32: every float is exactly the sum of three bfloat16 (8 + 8 + 8 bits), so
+// with L^-1 = a1 + a2 + a3 (split on the host, from double) and K* = b1 + b2 +
+// b3 (split in registers) a product is the six terms a1 b1, a1 b2, a2 b1,
+// a2 b2, a1 b3, a3 b1, accumulated in float, smallest first; the three terms
+// left out are below 2^-25 of the product.  Measured against 64 bits: sigma no
+// further off than with fp32 MFMA chains.  Why: six bf16 instructions take
+// 6/16 of the fp32 instruction's time, and while the fp32 matrix instruction
+// and the vector ALU exclude each other, a bf16 one leaves the vector ALU free
+// for about 19 of its 32 cycles (measured), so the K* generation is woven
+// into the product, four vector instructions or so after each matrix one.
+//
+// Loop order: observation blocks j of 16 outermost, and inside the row blocks
+// P >= j / 2, their accumulators (two 32 x 32 tiles of 16 registers each)
+// resident for the whole tile.  Row block nb - 1 - s is slot s; wave r owns
+// slots r, r + RS, ..., so that at every j the live slots are the first ones
+// of every wave.  The waves share the generation: wave r makes K* of block
+// j + 1 for 64 / RS of the candidates while the product of block j runs, and
+// the parts go through LDS in the order of the product's B operand (lane l:
+// observations 8 (l / 32) .. + 7 of candidate l % 32), two buffers, one barrier
+// per j.  Executed matrix work is (nb32 + 1) / nb32 of the triangle's.
+//
+// L^-1 comes straight from L2 into registers, in units (32 rows x 16 columns,
+// three parts, 3 KiB), each slot's next unit requested as soon as the slot's
+// matrix instructions of this j are issued.  A unit feeds twelve matrix
+// instructions (384 cycles); at two waves per SIMD a CU reads about 20 bytes
+// per cycle.
+//
+// Bound: issue.  Per 32 candidates at m = 256 a SIMD needs 13.8k cycles of bf16
+// and 6.1k of fp64 matrix instructions and about 9k of vector instructions,
+// and takes 34k: the phases overlap little (the fp64 instructions exclude the
+// vector ALU, and two waves often want the same unit).  Against the kernel with
+// fp32 MFMA: 183 -> 141 us at m = 256, 69 -> 43 at m = 128, 286 -> 195 at m =
+// 300, 2559 -> 1700 at m = 512 and n = 2^20 (n = 262,144 otherwise).  A ring of
+// L^-1 units in LDS (four waves of 32 candidates each, every wave with all row
+// blocks) took 135 us at m = 256 but 52 at m = 128 and 2210 at m = 512, where
+// one wave per SIMD is left; K* two blocks ahead instead of one: no faster.
 // ---------------------------------------------------------------------------
 struct Post32 {
   int64_t n;
-  int d, nb16;
+  int nj, nb32;  // observation blocks of 16, row blocks of 32
+  int d;
   double scale[SCOOT_MAX_DIM];
   float c0, c1, c2;
   double s2, prior, ei_c;
-  RowPlan16 plan;  // 16-row blocks of each wave and where they start in the packed inverse
   int64_t v_ld;    // row stride of a kept V
 };
 
-// The 16 MFMA steps of a block: four k-steps for each of the four column
-// tiles, the tiles' chains interleaved.  The next block's A (from L2 at
-// an_src) is requested first, a block ahead of its use; its B (from LDS at
-// bn_src) between the steps, not in one burst before them.
-__device__ inline void mfma_block16f(f4_t (&acc)[4], const f4_t& a, const f4_t (&b)[4], f4_t (&bn)[4],
-                                     const f4_t* bn_src, f4_t& an, const f4_t* an_src) {
-  an = *an_src;
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[ct][0], acc[ct], 0, 0, 0);
-  __builtin_amdgcn_sched_barrier(0);
-  bn[0] = bn_src[0];
-  bn[1] = bn_src[64];
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[ct][1], acc[ct], 0, 0, 0);
-  __builtin_amdgcn_sched_barrier(0);
-  bn[2] = bn_src[128];
-  bn[3] = bn_src[192];
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[ct][2], acc[ct], 0, 0, 0);
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[ct][3], acc[ct], 0, 0, 0);
+constexpr int kUnitBytes = 3 * 64 * 16;   // a unit's three parts in A-operand order
+constexpr int kPostTile = 64;             // candidates per workgroup and tile
+
+typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef float f2_t __attribute__((ext_vector_type(2)));
+typedef unsigned u2_t __attribute__((ext_vector_type(2)));
+typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+
+// Two floats as packed bf16 (round to nearest even); the floats become the
+// (exact) remainders, x - 1.0 * low and y - 1.0 * high by the two-term bf16
+// dot product.  neg = {(-1, 0), (0, -1)} must come from registers: given as
+// constants the compiler writes (-1, 0) as the inline operand -1.0, which the
+// instruction reads as (0, -1) (seen in a comparison with the plain form).
+struct NegPairs {
+  unsigned lo = 0x0000bf80u, hi = 0xbf800000u;
+  __device__ NegPairs() { asm volatile("" : "+s"(lo), "+s"(hi)); }
+};
+__device__ inline unsigned split_bf16(float& x, float& y, const NegPairs& neg) {
+  const bf2_t p = __builtin_convertvector(f2_t{x, y}, bf2_t);
+  x = __builtin_amdgcn_fdot2_f32_bf16(p, __builtin_bit_cast(bf2_t, neg.lo), x, false);
+  y = __builtin_amdgcn_fdot2_f32_bf16(p, __builtin_bit_cast(bf2_t, neg.hi), y, false);
+  return __builtin_bit_cast(unsigned, p);
 }
-__device__ inline void load_b16f(f4_t (&b)[4], const f4_t* ks, int J, int lane) {
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) b[ct] = ks[(J * 4 + ct) * 64 + lane];
+__device__ inline unsigned pack_bf16(float x, float y) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(f2_t{x, y}, bf2_t));
+}
+__device__ inline void mfma_bf16(const u4_t& a, const u4_t& b, f16_t& c) {
+  c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8_t, a), __builtin_bit_cast(bf8_t, b), c, 0, 0, 0);
 }
 
-// Where V goes when it is kept (the sequential believer needs it): row-major,
-// rows = observations in their order, row stride ld.
-struct VStore {
-  float* v;
-  int64_t ld;
-  int64_t c0;  // first candidate of the tile
-  int64_t n;
+// LDS of a workgroup: K* parts, the candidates' augmented rows, the next
+// tile's coordinates, the reductions.
+template <int S, int RS>
+struct PostLds {
+  u4_t b[RS == 1 ? 1 : 2][2][3][64];  // [buffer][32-candidate tile][part][lane]
+  double bq[4][S][64];                // [16-candidate tile][step][lane]
+  float xb[4][S][64];
+  double sq[RS][64], mu[64];
+  double scale[S * 4];
 };
 
-// Completes a row block: squared norms of its V columns into sq[ct], the
-// block itself into V when kept, and clears the accumulators for the next row.
-template <bool KEEP_V>
-__device__ inline void finish_row16(f4_t (&acc)[4], float (&sq)[4], const VStore& vs, int I, int lane) {
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    float p = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float v = acc[ct][r];
-      if constexpr (KEEP_V) {
-        const int64_t cand = vs.c0 + ct * 16 + (lane & 15);
-        const int64_t row = 16 * I + 4 * (lane >> 4) + r;
-        if (cand < vs.n) vs.v[row * vs.ld + cand] = v;
-      }
-      p = fmaf(v, v, p);
-    }
-    sq[ct] += p;
-    acc[ct] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-}
-
-// One tile's pass over the wave's blocks, one block of read-ahead of both
-// operands in two fixed register sets.  The A stream is the same for every
-// tile, so its read-ahead wraps: on entry ax holds the wave's first block,
-// and on exit it holds it again for the next tile.
-template <bool KEEP_V>
-__device__ inline void wave_tile16f(const f4_t* __restrict__ ap, const f4_t* ks, uint64_t lo, uint64_t hi, int count,
-                                    int lane, f4_t& ax, float (&sq)[4], const VStore& vs) {
-  // the accumulators start each row at zero (finish_row16 clears them)
-  f4_t acc[4];
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  constexpr uint64_t kMask = (1u << kRowBits16) - 1;
-  int I = (int)(lo & kMask), J = 0;
-  auto next_j = [&](int j, int i) { return j == i ? 0 : j + 1; };
-  auto advance = [&]() {
-    if (J == I) {
-      finish_row16<KEEP_V>(acc, sq, vs, I, lane);
-      J = 0;
-      lo = (lo >> kRowBits16) | (hi << (64 - kRowBits16));
-      hi >>= kRowBits16;
-      I = (int)(lo & kMask);
-    } else {
-      ++J;
-    }
-  };
-  f4_t ay, bx[4], by[4];
-  load_b16f(bx, ks, 0, lane);
-  const f4_t* kl = ks + lane;
-  int k = 0;
-  for (; k + 1 < count; k += 2) {
-    mfma_block16f(acc, ax, bx, by, kl + next_j(J, I) * 256, ay, ap + (size_t)(k + 1) * 64);
-    __builtin_amdgcn_sched_barrier(0);
-    advance();
-    mfma_block16f(acc, ay, by, bx, kl + next_j(J, I) * 256, ax, ap + (size_t)(k + 2 < count ? k + 2 : 0) * 64);
-    __builtin_amdgcn_sched_barrier(0);
-    advance();
-  }
-  if (k < count) {
-    mfma_block16f(acc, ax, bx, by, kl + next_j(J, I) * 256, ay, ap);
-    __builtin_amdgcn_sched_barrier(0);
-    advance();
-    ax = ay;
-  }
-}
-
-// Persistent: workgroup g takes tiles g, g + G, g + 2G, ... (G = grid size),
-// so the inverse-factor stream and the next tile's coordinates are in flight
-// across tile boundaries.  Phase 1: wave w takes the 16-observation blocks
-// J = w, w + WAVES, ...  Phase 2: the wave's row blocks from the plan.
-// Phase 3: partial norms and means summed per candidate.
-template <int WAVES, int D, bool KEEP_V>
-__global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void posterior_f32_kernel(
-    const float* __restrict__ Xc, const f4_t* __restrict__ linv, const double* __restrict__ xq,
+// S: fp64 MFMA steps of the distances; RS: waves that share a tile's rows;
+// NBW: slots per wave; KA: register sets for units of L^-1; WPS: waves per SIMD
+// that the register budget is set for.
+template <int S, int RS, int NBW, int KA, int WPS, bool KEEP_V>
+__global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
+    const float* __restrict__ Xc, const unsigned char* __restrict__ linv, const double* __restrict__ xq,
     const float* __restrict__ alpha, float* __restrict__ mu_out, float* __restrict__ sd_out,
     float* __restrict__ ei_out, float* __restrict__ v_out, const Post32 a) {
-  constexpr int S = (D + 2 + 3) / 4;  // fp64 MFMA steps of the augmented rows
-  extern __shared__ __align__(16) unsigned char smem[];
-  f4_t* ks = reinterpret_cast<f4_t*>(smem);  // [nb16][4 ct][64 lanes] float4
-  const int nb16 = a.nb16;
-  float* sig_red = reinterpret_cast<float*>(ks + (size_t)nb16 * 4 * 64);  // [WAVES][4 ct][16]
-  float* mu_red = sig_red + WAVES * 64;                                    // [WAVES][4 ct][16]
-
+  constexpr int CT = 4 / RS;      // 16-candidate tiles whose K* this wave makes
+  constexpr int NP = 2 * CT;      // pieces of that work, two observations each
+  constexpr int PPS = (NP + NBW - 1) / NBW;  // pieces beside a slot, in order
+  const NegPairs neg;
+  __shared__ PostLds<S, RS> sm;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int g = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t n_tiles = (a.n + 63) >> 6;
+  // Two workgroups of a CU own their slots in opposite orders, since the first
+  // slots live longest (workgroups gridDim / 2 apart usually share a CU).
+  const int r = blockIdx.x >= (gridDim.x + 1) / 2 ? RS - 1 - wave : wave;
+  const int64_t n_tiles = (a.n + kPostTile - 1) / kPostTile;
+  auto sync = [&]() {
+    if constexpr (RS > 1) __syncthreads();
+  };
 
-  // Plan entry of this wave.  With 8 waves, entries p and p + 4 are meant to
-  // share a SIMD: each wave takes simd + 4 * (its arrival order on the SIMD),
-  // unless the workgroup did not land as two waves per SIMD; then entry =
-  // wave.  Either way every entry is taken exactly once.
-  int p = wave;
-  if constexpr (WAVES == 8) {
-    int* on_simd = reinterpret_cast<int*>(mu_red + WAVES * 64);  // [4]
-    if (tid < 4) on_simd[tid] = 0;
-    __syncthreads();
-    const int simd = (int)((__builtin_amdgcn_s_getreg((31 << 11) | 4) >> 4) & 3);  // HW_ID.SIMD_ID
-    int slot = 0;
-    if (lane == 0) slot = atomicAdd(&on_simd[simd], 1);
-    slot = __shfl(slot, 0);
-    __syncthreads();
-    if (on_simd[0] == 2 && on_simd[1] == 2 && on_simd[2] == 2 && on_simd[3] == 2) p = simd + 4 * slot;
-    p = __builtin_amdgcn_readfirstlane(p);
-  }
-  const uint64_t rows_lo = a.plan.lo[p], rows_hi = a.plan.hi[p];
-  const int count = a.plan.blk_start[p + 1] - a.plan.blk_start[p];
-  const f4_t* ap = linv + (size_t)a.plan.blk_start[p] * 64 + lane;
-  f4_t ax = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (count > 0) ax = ap[0];
+  if (tid < S * 4) sm.scale[tid] = tid < a.d ? a.scale[min(tid, SCOOT_MAX_DIM - 1)] : 0.0;
+  __syncthreads();
 
-  // The lane's components of the candidates' augmented rows: step s of the
-  // cross-term chain reads component k = 4s + g.
-  double wk[S];
+  // ---- this wave's 16-candidate tiles: coordinates and augmented rows -------
+  // step s of the distance chain reads component k = 4s + g
+  float xr[CT][S];
+  auto load_x = [&](int64_t t) {
 #pragma unroll
-  for (int s = 0; s < S; ++s) wk[s] = 4 * s + g < D ? a.scale[4 * s + g] : 0.0;
-
-  int64_t tile = blockIdx.x;
-  float xr[D];  // candidate tile * 64 + lane, for its squared norm
-  float xb[4][S];  // component 4s + g of candidate 16 ct + c (raw float)
-  auto load_tile = [&](int64_t t) {
-    const int64_t own = min(t * 64 + lane, a.n - 1);
+    for (int q = 0; q < CT; ++q) {
+      const int64_t cand = min(t * kPostTile + (wave * CT + q) * 16 + c, a.n - 1);
 #pragma unroll
-    for (int q = 0; q < D; ++q) xr[q] = Xc[own * D + q];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const int64_t cand = min(t * 64 + ct * 16 + c, a.n - 1);
-#pragma unroll
-      for (int s = 0; s < S; ++s) xb[ct][s] = 4 * s + g < D ? Xc[cand * D + min(4 * s + g, D - 1)] : 0.0f;
+      for (int s = 0; s < S; ++s) xr[q][s] = Xc[cand * a.d + min(4 * s + g, a.d - 1)];
     }
   };
-  load_tile(tile);
-
-  for (; tile < n_tiles; tile += gridDim.x) {
-    const int64_t c0 = tile * 64;
-    // squared norm of the lane's own candidate, then the B operands
-    double nrm = 0.0;
+  auto store_x = [&]() {
 #pragma unroll
-    for (int q = 0; q < D; ++q) {
-      const double t = (double)xr[q] * a.scale[q];
-      nrm = fma(t, t, nrm);
-    }
-    double bq[4][S];
+    for (int q = 0; q < CT; ++q)
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const double nc = __shfl(nrm, ct * 16 + c);
+      for (int s = 0; s < S; ++s) sm.xb[wave * CT + q][s][lane] = xr[q][s];
+  };
+  auto operands = [&]() {
+#pragma unroll
+    for (int q = 0; q < CT; ++q) {
+      double x[S], nrm = 0.0;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        x[s] = (double)sm.xb[wave * CT + q][s][lane] * sm.scale[4 * s + g];
+        if (4 * s + g < a.d) nrm = fma(x[s], x[s], nrm);
+      }
+      nrm += __shfl_xor(nrm, 16);
+      nrm += __shfl_xor(nrm, 32);
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         const int k = 4 * s + g;
-        bq[ct][s] = k < D ? (double)xb[ct][s] * wk[s] : (k == D ? 1.0 : (k == D + 1 ? nc : 0.0));
+        sm.bq[wave * CT + q][s][lane] = k < a.d ? x[s] : (k == a.d ? 1.0 : (k == a.d + 1 ? nrm : 0.0));
       }
     }
-    // next tile's coordinates, in flight during this one
-    const int64_t next = tile + gridDim.x;
-    if (next < n_tiles) load_tile(next);
+  };
 
-    // The K* generation runs at a raised wave priority and the product at
-    // the normal one: where the CU's two workgroups are in different phases,
-    // the one generating is served first and reaches its product sooner, so
-    // that the SIMDs less often wait with both in the same phase (measured:
-    // 2-3% less time per launch at m = 256).
-    __builtin_amdgcn_s_setprio(2);
-    // ---- phase 1: K* of observation blocks J = wave, wave + WAVES, ... ---
-    // The block's operands are loaded one block ahead; its four column
-    // tiles' chains are issued interleaved (independent accumulators), then
-    // their values are turned into K*.
-    float mu_part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    double aq[S];
-    f4_t al = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (wave < nb16) {
+  // ---- K* of an observation block, in pieces ---------------------------------
+  // Piece 2q makes the distances of tile q and its first two observations'
+  // values, piece 2q + 1 the other two and the LDS writes.
+  double aq[S];
+  f4_t al;
+  auto load_obs = [&](int j) {
 #pragma unroll
-      for (int s = 0; s < S; ++s) aq[s] = xq[((size_t)wave * S + s) * 64 + lane];
-      al = *reinterpret_cast<const f4_t*>(alpha + 16 * wave + 4 * g);
-    }
-    for (int J = wave; J < nb16; J += WAVES) {
-      d4_t cr[4];
+    for (int s = 0; s < S; ++s) aq[s] = (xq + (size_t)j * S * 64)[(unsigned)(s * 64 + lane)];
+    al = reinterpret_cast<const f4_t*>(alpha + 16 * j)[(unsigned)g];
+  };
+  double mu_acc[CT];
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) cr[ct] = d4_t{0.0, 0.0, 0.0, 0.0};
+  for (int q = 0; q < CT; ++q) mu_acc[q] = 0.0;
+  d4_t cr;
+  float m_part;
+  unsigned pk[3][2];
+  auto piece = [&](int p, int to_buf) {
+    const int q = p >> 1, h = p & 1;
+    if (h == 0) {
+      cr = d4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int s = 0; s < S; ++s)
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) cr[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], bq[ct][s], cr[ct], 0, 0, 0);
-      const f4_t alj = al;
-      const int Jn = J + WAVES < nb16 ? J + WAVES : J;
-#pragma unroll
-      for (int s = 0; s < S; ++s) aq[s] = xq[((size_t)Jn * S + s) * 64 + lane];
-      al = *reinterpret_cast<const f4_t*>(alpha + 16 * Jn + 4 * g);
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        f4_t kv;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float u = __builtin_amdgcn_sqrtf(fmaxf((float)(-cr[ct][r]), 0.0f));
-          const float kval = fmaf(u, fmaf(u, a.c2, a.c1), a.c0) * __builtin_amdgcn_exp2f(-u);
-          kv[r] = kval;
-          mu_part[ct] = fmaf(kval, alj[r], mu_part[ct]);
-        }
-        ks[(J * 4 + ct) * 64 + lane] = kv;
-      }
+        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], sm.bq[wave * CT + q][s][lane], cr, 0, 0, 0);
+      m_part = 0.0f;
     }
-    __syncthreads();
+    float kv[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float u = __builtin_amdgcn_sqrtf(fmaxf((float)(-cr[2 * h + i]), 0.0f));
+      kv[i] = fmaf(u, fmaf(u, a.c2, a.c1), a.c0) * __builtin_amdgcn_exp2f(-u);
+      m_part = fmaf(kv[i], al[2 * h + i], m_part);
+    }
+    pk[0][h] = split_bf16(kv[0], kv[1], neg);
+    pk[1][h] = split_bf16(kv[0], kv[1], neg);
+    pk[2][h] = pack_bf16(kv[0], kv[1]);
+    if (h == 1) {
+      mu_acc[q] += (double)m_part;
+      const int ct = wave * CT + q;
+      u4_t* to = &sm.b[to_buf][ct >> 1][0][(g >> 1) * 32 + (ct & 1) * 16 + c];
+#pragma unroll
+      for (int part = 0; part < 3; ++part)
+        reinterpret_cast<u2_t*>(to + part * 64)[g & 1] = u2_t{pk[part][0], pk[part][1]};
+    }
+  };
 
-    __builtin_amdgcn_s_setprio(0);
-    // ---- phase 2: this wave's row blocks of V = L^-1 K*^T -----------------
-    float sq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (count > 0) {
-      const VStore vs{v_out, a.v_ld, c0, a.n};
-      wave_tile16f<KEEP_V>(ap, ks, rows_lo, rows_hi, count, lane, ax, sq, vs);
-    }
+  // ---- L^-1 ----------------------------------------------------------------
+  // Register set k holds the units of slots k, k + KA, ... one after the other,
+  // and then block j + 1's of slot k (the next tile's block 0 once that slot
+  // has died).  Every index is within the stream.
+  u4_t au[KA][3];
+  auto load_unit = [&](int k, int unit) {
+    const u4_t* at = reinterpret_cast<const u4_t*>(linv + (size_t)unit * kUnitBytes);
+#pragma unroll
+    for (int part = 0; part < 3; ++part) au[k][part] = at[(unsigned)(part * 64 + lane)];
+  };
+  auto first_unit = [&](int k) { return min(r + RS * k, a.nb32 - 1); };
 
-    // ---- phase 3: reduce over the four lane rows, the waves, write ---------
+  int64_t tile = blockIdx.x;
+  load_x(tile);
+  store_x();
+  load_obs(0);
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      sq[ct] += __shfl_xor(sq[ct], 16);
-      sq[ct] += __shfl_xor(sq[ct], 32);
-      mu_part[ct] += __shfl_xor(mu_part[ct], 16);
-      mu_part[ct] += __shfl_xor(mu_part[ct], 32);
-    }
-    if (g == 0) {
+  for (int k = 0; k < KA; ++k) load_unit(k, first_unit(k));
+  operands();
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        sig_red[(wave * 4 + ct) * 16 + c] = sq[ct];
-        mu_red[(wave * 4 + ct) * 16 + c] = mu_part[ct];
-      }
-    }
-    __syncthreads();
-    if (tid < 64) {
-      const int64_t cand = c0 + tid;
-      if (cand < a.n) {
-        double ss = 0.0, mm = 0.0;
+  for (int p = 0; p < NP; ++p) piece(p, 0);
+  int buf = 0;  // the buffer that holds K* of the block being multiplied
+  load_obs(a.nj > 1 ? 1 : 0);
+  load_x(tile + gridDim.x);
+  store_x();
+  f16_t acc[NBW][2];
+
+  for (; tile < n_tiles; tile += gridDim.x) {
+    const int64_t c0 = tile * kPostTile;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-          ss += (double)sig_red[w * 64 + tid];
-          mm += (double)mu_red[w * 64 + tid];
+    for (int t = 0; t < NBW; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][0][i] = acc[t][1][i] = 0.0f;
+
+    int off = 0;  // first unit of block j
+#pragma unroll 1
+    for (int j = 0; j < a.nj; ++j) {
+      const int live = a.nb32 - (j >> 1);
+      sync();  // K* of block j is in LDS
+      u4_t bc[2][3];
+#pragma unroll
+      for (int part = 0; part < 3; ++part)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) bc[h][part] = sm.b[buf][h][part][lane];
+      if constexpr (RS > 1) buf ^= 1;
+      // block to generate beside this product, and the one after it
+      int jn = j + 1;
+      const int cur = off;
+      off += live;
+      int noff = off, nlive = a.nb32 - (jn >> 1);
+      if (jn == a.nj) {
+        // every K* of this tile is made: its mean is complete, and the next
+        // tile's first block is generated beside this tile's last rows
+#pragma unroll
+        for (int q = 0; q < CT; ++q) {
+          mu_acc[q] += __shfl_xor(mu_acc[q], 16);
+          mu_acc[q] += __shfl_xor(mu_acc[q], 32);
+          if (g == 0) sm.mu[(wave * CT + q) * 16 + c] = mu_acc[q];
+          mu_acc[q] = 0.0;
         }
-        const double sd = sqrt(fmax(a.s2 - ss, 0.0));
-        const double mu = a.prior + mm;
-        mu_out[cand] = (float)mu;
-        sd_out[cand] = (float)sd;
-        if (ei_out) ei_out[cand] = (float)partial_expectation_d(a.ei_c, (double)(float)mu, (double)(float)sd);
+        operands();
+        jn = 0;
+        noff = 0;
+        nlive = a.nb32;
       }
+#pragma unroll
+      for (int t = 0; t < NBW; ++t) {
+        if (r + RS * t < live) {
+          // the matrix phases go first: the other waves' vector work fills the
+          // gaps between their instructions (3-4% per launch)
+          __builtin_amdgcn_s_setprio(2);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][2], bc[h][0], acc[t][h]);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][0], bc[h][2], acc[t][h]);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][1], bc[h][1], acc[t][h]);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][1], bc[h][0], acc[t][h]);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][0], bc[h][1], acc[t][h]);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][0], bc[h][0], acc[t][h]);
+          {
+            const int k = t % KA, sn = r + RS * k;  // the set, and its first slot
+            int unit = sn < nlive ? noff + sn : first_unit(k);
+            if (t + KA < NBW && r + RS * (t + KA) < live) unit = cur + r + RS * (t + KA);
+            load_unit(k, unit);
+          }
+#pragma unroll
+          for (int p = t * PPS; p < NP && p < (t + 1) * PPS; ++p) piece(p, buf);
+          __builtin_amdgcn_s_setprio(0);
+          asm volatile("; slot %0" ::"i"(t));  // keeps the two copies of the pieces apart
+        } else {
+#pragma unroll
+          for (int p = t * PPS; p < NP && p < (t + 1) * PPS; ++p) piece(p, buf);
+        }
+      }
+      load_obs(jn + 1 < a.nj ? jn + 1 : 0);
+    }
+    // ---- squared norms of the columns -----------------------------------------
+    load_x(tile + 2 * (int64_t)gridDim.x);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      double sq = 0.0;
+#pragma unroll
+      for (int t = 0; t < NBW; ++t) {
+        if (r + RS * t < a.nb32) {
+          float q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int i = 0; i < 16; ++i) q[i & 3] = fmaf(acc[t][h][i], acc[t][h][i], q[i & 3]);
+          sq += (double)((q[0] + q[1]) + (q[2] + q[3]));
+          if constexpr (KEEP_V) {
+            const int64_t cand = c0 + h * 32 + (lane & 31);
+            float* v = v_out + (32 * (a.nb32 - 1 - (r + RS * t)) + 4 * (lane >> 5)) * a.v_ld + cand;
+            if (cand < a.n) {
+#pragma unroll
+              for (int i = 0; i < 16; ++i) {
+                *v = acc[t][h][i];
+                v += (i & 3) == 3 ? 5 * a.v_ld : a.v_ld;
+              }
+            }
+          }
+        }
+      }
+      sq += __shfl_xor(sq, 32);
+      if (lane < 32) sm.sq[wave][h * 32 + lane] = sq;
+    }
+    store_x();
+    sync();
+    const int64_t cand = c0 + lane;
+    if (wave == 0 && cand < a.n) {
+      double sq = 0.0;
+#pragma unroll
+      for (int w = 0; w < RS; ++w) sq += sm.sq[w][lane];
+      const double sd = sqrt(fmax(a.s2 - sq, 0.0));
+      const double mu = a.prior + sm.mu[lane];
+      mu_out[cand] = (float)mu;
+      sd_out[cand] = (float)sd;
+    }
+  }
+  // The EI of the candidates whose mean and deviation this lane has written;
+  // in a loop of its own, so that the constants of erfc and exp hold no
+  // registers beside the accumulators.
+  if (ei_out && wave == 0) {
+    for (tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+      const int64_t cand = tile * kPostTile + lane;
+      if (cand < a.n) ei_out[cand] = (float)partial_expectation_d(a.ei_c, (double)mu_out[cand], (double)sd_out[cand]);
     }
   }
 }
@@ -610,6 +655,58 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void posterior_f64_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// Packing of a device factorization for the fp32 kernel, as pack_linv_f32 does
+// on the host: one wave per unit, eight entries (64 contiguous bytes of a
+// factor block) per lane.  It replaces the read-back of L^-1, the host packing
+// and the upload (m = 300: 0.7 MiB down and 0.33 MiB up).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(64) void pack_f32_kernel(const double* __restrict__ Xi, int nbf,
+                                                      const double* __restrict__ alpha, int m, int nb32,
+                                                      u4_t* __restrict__ linv, double* __restrict__ alpha64,
+                                                      float* __restrict__ alpha32) {
+  const int j = blockIdx.x, P = blockIdx.y, lane = threadIdx.x;
+  if (j == 0 && P == 0) {
+    for (int i = lane; i < nb32 * 32; i += 64) {
+      const double v = i < m ? alpha[i] : 0.0;
+      alpha64[i] = v;
+      alpha32[i] = (float)v;
+    }
+  }
+  if (P < j / 2) return;
+  // the units before block j's, then row blocks from the last one down
+  const int unit = j * nb32 - (j - 1) * (j - 1) / 4 + nb32 - 1 - P;
+  const int row = 32 * P + (lane & 31), col = 16 * j + 8 * (lane >> 5);
+  u4_t part[3];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    double v[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int c = col + 2 * i + q;
+      v[q] = row < m && c <= row ? Xi[((size_t)(row >> 4) * nbf + (c >> 4)) * 256 + (row & 15) * 16 + (c & 15)] : 0.0;
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const unsigned w = pack_bf16((float)v[0], (float)v[1]);
+      part[p][i] = w;
+      v[0] -= (double)__builtin_bit_cast(float, w << 16);
+      v[1] -= (double)__builtin_bit_cast(float, w & 0xffff0000u);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < 3; ++p) linv[((size_t)unit * 3 + p) * 64 + lane] = part[p];
+}
+
+int launch_pack_f32(const double* Xi, int nbf, const double* alpha, int m, int nb32, void* linv, double* alpha64,
+                    float* alpha32, void* stream) {
+  hipLaunchKernelGGL(pack_f32_kernel, dim3((unsigned)((m + 15) / 16), (unsigned)nb32), dim3(64), 0,
+                     (hipStream_t)stream, Xi, nbf, alpha, m, nb32, (u4_t*)linv, alpha64, alpha32);
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return fail(SCOOT_ERR_DEVICE, std::string("gp fit: pack launch: ") + hipGetErrorString(err));
+  return SCOOT_OK;
+}
+
+// ---------------------------------------------------------------------------
 // Input warping of the pool (fp32 path): every coordinate through
 // w = 1 - (1 - x^a_k)^b_k, x clamped to [0, 1], in float and without
 // cancellation: ln x from log1p(x - 1) above 1/2 (x - 1 exact there),
@@ -665,19 +762,23 @@ int64_t persistent_grid(const void* kern, int threads, size_t lds, int64_t tiles
   return std::min(tiles, (int64_t)cus * per_cu);
 }
 
-template <int WAVES, int D, bool KEEP_V>
+template <int S, int RS, int NBW, int KA, int WPS, bool KEEP_V>
 int run32(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, float* ei, float* v_out,
           const Post32& a, hipStream_t s) {
-  // K* tile, per-wave partial norms and means, four SIMD counters
-  const size_t lds = (size_t)a.nb16 * 4 * 64 * 16 + 2 * WAVES * 64 * 4 + 16;
-  auto kern = posterior_f32_kernel<WAVES, D, KEEP_V>;
-  const int rc = allow_full_lds((const void*)kern, "posterior");
-  if (rc != SCOOT_OK) return rc;
-  const int64_t grid = persistent_grid((const void*)kern, WAVES * 64, lds, (n + 63) / 64);
+  auto kern = posterior_f32_kernel<S, RS, NBW, KA, WPS, KEEP_V>;
+  const int64_t grid = persistent_grid((const void*)kern, RS * 64, 0, (n + kPostTile - 1) / kPostTile);
   if (grid < 1) return fail(SCOOT_ERR_DEVICE, "posterior: workgroup does not fit on a compute unit");
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WAVES * 64), lds, s, Xc,
-                     (const f4_t*)g.linv, (const double*)g.xs, g.alpha32, mu, sd, ei, v_out, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(RS * 64), 0, s, Xc, (const unsigned char*)g.linv,
+                     (const double*)g.xs, g.alpha32, mu, sd, ei, v_out, a);
   return SCOOT_OK;
+}
+template <int S, bool KEEP_V>
+int run32_by_rows(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, float* ei, float* v_out,
+                  const Post32& a, hipStream_t s) {
+  if (a.nb32 <= 4) return run32<S, 2, 2, 2, 3, KEEP_V>(g, Xc, n, mu, sd, ei, v_out, a, s);
+  if (a.nb32 <= 8) return run32<S, 2, 4, 3, 2, KEEP_V>(g, Xc, n, mu, sd, ei, v_out, a, s);
+  if (a.nb32 <= 16) return run32<S, 4, 4, 4, 2, KEEP_V>(g, Xc, n, mu, sd, ei, v_out, a, s);
+  return run32<S, 4, 5, 2, 2, KEEP_V>(g, Xc, n, mu, sd, ei, v_out, a, s);
 }
 
 template <int WAVES, int D>
@@ -725,7 +826,8 @@ int launch_posterior(const GPDevice& g, const float* Xc, int64_t n, void* mu, vo
     Post32 a{};
     a.n = n;
     a.d = g.d;
-    a.nb16 = g.m_pad / kBlk16;
+    a.nj = (g.m + 15) / 16;
+    a.nb32 = g.nb;
     for (int k = 0; k < SCOOT_MAX_DIM; ++k) a.scale[k] = g.scale64[k];
     a.c0 = g.coef32[0];
     a.c1 = g.coef32[1];
@@ -733,19 +835,17 @@ int launch_posterior(const GPDevice& g, const float* Xc, int64_t n, void* mu, vo
     a.s2 = g.s2;
     a.prior = g.c;
     a.ei_c = ei_c ? *ei_c : 0.0;
-    a.plan = plan_rows16(a.nb16, posterior_waves(g.nb));
     a.v_ld = v_ld > 0 ? v_ld : n;
-    for (int e = 0; e < 8; ++e)
-      if (a.plan.nrows[e] > kMaxRows16) return fail(SCOOT_ERR_UNSUPPORTED, "posterior: row plan does not pack");
     float* e = ei_c ? (float*)ei : nullptr;
-    rc = by_d_rec<1>(g.d, [&](auto Dc) {
-      constexpr int D = decltype(Dc)::value;
-      float *m32 = (float*)mu, *s32 = (float*)sigma;
-      if (posterior_waves(g.nb) == 8)
-        return v_out ? run32<8, D, true>(g, Xc, n, m32, s32, e, v_out, a, s)
-                     : run32<8, D, false>(g, Xc, n, m32, s32, e, nullptr, a, s);
-      return v_out ? run32<4, D, true>(g, Xc, n, m32, s32, e, v_out, a, s)
-                   : run32<4, D, false>(g, Xc, n, m32, s32, e, nullptr, a, s);
+    rc = by_d_rec<1>((g.d + 2 + 3) / 4, [&](auto Sc) {
+      constexpr int S = decltype(Sc)::value;
+      if constexpr (S > (SCOOT_MAX_DIM + 5) / 4) {
+        return fail(SCOOT_ERR_UNSUPPORTED, "posterior: d exceeds SCOOT_MAX_DIM");
+      } else {
+        float *m32 = (float*)mu, *s32 = (float*)sigma;
+        return v_out ? run32_by_rows<S, true>(g, Xc, n, m32, s32, e, v_out, a, s)
+                     : run32_by_rows<S, false>(g, Xc, n, m32, s32, e, nullptr, a, s);
+      }
     });
   } else {
     Post64 a{};
