@@ -379,14 +379,15 @@ int scoot_score_pool_ex(const scoot_gp* gps, int p, scoot_forest f, const uint8_
  * pick maximises EHVI (Eq. 9, p = 1..3) over the feasible (Eq. 3 with delta;
  * f nullable: all feasible), not yet picked candidates; the pick then joins
  * the observations with its posterior mean as a fantasy value and noise
- * tau^2: the Cholesky factor is extended by one row, V = L^-1 K*^T gains the
- * row (k(x, x_p) - v_p^T V[:, x]) / d, sigma^2 drops by its square, the mean
- * stays, and the front gains the fantasy.  Ties go to the lowest index.
+ * tau^2: the Cholesky factor is extended by one row, sigma^2 drops by the
+ * square of the new row of L^-1 K*^T, the mean stays, and the front gains the
+ * fantasy.  Ties go to the lowest index.
  *
  * gps: p fp32 handles (fp64: UNSUPPORTED) sharing d.  Xc [n*d] device.
  * Y_obs [m_obs*p], ref [p]: host.  workspace: device, at least the size
- * scoot_suggest_kb_workspace returns (it holds V of every objective: about
- * 4 (m + q) n p bytes); NULL: the library allocates and frees it in the call.
+ * scoot_suggest_kb_workspace returns (about 4 (m + q) n p bytes, more than the
+ * call touches); NULL: the library allocates what it needs, some 4 n (4 p + 4)
+ * bytes up to nine picks and 4 n p more per pick above, and frees it in the call.
  * picks [q], pick_acq [q] (nullable), n_picked: HOST outputs — the call
  * synchronises `stream` after every pick.  Fewer than q feasible candidates:
  * *n_picked < q and the tail of picks is untouched.

@@ -356,13 +356,11 @@ int allow_full_lds(const void* kernel, const char* what);
 int upload_async(void* dst, const void* src, size_t bytes, int slot, void* stream);
 
 // ---- launchers (device) -----------------------------------------------------
-// v_out (nullable, fp32 handles only): V = L^-1 K*^T, m_pad rows of n floats.
 // With input warping (g.warp) the pool is warped first (fp32: into scratch by
 // launch_warp_pool; fp64: inside the kernel), unless xc_warped says Xc already is.
 int launch_posterior(const GPDevice& g, const float* Xc, int64_t n, void* mu, void* sigma,
                      const double* ei_c /* nullable: fused EI with c = best + xi */, void* ei,
-                     void* stream, float* v_out = nullptr, bool xc_warped = false,
-                     int64_t v_ld = 0 /* row stride of v_out; 0: n */);
+                     void* stream, bool xc_warped = false);
 // The units of pack_linv_f32 and alpha's two copies (m_pad entries), from a
 // factorization's L^-1 blocks on the device.
 int launch_pack_f32(const double* Xi, int nbf, const double* alpha, int m, int nb32, void* linv, double* alpha64,
@@ -405,7 +403,8 @@ int launch_pareto_front3(const void* a, const void* b, const void* c, const uint
                          uint8_t* front, int32_t* n_front, void* stream);
 
 // Sequential Kriging-believer picks (fp32 GPs only).
-size_t kb_workspace_bytes(const GPDevice* const* g, int p, int64_t n, int q);
+size_t kb_workspace_bytes(const GPDevice* const* g, int p, int64_t n, int q);  // as reported
+size_t kb_needed_bytes(const GPDevice* const* g, int p, int64_t n, int q);     // as used
 int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f, const uint8_t* known,
                          int64_t vote_min, const float* Xc, int64_t n, const double* Y_obs, int m_obs, const double* ref, int q, void* ws,
                          int64_t* picks, double* pick_acq, int* n_picked, float* mu_out, float* sigma_out,

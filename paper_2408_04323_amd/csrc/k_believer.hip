@@ -2,150 +2,558 @@
 // parallel suggestion of Sec. 4.6 (the paper takes the top k by EHVI at once).
 //
 // Each pick x_p joins the observations with the fantasy value y = mu(x_p) and
-// the observation noise tau^2.  For a GP with V = L^-1 K*^T kept in memory:
-//   L gains the row [v_p^T  d],  v_p = V[:, p],  d = sqrt(sigma^2(x_p) + tau^2),
-//   V gains the row v_new(x) = (k(x, x_p) - v_p^T V[:, x]) / d,
-//   sigma^2(x) -= v_new(x)^2,  and mu does not move (the fantasy equals it).
-// The front gains mu(x_p) of every objective; EHVI is then re-scored over the
-// whole pool and the next pick is the top-1 of the feasible, not yet picked
-// candidates.  The V row update reads all of V: it is bound by HBM bandwidth.
+// the observation noise tau^2; the mean does not move (the fantasy equals it),
+// the variance drops, the front gains the fantasy, and the next pick maximises
+// EHVI over the feasible, not yet picked candidates.
+//
+// The variance after k picks, from the posterior of the observations alone:
+//   C_p(x)   = k(x, x_p) - beta_p . k(x, X),  beta_p = K^-1 k(X, x_p)
+//   w(x)     = L_S^-1 C(x),   L_S L_S^T = [C_p(x_p')] + tau^2 I
+//   sigma^2  = sigma_0^2 - |w|^2
+// so a candidate needs its m covariances once and k dot products with them,
+// and nothing is kept per candidate between the picks.
+//
+// Only candidates that can win are scored again.  EHVI never grows from one
+// pick to the next: the hypervolume improvement is convex in every objective
+// (along one axis its slope is minus the open cross-section, which shrinks as
+// the axis grows), so a smaller variance at the same mean lowers its
+// expectation, and a larger front lowers it everywhere.  Hence every score
+// computed earlier is an upper bound.  Per pick the seven best by bound are
+// scored, the best of them is a lower bound on the maximum, and exactly the
+// candidates whose bound reaches it (less a slack for rounding) are scored
+// too; the pick is the maximum over all bounds, ties to the lowest index.  On
+// the workloads (2^20 candidates, front of about 30) that is tens to a few
+// thousand candidates per pick instead of the pool: a suggestion of eight
+// took 12.4 ms when every pick streamed V = L^-1 K*^T (4.3 GB) from memory.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
 
 namespace scoot {
 
-constexpr int kKbThreads = 256;
+namespace {
 
-// v_p = V[:, pick] (rows entries), and 1 / d with d^2 = sigma(pick)^2 + tau^2.
-__global__ __launch_bounds__(kKbThreads) void kb_gather_kernel(const float* __restrict__ V, int64_t ld, int rows,
-                                                               int64_t pick, const float* __restrict__ sd, double tau2,
-                                                               float* __restrict__ vp, float* __restrict__ dinv) {
-  for (int i = threadIdx.x; i < rows; i += kKbThreads) vp[i] = V[(int64_t)i * ld + pick];
-  if (threadIdx.x == 0) {
-    const double s = (double)sd[pick];
-    dinv[0] = (float)(1.0 / sqrt(s * s + tau2));
-  }
-}
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef double d4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 
-struct KbArgs {
-  int64_t n, ld, pick;
-  int rows, d;
-  float scale[SCOOT_MAX_DIM];
+constexpr int kTop = 8;     // candidates a selection returns: the pick and the next round's first guesses
+constexpr int kPicks = 8;   // picks whose covariances one pass over the observations makes
+constexpr int kListed = 16384;   // list entries scored without waiting for their count
+constexpr double kSlack = 1e-4;  // of the best score, against rounding of the bounds
+
+// One objective: its GP, the pool as the GP sees it, and what the picks left.
+struct KbGp {
+  const unsigned char* linv;  // units of L^-1 (pack_linv_f32)
+  const double* xq;           // augmented observation rows
+  const float* xc;            // pool, n x d, after input warping
+  const float* mu;            // n
+  const float* sd0;           // n: sigma of the observations alone
+  double* v;                  // m_pad: L^-1 k(X, x) of the newest pick
+  double* beta;               // q x m_pad
+  double* ls;                 // q x q: rows of L_S
+  float* w;                   // (q - 1) x ld: w of earlier chunks of picks
+  float* mu_list;             // outputs, per list entry
+  float* sd_list;
+  float* sd_out;              // n
+  double scale[SCOOT_MAX_DIM];
+  double c0d, c1d, c2d, s2, tau2;
   float c0, c1, c2;
+  int m, nj, nb32, m_pad, S;
+};
+struct KbArgs {
+  KbGp g[SCOOT_MAX_OBJECTIVES];
+  const int64_t* picks;  // device, in order
+  int64_t ld;            // row stride of w: the pool's length, or of the first guesses
+  int d, q, p;
 };
 
-// New row of V and the variance downdate, one candidate per thread: each
-// thread reads its column of V sixteen rows at a time with every load issued
-// before the first is used (a wave keeps 16 x 256 bytes in flight), on two
-// accumulation chains.  Measured at n = 2^20, m = 512 against four rows in
-// flight: 2% less time per suggestion; two or four candidates per thread
-// (8- or 16-byte loads, fewer waves) were slower.  The loads are marked
-// non-temporal: V (gigabytes) is streamed once per pick and would only evict
-// what the caches hold (3% less time per suggestion at n = 2^20, m = 512).
-constexpr int kKbRows = 16;
+// k(x, y) in double from scaled coordinates' squared distance.
+__device__ inline double kb_cov(const KbGp& g, double r2) {
+  const double u = sqrt(r2);
+  return fma(u, fma(u, g.c2d, g.c1d), g.c0d) * exp2(-u);
+}
+// Scaled component k of observation i, from the augmented rows (they hold
+// twice the coordinate, in the order pack_obs_f32 documents).
+__device__ inline double kb_obs(const KbGp& g, int i, int k) {
+  const int r = i & 15, t = 4 * (r & 3) + (r >> 2);
+  return 0.5 * g.xq[((size_t)(i >> 4) * g.S + (k >> 2)) * 64 + 16 * (k & 3) + t];
+}
+// Eight consecutive entries of a row of L^-1 (the lane's, of one unit).
+__device__ inline void kb_unit(const KbGp& g, int unit, int lane, double (&a)[8]) {
+  const u4_t* at = reinterpret_cast<const u4_t*>(g.linv + (size_t)unit * 3 * 64 * 16) + lane;
+  const u4_t p0 = at[0], p1 = at[64], p2 = at[128];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    auto lo = [](unsigned w) { return (double)__builtin_bit_cast(float, w << 16); };
+    auto hi = [](unsigned w) { return (double)__builtin_bit_cast(float, w & 0xffff0000u); };
+    a[2 * i] = (lo(p2[i]) + lo(p1[i])) + lo(p0[i]);
+    a[2 * i + 1] = (hi(p2[i]) + hi(p1[i])) + hi(p0[i]);
+  }
+}
+__device__ inline int kb_unit_index(const KbGp& g, int j, int P) {
+  return j * g.nb32 - (j - 1) * (j - 1) / 4 + g.nb32 - 1 - P;
+}
 
-__global__ __launch_bounds__(kKbThreads) void kb_update_kernel(float* __restrict__ V, const float* __restrict__ vp_g,
-                                                               const float* __restrict__ dinv_g,
-                                                               const float* __restrict__ Xc, float* __restrict__ sd,
-                                                               const KbArgs a) {
-  __shared__ float vp[SCOOT_MAX_OBS + SCOOT_MAX_Q + 32];
-  for (int i = threadIdx.x; i < a.rows; i += kKbThreads) vp[i] = vp_g[i];
+// What the host reads back after a selection: the pick (-1: none), how many
+// candidates were listed for it, its score and its means (the fantasies).
+struct KbInfo {
+  int64_t pick;
+  int32_t count;
+  float score, mu[SCOOT_MAX_OBJECTIVES];
+};
+
+// After a selection: the pick joins the list of picks and leaves the pool, the
+// host's figures are gathered, and the list is emptied.
+__global__ void kb_pick_kernel(const KbArgs a, const int64_t* __restrict__ idx, const float* __restrict__ score,
+                               int k, uint8_t* __restrict__ elig, int64_t* __restrict__ picks,
+                               KbInfo* __restrict__ info, int32_t* __restrict__ count) {
+  const int64_t pick = idx[0];
+  const int t = threadIdx.x;
+  if (t == 0) {
+    info->pick = pick;
+    info->count = count[0];
+    info->score = score[0];
+    count[0] = 0;
+    if (pick >= 0) {
+      picks[k] = pick;
+      elig[pick] = 0;
+    }
+  }
+  if (t < a.p && pick >= 0) info->mu[t] = a.g[t].mu[pick];
+}
+__global__ void kb_zero_kernel(int32_t* count) { count[0] = 0; }
+__global__ void kb_unpick_kernel(const int64_t* __restrict__ picks, int k, uint8_t* __restrict__ elig) {
+  elig[picks[k]] = 1;
+}
+
+// v = L^-1 k(X, x_k), one row block of 32 per workgroup.
+__global__ __launch_bounds__(256) void kb_v_kernel(const KbArgs a, int k) {
+  const KbGp& g = a.g[blockIdx.y];
+  __shared__ double ks[SCOOT_MAX_OBS + 32];
+  __shared__ double part[4][32];
+  const int P = blockIdx.x;
+  if (P >= g.nb32) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float* x = g.xc + a.picks[k] * a.d;
+  const int cols = min(32 * P + 32, g.nj * 16);
+  for (int i = tid; i < cols; i += 256) {
+    double r2 = 0.0;
+    for (int q = 0; q < a.d; ++q) {
+      const double t = (double)x[q] * g.scale[q] - kb_obs(g, i, q);
+      r2 = fma(t, t, r2);
+    }
+    ks[i] = i < g.m ? kb_cov(g, r2) : 0.0;
+  }
   __syncthreads();
-  const float dinv = dinv_g[0];
-  const float* xp = Xc + a.pick * a.d;
-  for (int64_t x = (int64_t)blockIdx.x * kKbThreads + threadIdx.x; x < a.n; x += (int64_t)gridDim.x * kKbThreads) {
-    const float* col = V + x;
-    float acc0 = 0.0f, acc1 = 0.0f;
-    int i = 0;
-    for (; i + kKbRows - 1 < a.rows; i += kKbRows) {
-      float v[kKbRows];
+  double acc = 0.0;
+  for (int j = wave; j < min(2 * P + 2, g.nj); j += 4) {
+    double l[8];
+    kb_unit(g, kb_unit_index(g, j, P), lane, l);
 #pragma unroll
-      for (int r = 0; r < kKbRows; ++r) v[r] = __builtin_nontemporal_load(&col[(int64_t)(i + r) * a.ld]);
+    for (int i = 0; i < 8; ++i) acc = fma(l[i], ks[16 * j + 8 * (lane >> 5) + i], acc);
+  }
+  acc += __shfl_xor(acc, 32);
+  if (lane < 32) part[wave][lane] = acc;
+  __syncthreads();
+  if (tid < 32) g.v[32 * P + tid] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+}
+
+// beta_k = L^-T v, one block of 16 columns per workgroup.
+__global__ __launch_bounds__(256) void kb_beta_kernel(const KbArgs a, int k) {
+  const KbGp& g = a.g[blockIdx.y];
+  __shared__ double part[4][16];
+  const int j = blockIdx.x;
+  if (j >= g.nj) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double acc[8] = {};
+  for (int P = j / 2 + wave; P < g.nb32; P += 4) {
+    double l[8];
+    kb_unit(g, kb_unit_index(g, j, P), lane, l);
+    const double v = g.v[32 * P + (lane & 31)];
 #pragma unroll
-      for (int r = 0; r < kKbRows; r += 2) {
-        acc0 = fmaf(vp[i + r], v[r], acc0);
-        acc1 = fmaf(vp[i + r + 1], v[r + 1], acc1);
+    for (int i = 0; i < 8; ++i) acc[i] = fma(l[i], v, acc[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    for (int o = 16; o >= 1; o >>= 1) acc[i] += __shfl_xor(acc[i], o);
+    if ((lane & 31) == 0) part[wave][8 * (lane >> 5) + i] = acc[i];
+  }
+  __syncthreads();
+  if (tid < 16)
+    g.beta[(size_t)k * g.m_pad + 16 * j + tid] =
+        (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+}
+
+// Row k of L_S.  C_p(x_k) = k(x_k, x_p) - beta_p . k(X, x_k), where
+// k(X, x_k) . beta_p = (L v_k) . (L^-T v_p): the covariances are made again.
+__global__ __launch_bounds__(256) void kb_chol_kernel(const KbArgs a, int k) {
+  const KbGp& g = a.g[blockIdx.x];
+  __shared__ double ks[SCOOT_MAX_OBS + 32];
+  __shared__ double row[SCOOT_MAX_Q + 1];
+  __shared__ double var[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float* x = g.xc + a.picks[k] * a.d;
+  double s = 0.0;
+  for (int i = tid; i < g.m; i += 256) {
+    double r2 = 0.0;
+    for (int q = 0; q < a.d; ++q) {
+      const double t = (double)x[q] * g.scale[q] - kb_obs(g, i, q);
+      r2 = fma(t, t, r2);
+    }
+    ks[i] = kb_cov(g, r2);
+    s = fma(g.v[i], g.v[i], s);
+  }
+  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  if (lane == 0) var[wave] = s;
+  __syncthreads();
+  for (int p = wave; p < k; p += 4) {
+    const double* beta = g.beta + (size_t)p * g.m_pad;
+    double dot = 0.0;
+    for (int i = lane; i < g.m; i += 64) dot = fma(beta[i], ks[i], dot);
+    for (int o = 32; o >= 1; o >>= 1) dot += __shfl_xor(dot, o);
+    if (lane == 0) {
+      const float* y = g.xc + a.picks[p] * a.d;
+      double r2 = 0.0;
+      for (int q = 0; q < a.d; ++q) {
+        const double t = ((double)x[q] - (double)y[q]) * g.scale[q];
+        r2 = fma(t, t, r2);
       }
+      row[p] = kb_cov(g, r2) - dot;
     }
-    for (; i < a.rows; ++i) acc0 = fmaf(vp[i], col[(int64_t)i * a.ld], acc0);
-    const float dot = acc0 + acc1;
-    // k(x, x_p): same covariance and constants as the posterior kernel
-    float r2 = 0.0f;
-    for (int k = 0; k < a.d; ++k) {
-      const float t = (Xc[x * a.d + k] - xp[k]) * a.scale[k];
-      r2 = fmaf(t, t, r2);
-    }
-    const float u = __builtin_amdgcn_sqrtf(r2);
-    const float kxp = fmaf(u, fmaf(u, a.c2, a.c1), a.c0) * __builtin_amdgcn_exp2f(-u);
-    const float vnew = (kxp - dot) * dinv;
-    V[(int64_t)a.rows * a.ld + x] = vnew;
-    const float s = sd[x];
-    sd[x] = sqrtf(fmaxf(fmaf(-vnew, vnew, s * s), 0.0f));
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  // forward substitution against the rows before, one wave
+  double mine = 0.0;  // lane t: entry t of the new row, once known
+  double sum2 = 0.0;
+  for (int p = 0; p < k; ++p) {
+    double t = lane < p ? mine * g.ls[(size_t)p * a.q + lane] : 0.0;
+    for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o);
+    const double l = (row[p] - t) / g.ls[(size_t)p * a.q + p];
+    if (lane == p) mine = l;
+    sum2 = fma(l, l, sum2);
+  }
+  if (lane < k) g.ls[(size_t)k * a.q + lane] = mine;
+  if (lane == 0) {
+    const double prior = g.s2 - ((var[0] + var[1]) + (var[2] + var[3]));
+    g.ls[(size_t)k * a.q + k] = sqrt(fmax(prior, 0.0) + g.tau2 - fmin(sum2, fmax(prior, 0.0)));
   }
 }
 
-__global__ void kb_exclude_kernel(uint8_t* __restrict__ eligible, int64_t pick) { eligible[pick] = 0; }
-
-// What the host needs after a top-1, in one place: out = (score, mu_0(pick),
-// ..., mu_{p-1}(pick)); the means are left alone when there is no pick.
-__global__ void kb_pick_kernel(const int64_t* __restrict__ idx, const float* __restrict__ score,
-                               const float* __restrict__ mu, int64_t n, int p, float* __restrict__ out) {
-  const int j = threadIdx.x;
-  const int64_t pick = idx[0];
-  if (j == 0) out[0] = score[0];
-  if (j < p && pick >= 0) out[1 + j] = mu[(int64_t)j * n + pick];
+// sigma after the picks k0 + kn (those before k0 through their stored w).
+// LIST: 16 list entries per workgroup, its four waves sharing the
+// observations, min(n, *live) entries (live nullable); otherwise 64 candidates per wave, four per workgroup.  K* as
+// in the posterior (distances on the fp64 matrix cores), the dot products in
+// double.  Bound (whole pool, m = 512, eight picks): the covariances, as in
+// the posterior.
+template <int S, bool LIST>
+__global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const int32_t* __restrict__ list,
+                                                          const int64_t* __restrict__ list64,
+                                                          const int32_t* __restrict__ live, int64_t n, int k0, int kn,
+                                                          int last) {
+  constexpr int NT = LIST ? 1 : 4;
+  const KbGp& g = a.g[blockIdx.y];
+  if (g.S != S) return;
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* beta_l = reinterpret_cast<double*>(smem);  // [nj][kPicks][16]; LIST: [4 waves][16][kPicks]
+  const int tid = threadIdx.x, lane = tid & 63, gr = lane >> 4, c = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t base = LIST ? (int64_t)blockIdx.x * 16 : (int64_t)blockIdx.x * 256 + wave * 64;
+  if constexpr (LIST) {
+    if (live) n = min(n, (int64_t)*live);
+    if (base >= n) return;
+  }
+  if constexpr (!LIST) {
+    for (int i = tid; i < g.nj * 16 * kPicks; i += 256) {
+      const int j = i / (16 * kPicks), p = (i / 16) % kPicks;
+      beta_l[i] = p < kn ? g.beta[(size_t)(k0 + p) * g.m_pad + 16 * j + (i & 15)] : 0.0;
+    }
+    __syncthreads();
+  }
+  int64_t cand[NT];
+  double bq[NT][S];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int64_t e = min(base + t * 16 + c, n - 1);
+    cand[t] = e;
+    if constexpr (LIST) cand[t] = max(list64 ? list64[e] : (int64_t)list[e], (int64_t)0);
+    double nrm = 0.0;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int k = 4 * s + gr;
+      bq[t][s] = k < a.d ? (double)g.xc[cand[t] * a.d + k] * g.scale[min(k, SCOOT_MAX_DIM - 1)] : 0.0;
+      nrm = fma(bq[t][s], bq[t][s], nrm);
+    }
+    nrm += __shfl_xor(nrm, 16);
+    nrm += __shfl_xor(nrm, 32);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int k = 4 * s + gr;
+      if (k >= a.d) bq[t][s] = k == a.d ? 1.0 : (k == a.d + 1 ? nrm : 0.0);
+    }
+  }
+  double acc[NT][kPicks];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int p = 0; p < kPicks; ++p) acc[t][p] = 0.0;
+  if constexpr (LIST) {
+    // k(x, x_p), one pick per lane group (the waves' sums are added below)
+    const int p = wave * 4 + gr;
+    if (p < kn) {
+      const float* xr = g.xc + cand[0] * a.d;
+      const float* xp = g.xc + a.picks[k0 + p] * a.d;
+      double r2 = 0.0;
+      for (int q = 0; q < a.d; ++q) {
+        const double t = ((double)xr[q] - (double)xp[q]) * g.scale[q];
+        r2 = fma(t, t, r2);
+      }
+      const double kx = kb_cov(g, r2);
+#pragma unroll
+      for (int q = 0; q < kPicks; ++q) acc[0][q] = q == p ? kx : 0.0;
+    }
+  }
+  for (int j = LIST ? wave : 0; j < g.nj; j += LIST ? 4 : 1) {
+    double aq[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) aq[s] = (g.xq + (size_t)j * S * 64)[(unsigned)(s * 64 + lane)];
+    double kv[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      d4_t cr = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < S; ++s) cr = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], bq[t][s], cr, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float u = __builtin_amdgcn_sqrtf(fmaxf((float)(-cr[r]), 0.0f));
+        kv[t][r] = (double)(fmaf(u, fmaf(u, g.c2, g.c1), g.c0) * __builtin_amdgcn_exp2f(-u));
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < kPicks; ++p) {
+      if (p < kn) {
+        const d4_t b = LIST ? *reinterpret_cast<const d4_t*>(g.beta + (size_t)(k0 + p) * g.m_pad + 16 * j + 4 * gr)
+                            : *reinterpret_cast<const d4_t*>(beta_l + (j * kPicks + p) * 16 + 4 * gr);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[t][p] = fma(-b[r], kv[t][r], acc[t][p]);
+      }
+    }
+  }
+  // the lane groups' shares; LIST: the waves' too
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int p = 0; p < kPicks; ++p) {
+      acc[t][p] += __shfl_xor(acc[t][p], 16);
+      acc[t][p] += __shfl_xor(acc[t][p], 32);
+    }
+  double C[kPicks];
+  int64_t e, x;
+  if constexpr (LIST) {
+    if (gr == 0)
+#pragma unroll
+      for (int p = 0; p < kPicks; ++p) beta_l[(wave * 16 + c) * kPicks + p] = acc[0][p];
+    __syncthreads();
+    if (wave != 0 || gr != 0) return;
+#pragma unroll
+    for (int p = 0; p < kPicks; ++p)
+      C[p] = (beta_l[c * kPicks + p] + beta_l[(16 + c) * kPicks + p]) +
+             (beta_l[(32 + c) * kPicks + p] + beta_l[(48 + c) * kPicks + p]);
+    e = base + c;
+    x = cand[0];
+  } else {
+    // lane group gr finishes tile gr
+#pragma unroll
+    for (int p = 0; p < kPicks; ++p)
+      C[p] = gr == 0 ? acc[0][p] : (gr == 1 ? acc[NT > 1 ? 1 : 0][p] : (gr == 2 ? acc[NT > 2 ? 2 : 0][p] : acc[NT - 1][p]));
+    e = base + lane;
+    x = min(e, n - 1);
+  }
+  if (e >= n) return;
+  const double s0 = (double)g.sd0[x];
+  double var = s0 * s0;
+  for (int t = 0; t < k0; ++t) {
+    const double w = (double)g.w[(size_t)t * a.ld + e];
+    var = fma(-w, w, var);
+  }
+#pragma unroll
+  for (int p = 0; p < kPicks; ++p) {
+    if (p < kn) {
+      const double* l = g.ls + (size_t)(k0 + p) * a.q;
+      double w = C[p];
+      if constexpr (!LIST) {
+        const float* xr = g.xc + x * a.d;
+        const float* xp = g.xc + a.picks[k0 + p] * a.d;
+        double r2 = 0.0;
+        for (int q = 0; q < a.d; ++q) {
+          const double t = ((double)xr[q] - (double)xp[q]) * g.scale[q];
+          r2 = fma(t, t, r2);
+        }
+        w += kb_cov(g, r2);
+      }
+      for (int t = 0; t < k0; ++t) w = fma(-l[t], (double)g.w[(size_t)t * a.ld + e], w);
+#pragma unroll
+      for (int t = 0; t < p; ++t) w = fma(-l[k0 + t], C[t], w);
+      C[p] = w / l[k0 + p];
+      var = fma(-C[p], C[p], var);
+      if (!last) g.w[(size_t)(k0 + p) * a.ld + e] = (float)C[p];
+    }
+  }
+  if (last) {
+    const float sd = (float)sqrt(fmax(var, 0.0));
+    if constexpr (LIST) {
+      g.sd_list[e] = sd;
+      g.mu_list[e] = g.mu[x];
+    } else {
+      g.sd_out[e] = sd;
+    }
+  }
 }
 
-namespace {
+// Lists the candidates that can still win: eligible, and a bound that reaches
+// the best score of the first guesses (less the slack).
+__global__ __launch_bounds__(256) void kb_compact_kernel(const float* __restrict__ bound,
+                                                         const uint8_t* __restrict__ elig, int64_t n,
+                                                         const int64_t* __restrict__ idx,
+                                                         const float* __restrict__ first, int n_first,
+                                                         int32_t* __restrict__ list, int32_t* __restrict__ count) {
+  const int lane = threadIdx.x & 63;
+  float best = -INFINITY;
+  if (lane < n_first && idx[lane] >= 0) best = first[lane] >= best ? first[lane] : best;
+  for (int o = 32; o >= 1; o >>= 1) best = fmaxf(best, __shfl_xor(best, o));
+  const float thr = best - (float)kSlack * fabsf(best);
+  const bool any = best > -INFINITY;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i - lane < n; i += (int64_t)gridDim.x * 256) {
+    const bool in = i < n && elig[i] != 0 && (any ? bound[i] >= thr : bound[i] == bound[i]);
+    const uint64_t m = __ballot(in);
+    if (m == 0) continue;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(count, __popcll(m));
+    at = __shfl(at, 0);
+    if (in) list[at + __popcll(m & ((1ull << lane) - 1))] = (int32_t)i;
+  }
+}
+
+__global__ __launch_bounds__(256) void kb_scatter_kernel(const int32_t* __restrict__ list,
+                                                         const int32_t* __restrict__ live, int n,
+                                                         const float* __restrict__ val, float* __restrict__ bound) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (live) n = min(n, *live);
+  if (i < n) bound[list[i]] = val[i];
+}
+
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
-// Row stride of a kept V: n rounded up to 64 floats (256 bytes).
-int64_t kb_ld(int64_t n) { return (n + 63) / 64 * 64; }
 
 struct KbLayout {
-  size_t v, mu, sd, acq, elig, votes, idx, score, nvalid, vp, dinv, pickinfo, xw, total;
+  size_t mu, sd, bound, elig, votes, list, mu_list, sd_list, val, w, xw;  // of the pool's size
+  size_t idx, score, nvalid, picks, info, count, v, beta, ls;             // small
+  size_t total;
 };
 
 KbLayout kb_layout(const GPDevice* const* g, int p, int64_t n, int q) {
   KbLayout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) {
-    size_t at = off;
+    const size_t at = off;
     off += align256(bytes);
     return at;
   };
-  size_t vbytes = 0;
-  int rows_max = 0;
+  size_t m_pad = 0, xw = 0;
   for (int j = 0; j < p; ++j) {
-    vbytes += align256((size_t)(g[j]->m_pad + q) * kb_ld(n) * 4);
-    rows_max = std::max(rows_max, g[j]->m_pad + q);
+    m_pad = std::max(m_pad, (size_t)g[j]->m_pad);
+    xw += g[j]->warp ? align256((size_t)n * g[j]->d * 4) : 0;  // the pool after each warped GP's input warping
   }
-  L.v = take(vbytes);
   L.mu = take((size_t)p * n * 4);
   L.sd = take((size_t)p * n * 4);
-  L.acq = take((size_t)n * 4);
+  L.bound = take((size_t)n * 4);
   L.elig = take((size_t)n);
   L.votes = take((size_t)n * 4);
-  L.idx = take(8);
-  L.score = take(8);
-  L.nvalid = take(4);
-  L.vp = take((size_t)p * rows_max * 4);
-  L.dinv = take((size_t)p * 4);
-  L.pickinfo = take((size_t)(1 + SCOOT_MAX_OBJECTIVES) * 4);
-  size_t xw = 0;  // the pool after each warped GP's input warping
-  for (int j = 0; j < p; ++j) xw += g[j]->warp ? align256((size_t)n * g[j]->d * 4) : 0;
+  L.list = take((size_t)n * 4);
+  L.mu_list = take((size_t)p * std::max<int64_t>(n, kTop) * 4);
+  L.sd_list = take((size_t)p * std::max<int64_t>(n, kTop) * 4);
+  L.val = take((size_t)std::max<int64_t>(n, kTop) * 4);
+  L.w = take(q > kPicks + 1 ? (size_t)p * (q - 1) * std::max<int64_t>(n, kTop) * 4 : 0);
   L.xw = take(xw);
+  L.idx = take(kTop * 8);
+  L.score = take(kTop * 4);
+  L.nvalid = take(4);
+  L.picks = take((size_t)q * 8);
+  L.info = take(sizeof(KbInfo));
+  L.count = take(4);
+  L.v = take((size_t)p * m_pad * 8);
+  L.beta = take((size_t)p * q * m_pad * 8);
+  L.ls = take((size_t)p * q * q * 8);
   L.total = off;
   return L;
 }
+
+template <int S, bool LIST>
+int launch_sigma_s(const KbArgs& a, const int32_t* list, const int64_t* list64, const int32_t* live, int64_t n, int k0,
+                   int kn, bool last, hipStream_t s) {
+  auto kern = kb_sigma_kernel<S, LIST>;
+  int nj = 0;
+  for (int j = 0; j < a.p; ++j) nj = std::max(nj, a.g[j].nj);
+  const size_t lds = LIST ? (size_t)4 * 16 * kPicks * 8 : (size_t)nj * 16 * kPicks * 8;
+  const int rc = allow_full_lds((const void*)kern, "believer");
+  if (rc != SCOOT_OK) return rc;
+  const int64_t blocks = LIST ? (n + 15) / 16 : (n + 255) / 256;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)a.p), dim3(256), lds, s, a, list, list64, live, n, k0,
+                     kn, last ? 1 : 0);
+  return SCOOT_OK;
+}
+
+template <bool LIST>
+int launch_sigma(const KbArgs& a, const int32_t* list, const int64_t* list64, const int32_t* live, int64_t n, int picks,
+                 hipStream_t s) {
+  if (n == 0) return SCOOT_OK;
+  for (int k0 = 0; k0 < picks; k0 += kPicks) {
+    const int kn = std::min(kPicks, picks - k0);
+    const bool last = k0 + kn == picks;
+    int rc;
+    switch (a.g[0].S) {  // the GPs share d
+      case 1: rc = launch_sigma_s<1, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
+      case 2: rc = launch_sigma_s<2, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
+      case 3: rc = launch_sigma_s<3, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
+      case 4: rc = launch_sigma_s<4, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
+      default: rc = launch_sigma_s<5, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
+    }
+    if (rc != SCOOT_OK) return rc;
+  }
+  return SCOOT_OK;
+}
+
 }  // namespace
 
-size_t kb_workspace_bytes(const GPDevice* const* g, int p, int64_t n, int q) { return kb_layout(g, p, n, q).total; }
+size_t kb_needed_bytes(const GPDevice* const* g, int p, int64_t n, int q) { return kb_layout(g, p, n, q).total; }
+
+// What scoot_suggest_kb_workspace reports and a caller's workspace is held to:
+// the size of the form that kept V of every objective (m_pad + q rows of the
+// pool's length), which programs may have stored; what is used is less.
+size_t kb_workspace_bytes(const GPDevice* const* g, int p, int64_t n, int q) {
+  size_t off = 0, vbytes = 0, xw = 0;
+  int rows_max = 0;
+  auto take = [&](size_t bytes) { off += align256(bytes); };
+  const int64_t ld = (n + 63) / 64 * 64;
+  for (int j = 0; j < p; ++j) {
+    vbytes += align256((size_t)(g[j]->m_pad + q) * ld * 4);
+    rows_max = std::max(rows_max, g[j]->m_pad + q);
+    xw += g[j]->warp ? align256((size_t)n * g[j]->d * 4) : 0;
+  }
+  take(vbytes);
+  for (size_t b : {(size_t)p * n * 4, (size_t)p * n * 4, (size_t)n * 4, (size_t)n, (size_t)n * 4, (size_t)8, (size_t)8,
+                   (size_t)4, (size_t)p * rows_max * 4, (size_t)p * 4, (size_t)(1 + SCOOT_MAX_OBJECTIVES) * 4, xw})
+    take(b);
+  return off;
+}
 
 int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f, const uint8_t* known,
                          int64_t vote_min, const float* Xc, int64_t n, const double* Y_obs, int m_obs,
@@ -154,110 +562,166 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
   hipStream_t s = (hipStream_t)stream;
   const KbLayout L = kb_layout(g, p, n, q);
   unsigned char* w = (unsigned char*)ws;
-  float* V[SCOOT_MAX_OBJECTIVES];
-  const int64_t ld = kb_ld(n);
-  size_t voff = L.v;
-  for (int j = 0; j < p; ++j) {
-    V[j] = (float*)(w + voff);
-    voff += align256((size_t)(g[j]->m_pad + q) * ld * 4);
-  }
   float* mu = (float*)(w + L.mu);
   float* sd = (float*)(w + L.sd);
-  float* acq = (float*)(w + L.acq);
+  float* bound = (float*)(w + L.bound);
   uint8_t* elig = (uint8_t*)(w + L.elig);
   int32_t* votes = (int32_t*)(w + L.votes);
+  int32_t* list = (int32_t*)(w + L.list);
+  float* val = (float*)(w + L.val);
   int64_t* idx = (int64_t*)(w + L.idx);
   float* score = (float*)(w + L.score);
   int32_t* nvalid = (int32_t*)(w + L.nvalid);
-  float* vp = (float*)(w + L.vp);
-  float* dinv = (float*)(w + L.dinv);
-  float* pickinfo = (float*)(w + L.pickinfo);
-  int rows_max = 0;
-  for (int j = 0; j < p; ++j) rows_max = std::max(rows_max, g[j]->m_pad + q);
-  // candidates as each GP sees them: warped copies kept for the whole loop
-  const float* xg[SCOOT_MAX_OBJECTIVES];
+  int64_t* picks_d = (int64_t*)(w + L.picks);
+  KbInfo* info_d = (KbInfo*)(w + L.info);
+  int32_t* count_d = (int32_t*)(w + L.count);
+  const int64_t nl = std::max<int64_t>(n, kTop);
+  int m_pad = 0;
+  for (int j = 0; j < p; ++j) m_pad = std::max(m_pad, g[j]->m_pad);
+
+  KbArgs a{};
+  a.picks = picks_d;
+  a.ld = nl;
+  a.d = g[0]->d;
+  a.q = q;
+  a.p = p;
+  const void *mus[SCOOT_MAX_OBJECTIVES], *sds[SCOOT_MAX_OBJECTIVES], *mul[SCOOT_MAX_OBJECTIVES],
+      *sdl[SCOOT_MAX_OBJECTIVES];
   size_t xoff = L.xw;
+  int rc;
   for (int j = 0; j < p; ++j) {
-    xg[j] = Xc;
-    if (g[j]->warp) {
+    KbGp& o = a.g[j];
+    o.linv = (const unsigned char*)g[j]->linv;
+    o.xq = (const double*)g[j]->xs;
+    o.xc = Xc;
+    if (g[j]->warp) {  // the pool as this GP sees it
       float* xw = (float*)(w + xoff);
       xoff += align256((size_t)n * g[j]->d * 4);
-      int rc = launch_warp_pool(*g[j], Xc, n, xw, stream);
+      rc = launch_warp_pool(*g[j], Xc, n, xw, stream);
       if (rc != SCOOT_OK) return rc;
-      xg[j] = xw;
+      o.xc = xw;
     }
-  }
-
-  // Posterior of every objective, V kept; the feasibility mask is the initial eligibility.
-  const void* mus[SCOOT_MAX_OBJECTIVES];
-  const void* sds[SCOOT_MAX_OBJECTIVES];
-  for (int j = 0; j < p; ++j) {
-    mus[j] = mu + (size_t)j * n;
-    sds[j] = sd + (size_t)j * n;
-    int rc = launch_posterior(*g[j], xg[j], n, mu + (size_t)j * n, sd + (size_t)j * n, nullptr, nullptr, stream, V[j],
-                              true, ld);
+    o.mu = mu + (size_t)j * n;
+    o.sd0 = sd + (size_t)j * n;
+    o.v = (double*)(w + L.v) + (size_t)j * m_pad;
+    o.beta = (double*)(w + L.beta) + (size_t)j * q * m_pad;
+    o.ls = (double*)(w + L.ls) + (size_t)j * q * q;
+    o.w = (float*)(w + L.w) + (size_t)j * (q - 1) * nl;
+    o.mu_list = (float*)(w + L.mu_list) + (size_t)j * nl;
+    o.sd_list = (float*)(w + L.sd_list) + (size_t)j * nl;
+    o.sd_out = sigma_out ? sigma_out + (size_t)j * n : nullptr;
+    for (int k = 0; k < SCOOT_MAX_DIM; ++k) o.scale[k] = g[j]->scale64[k];
+    o.c0d = g[j]->coef64[0];
+    o.c1d = g[j]->coef64[1];
+    o.c2d = g[j]->coef64[2];
+    o.c0 = g[j]->coef32[0];
+    o.c1 = g[j]->coef32[1];
+    o.c2 = g[j]->coef32[2];
+    o.s2 = g[j]->s2;
+    o.tau2 = g[j]->tau2;
+    o.m = g[j]->m;
+    o.nj = (g[j]->m + 15) / 16;
+    o.nb32 = g[j]->nb;
+    o.m_pad = m_pad;
+    o.S = (g[j]->d + 2 + 3) / 4;
+    mus[j] = o.mu;
+    sds[j] = o.sd0;
+    mul[j] = o.mu_list;
+    sdl[j] = o.sd_list;
+    rc = launch_posterior(*g[j], o.xc, n, mu + (size_t)j * n, sd + (size_t)j * n, nullptr, nullptr, stream, true);
     if (rc != SCOOT_OK) return rc;
   }
-  int rc = f ? launch_forest(*f, Xc, n, vote_min, votes, elig, nullptr, stream, known)
-             : launch_mask_init(elig, known, n, stream);
+  rc = f ? launch_forest(*f, Xc, n, vote_min, votes, elig, nullptr, stream, known)
+         : launch_mask_init(elig, known, n, stream);
   if (rc != SCOOT_OK) return rc;
 
-  std::vector<double> Yaug(Y_obs, Y_obs + (size_t)m_obs * p);
+  auto device_error = [](hipError_t e) {
+    return fail(SCOOT_ERR_DEVICE, std::string("believer: ") + hipGetErrorString(e));
+  };
+  // the front so far: the observations first, then the front and the fantasies
+  std::vector<double> front(Y_obs, Y_obs + (size_t)m_obs * p);
+  int nb32 = 0, nj = 0;
+  for (int j = 0; j < p; ++j) {
+    nb32 = std::max(nb32, a.g[j].nb32);
+    nj = std::max(nj, a.g[j].nj);
+  }
   *n_picked = 0;
   for (int k = 0; k < q; ++k) {
     BoxTable bt;
-    rc = build_boxes(Yaug.data(), (int)(Yaug.size() / p), p, ref, bt);
+    rc = build_boxes(front.data(), (int)(front.size() / p), p, ref, bt);
     if (rc != SCOOT_OK) return rc;
-    rc = launch_ehvi_topq(mus, sds, p, n, SCOOT_F32, bt, acq, elig, 1, idx, score, nvalid, stream);
-    if (rc != SCOOT_OK) return rc;
-    // One read-back per pick: the index, its score and its means (the
-    // fantasies).  The row updates below are left running while the host
-    // builds the next front.
-    hipLaunchKernelGGL(kb_pick_kernel, dim3(1), dim3(64), 0, s, idx, score, mu, n, p, pickinfo);
-    int64_t pick = -1;
-    float info[1 + SCOOT_MAX_OBJECTIVES] = {};
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&pick, idx, 8, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(info, pickinfo, (size_t)(1 + p) * 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return fail(SCOOT_ERR_DEVICE, std::string("believer: ") + hipGetErrorString(e));
-    if (pick < 0) break;
-    picks[k] = pick;
-    if (pick_acq) pick_acq[k] = info[0];
+    KbInfo info{};
+    // One read-back per selection: what the next round needs of the pick is
+    // made meanwhile.
+    auto pick = [&]() {
+      hipLaunchKernelGGL(kb_pick_kernel, dim3(1), dim3(64), 0, s, a, idx, score, k, elig, picks_d, info_d, count_d);
+      hipError_t e = hipGetLastError();
+      if (e == hipSuccess) e = hipMemcpyAsync(&info, info_d, sizeof info, hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+      return e;
+    };
+    if (k == 0) {
+      hipLaunchKernelGGL(kb_zero_kernel, dim3(1), dim3(1), 0, s, count_d);
+      rc = launch_ehvi_topq(mus, sds, p, n, SCOOT_F32, bt, bound, elig, kTop, idx, score, nvalid, stream);
+      if (rc != SCOOT_OK) return rc;
+      const hipError_t e = pick();
+      if (e != hipSuccess) return device_error(e);
+    } else {
+      // the first guesses: the other candidates of the last selection
+      rc = launch_sigma<true>(a, nullptr, idx + 1, nullptr, kTop - 1, k, s);
+      if (rc == SCOOT_OK) rc = launch_ehvi(mul, sdl, p, kTop - 1, SCOOT_F32, bt, val, stream);
+      if (rc != SCOOT_OK) return rc;
+      const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 2048));
+      hipLaunchKernelGGL(kb_compact_kernel, dim3((unsigned)blocks), dim3(256), 0, s, bound, elig, n, idx + 1, val,
+                         kTop - 1, list, count_d);
+      // The list's length stays on the device; the few lists that are longer
+      // than kListed are scored whole in a second turn.
+      int64_t cap = std::min<int64_t>(n, kListed);
+      const int32_t* live = count_d;
+      for (;;) {
+        rc = launch_sigma<true>(a, list, nullptr, live, cap, k, s);
+        if (rc == SCOOT_OK) rc = launch_ehvi(mul, sdl, p, cap, SCOOT_F32, bt, val, stream);
+        if (rc != SCOOT_OK) return rc;
+        hipLaunchKernelGGL(kb_scatter_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, list, live,
+                           (int)cap, val, bound);
+        rc = launch_topq(bound, elig, n, SCOOT_F32, kTop, idx, score, nvalid, stream);
+        if (rc != SCOOT_OK) return rc;
+        const hipError_t e = pick();
+        if (e != hipSuccess) return device_error(e);
+        if (info.count <= cap) break;
+        if (info.pick >= 0) hipLaunchKernelGGL(kb_unpick_kernel, dim3(1), dim3(1), 0, s, picks_d, k, elig);
+        cap = info.count;
+        live = nullptr;
+      }
+    }
+    if (info.pick < 0) break;
+    picks[k] = info.pick;
+    if (pick_acq) pick_acq[k] = info.score;
     *n_picked = k + 1;
     if (k + 1 == q) break;
-    // fantasies for the front, then the bordered update of every objective
-    for (int j = 0; j < p; ++j) Yaug.push_back((double)info[1 + j]);
-    for (int j = 0; j < p; ++j) {
-      const int rows = g[j]->m_pad + k;
-      float* vpj = vp + (size_t)j * rows_max;
-      hipLaunchKernelGGL(kb_gather_kernel, dim3(1), dim3(kKbThreads), 0, s, V[j], ld, rows, pick,
-                         sd + (size_t)j * n, g[j]->tau2, vpj, dinv + j);
-      KbArgs a{};
-      a.n = n;
-      a.ld = ld;
-      a.pick = pick;
-      a.rows = rows;
-      a.d = g[j]->d;
-      for (int t = 0; t < SCOOT_MAX_DIM; ++t) a.scale[t] = g[j]->scale32[t];
-      a.c0 = g[j]->coef32[0];
-      a.c1 = g[j]->coef32[1];
-      a.c2 = g[j]->coef32[2];
-      int64_t blocks = (n + kKbThreads - 1) / kKbThreads;
-      if (blocks > 8192) blocks = 8192;
-      hipLaunchKernelGGL(kb_update_kernel, dim3((unsigned)blocks), dim3(kKbThreads), 0, s, V[j], vpj, dinv + j, xg[j],
-                         sd + (size_t)j * n, a);
-    }
-    hipLaunchKernelGGL(kb_exclude_kernel, dim3(1), dim3(1), 0, s, elig, pick);
-    e = hipGetLastError();
-    if (e != hipSuccess) return fail(SCOOT_ERR_DEVICE, std::string("believer: ") + hipGetErrorString(e));
+    front = std::move(bt.front);
+    for (int j = 0; j < p; ++j) front.push_back((double)info.mu[j]);
+    hipLaunchKernelGGL(kb_v_kernel, dim3((unsigned)nb32, (unsigned)p), dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL(kb_beta_kernel, dim3((unsigned)nj, (unsigned)p), dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL(kb_chol_kernel, dim3((unsigned)p), dim3(256), 0, s, a, k);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return device_error(e);
   }
   // the posterior the last scoring round saw (mu never moves; sigma carries
-  // the downdates of every pick before that round)
+  // the picks before that round)
   hipError_t e = hipSuccess;
   if (mu_out) e = hipMemcpyAsync(mu_out, mu, (size_t)p * n * 4, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess && sigma_out) e = hipMemcpyAsync(sigma_out, sd, (size_t)p * n * 4, hipMemcpyDeviceToDevice, s);
-  if (e != hipSuccess) return fail(SCOOT_ERR_DEVICE, std::string("believer: ") + hipGetErrorString(e));
+  if (e == hipSuccess && sigma_out) {
+    const int seen = *n_picked == q ? q - 1 : *n_picked;
+    if (seen == 0) {
+      e = hipMemcpyAsync(sigma_out, sd, (size_t)p * n * 4, hipMemcpyDeviceToDevice, s);
+    } else {
+      rc = launch_sigma<false>(a, nullptr, nullptr, nullptr, n, seen, s);
+      if (rc != SCOOT_OK) return rc;
+      e = hipGetLastError();
+    }
+  }
+  if (e != hipSuccess) return device_error(e);
   return SCOOT_OK;
 }
 

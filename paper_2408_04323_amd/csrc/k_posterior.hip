@@ -110,7 +110,6 @@ struct Post32 {
   double scale[SCOOT_MAX_DIM];
   float c0, c1, c2;
   double s2, prior, ei_c;
-  int64_t v_ld;    // row stride of a kept V
 };
 
 constexpr int kUnitBytes = 3 * 64 * 16;   // a unit's three parts in A-operand order
@@ -158,11 +157,11 @@ struct PostLds {
 // S: fp64 MFMA steps of the distances; RS: waves that share a tile's rows;
 // NBW: slots per wave; KA: register sets for units of L^-1; WPS: waves per SIMD
 // that the register budget is set for.
-template <int S, int RS, int NBW, int KA, int WPS, bool KEEP_V>
+template <int S, int RS, int NBW, int KA, int WPS>
 __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
     const float* __restrict__ Xc, const unsigned char* __restrict__ linv, const double* __restrict__ xq,
     const float* __restrict__ alpha, float* __restrict__ mu_out, float* __restrict__ sd_out,
-    float* __restrict__ ei_out, float* __restrict__ v_out, const Post32 a) {
+    float* __restrict__ ei_out, const Post32 a) {
   constexpr int CT = 4 / RS;      // 16-candidate tiles whose K* this wave makes
   constexpr int NP = 2 * CT;      // pieces of that work, two observations each
   constexpr int PPS = (NP + NBW - 1) / NBW;  // pieces beside a slot, in order
@@ -376,17 +375,6 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
 #pragma unroll
           for (int i = 0; i < 16; ++i) q[i & 3] = fmaf(acc[t][h][i], acc[t][h][i], q[i & 3]);
           sq += (double)((q[0] + q[1]) + (q[2] + q[3]));
-          if constexpr (KEEP_V) {
-            const int64_t cand = c0 + h * 32 + (lane & 31);
-            float* v = v_out + (32 * (a.nb32 - 1 - (r + RS * t)) + 4 * (lane >> 5)) * a.v_ld + cand;
-            if (cand < a.n) {
-#pragma unroll
-              for (int i = 0; i < 16; ++i) {
-                *v = acc[t][h][i];
-                v += (i & 3) == 3 ? 5 * a.v_ld : a.v_ld;
-              }
-            }
-          }
         }
       }
       sq += __shfl_xor(sq, 32);
@@ -762,23 +750,23 @@ int64_t persistent_grid(const void* kern, int threads, size_t lds, int64_t tiles
   return std::min(tiles, (int64_t)cus * per_cu);
 }
 
-template <int S, int RS, int NBW, int KA, int WPS, bool KEEP_V>
-int run32(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, float* ei, float* v_out,
-          const Post32& a, hipStream_t s) {
-  auto kern = posterior_f32_kernel<S, RS, NBW, KA, WPS, KEEP_V>;
+template <int S, int RS, int NBW, int KA, int WPS>
+int run32(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, float* ei, const Post32& a,
+          hipStream_t s) {
+  auto kern = posterior_f32_kernel<S, RS, NBW, KA, WPS>;
   const int64_t grid = persistent_grid((const void*)kern, RS * 64, 0, (n + kPostTile - 1) / kPostTile);
   if (grid < 1) return fail(SCOOT_ERR_DEVICE, "posterior: workgroup does not fit on a compute unit");
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(RS * 64), 0, s, Xc, (const unsigned char*)g.linv,
-                     (const double*)g.xs, g.alpha32, mu, sd, ei, v_out, a);
+                     (const double*)g.xs, g.alpha32, mu, sd, ei, a);
   return SCOOT_OK;
 }
-template <int S, bool KEEP_V>
-int run32_by_rows(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, float* ei, float* v_out,
-                  const Post32& a, hipStream_t s) {
-  if (a.nb32 <= 4) return run32<S, 2, 2, 2, 3, KEEP_V>(g, Xc, n, mu, sd, ei, v_out, a, s);
-  if (a.nb32 <= 8) return run32<S, 2, 4, 3, 2, KEEP_V>(g, Xc, n, mu, sd, ei, v_out, a, s);
-  if (a.nb32 <= 16) return run32<S, 4, 4, 4, 2, KEEP_V>(g, Xc, n, mu, sd, ei, v_out, a, s);
-  return run32<S, 4, 5, 2, 2, KEEP_V>(g, Xc, n, mu, sd, ei, v_out, a, s);
+template <int S>
+int run32_by_rows(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, float* ei, const Post32& a,
+                  hipStream_t s) {
+  if (a.nb32 <= 4) return run32<S, 2, 2, 2, 3>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 8) return run32<S, 2, 4, 3, 2>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 16) return run32<S, 4, 4, 4, 2>(g, Xc, n, mu, sd, ei, a, s);
+  return run32<S, 4, 5, 2, 2>(g, Xc, n, mu, sd, ei, a, s);
 }
 
 template <int WAVES, int D>
@@ -810,7 +798,7 @@ int by_d_rec(int d, F&& f) {
 }  // namespace
 
 int launch_posterior(const GPDevice& g, const float* Xc, int64_t n, void* mu, void* sigma,
-                     const double* ei_c, void* ei, void* stream, float* v_out, bool xc_warped, int64_t v_ld) {
+                     const double* ei_c, void* ei, void* stream, bool xc_warped) {
   if (n == 0) return SCOOT_OK;
   if (n >= ((int64_t)1 << 37)) return fail(SCOOT_ERR_UNSUPPORTED, "posterior: n too large");
   hipStream_t s = (hipStream_t)stream;
@@ -835,16 +823,13 @@ int launch_posterior(const GPDevice& g, const float* Xc, int64_t n, void* mu, vo
     a.s2 = g.s2;
     a.prior = g.c;
     a.ei_c = ei_c ? *ei_c : 0.0;
-    a.v_ld = v_ld > 0 ? v_ld : n;
     float* e = ei_c ? (float*)ei : nullptr;
     rc = by_d_rec<1>((g.d + 2 + 3) / 4, [&](auto Sc) {
       constexpr int S = decltype(Sc)::value;
       if constexpr (S > (SCOOT_MAX_DIM + 5) / 4) {
         return fail(SCOOT_ERR_UNSUPPORTED, "posterior: d exceeds SCOOT_MAX_DIM");
       } else {
-        float *m32 = (float*)mu, *s32 = (float*)sigma;
-        return v_out ? run32_by_rows<S, true>(g, Xc, n, m32, s32, e, v_out, a, s)
-                     : run32_by_rows<S, false>(g, Xc, n, m32, s32, e, nullptr, a, s);
+        return run32_by_rows<S>(g, Xc, n, (float*)mu, (float*)sigma, e, a, s);
       }
     });
   } else {
