@@ -18,7 +18,7 @@
 //   K. K, one 16 x 16 block per workgroup;
 //   A. one workgroup (8 waves): the Cholesky factor L by 16-column block
 //      steps: the diagonal block factored and inverted by one wave in
-//      registers (a rank-1 update per column on v_mfma_f64_16x16x4f64), the
+//      registers (a rank-4 update per four columns on v_mfma_f64_16x16x4f64), the
 //      panel below it as the product with that inverse and the trailing
 //      update, both on the matrix cores, and u = L^-1 r by forward
 //      substitution alongside; the next diagonal block is factored as soon
@@ -88,6 +88,15 @@ __device__ inline d4_t mma16(d4_t acc, const double (&a)[4], const double (&b)[4
 #pragma unroll
   for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
   return acc;
+}
+// The same from 0 on two chains of two steps, where the result is waited for.
+__device__ inline d4_t mma16_zero(const double (&a)[4], const double (&b)[4]) {
+  const d4_t z = {0.0, 0.0, 0.0, 0.0};
+  d4_t x = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], b[0], z, 0, 0, 0);
+  d4_t y = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], b[1], z, 0, 0, 0);
+  x = __builtin_amdgcn_mfma_f64_16x16x4f64(a[2], b[2], x, 0, 0, 0);
+  y = __builtin_amdgcn_mfma_f64_16x16x4f64(a[3], b[3], y, 0, 0, 0);
+  return x + y;
 }
 __device__ inline d4_t zero4() { return d4_t{0.0, 0.0, 0.0, 0.0}; }
 // C layout of a row-major block in memory: element 64 r + l.
@@ -239,17 +248,30 @@ __device__ inline double lane_bcast(double v, int src) {
   return __hiloint2double(hi, lo);
 }
 
+// 1 / sqrt(p): the hardware estimate r and one third-order step (from the
+// series of (1 - e)^-1/2, e = 1 - p r^2: the error is about cubed), a shorter
+// dependent chain than two Newton steps or a square root and a division.
+__device__ inline double rsqrt_refined(double p) {
+  const double r = __builtin_amdgcn_rsq(p);
+  const double e = fma(-p * r, r, 1.0);
+  return fma(r * e, fma(e, 0.375, 0.5), r);
+}
+
 // Factors the 16 x 16 diagonal block kk, held in C layout by one wave, and
-// inverts the factor on the way.  Column c: the pivot p = D[c][c] comes from
-// one lane; l = D[c][.] / sqrt(p) (row c, by symmetry column c of L) sits in
-// register c / 4 of row group c % 4, which is where v_mfma_f64_16x16x4f64 takes
-// both operands of its k = c % 4 slice, so one MFMA subtracts l l^T from the
-// whole block.  The same l against row c of Y (Y = I at the start) scaled by
-// 1 / L[c][c], which is row c of L^-1, carries out the forward substitution of
-// L Y = I a column at a time.  Stores L_kk column-major to memory, L_kk^-1
-// row-major to memory (Di) and as a row slot (sX), the product of the pivots of
-// real rows to sProd[kk]; raises sFlag[0] when such a pivot is not above floor
-// (or a padding pivot is not positive).
+// inverts the factor on the way, four columns 4b .. 4b + 3 at a time.  Their
+// 4 x 4 diagonal block comes to every lane, which factors it and solves for
+// column g (its row group) of the inverse M of that factor.  Rows 4b .. 4b + 3
+// of D sit in register b, row 4b + g in group g, where
+// v_mfma_f64_16x16x4f64 takes its B operand, and its result's rows 0 .. 3 come
+// out the same way in register 0: so one MFMA with M makes four rows of L^T,
+// one subtracts their l^T l from the whole block, and two more do the same for
+// Y (Y = I at the start, whose rows become those of L^-1).  Bound: one serial
+// chain on one wave; with a rank-1 update per column (16 rounds of matrix
+// instruction, broadcast, reciprocal root) a block took 6000 cycles, a quarter
+// of every round's K = 4 in use; now about 4700, in rounds of four columns.  Stores L_kk column-major to
+// memory, L_kk^-1 row-major to memory (Di) and as a row slot (sX), the product
+// of the pivots of real rows to sProd[kk]; sets bit 0 of sFlag[0] when such a pivot is
+// not above floor (or a padding pivot is not positive).
 __device__ inline void diag_factor(const NllArgs& a, int kk, d4_t D, double* sX, double* sProd, int* sFlag,
                                    double floor, int lane) {
   const int g = lane >> 4, j = lane & 15, real = min(16, a.m - 16 * kk);
@@ -259,35 +281,43 @@ __device__ inline void diag_factor(const NllArgs& a, int kk, d4_t D, double* sX,
   double prod = 1.0;
   bool bad = false;
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int cg = c & 3, cr = c >> 2;
-    const double piv = lane_bcast(D[cr], cg * 16 + c);
-    const bool real_row = c < real;
-    bad = bad || !(piv > (real_row ? floor : 0.0));
-    prod *= real_row ? piv : 1.0;
-    // 1 / sqrt(piv): the hardware estimate and two Newton steps (each about
-    // squares the relative error), a shorter dependent chain than sqrt and
-    // a division
-    double ic = __builtin_amdgcn_rsq(piv);
-    const double h = 0.5 * piv;
-    ic = ic * fma(-h * ic, ic, 1.5);
-    ic = ic * fma(-h * ic, ic, 1.5);
-    const bool mine = g == cg;
-    const double l = mine && j >= c ? D[cr] * ic : 0.0;  // L[j][c], 0 above the diagonal
-    const double y = mine ? Y[cr] * ic : 0.0;            // (L^-1)[c][j]
-    if (mine) {
-      Lt[cr] = l;
-      X[cr] = y;
-    }
-    D = __builtin_amdgcn_mfma_f64_16x16x4f64(-l, l, D, 0, 0, 0);
-    Y = __builtin_amdgcn_mfma_f64_16x16x4f64(-l, y, Y, 0, 0, 0);
+  for (int b = 0; b < 4; ++b) {
+    auto at = [&](int r, int c) { return lane_bcast(D[b], r * 16 + 4 * b + c); };
+    auto pivot = [&](int r, double p) {
+      const bool real_row = 4 * b + r < real;
+      bad = bad || !(p > (real_row ? floor : 0.0));
+      prod *= real_row ? p : 1.0;
+      return rsqrt_refined(p);
+    };
+    const double i0 = pivot(0, at(0, 0));
+    const double l10 = at(1, 0) * i0, l20 = at(2, 0) * i0, l30 = at(3, 0) * i0;
+    const double i1 = pivot(1, fma(-l10, l10, at(1, 1)));
+    const double l21 = fma(-l20, l10, at(2, 1)) * i1, l31 = fma(-l30, l10, at(3, 1)) * i1;
+    const double i2 = pivot(2, fma(-l21, l21, fma(-l20, l20, at(2, 2))));
+    const double l32 = fma(-l31, l21, fma(-l30, l20, at(3, 2))) * i2;
+    const double i3 = pivot(3, fma(-l32, l32, fma(-l31, l31, fma(-l30, l30, at(3, 3)))));
+    // column g of M, then M as an A operand: lane (g, j) holds M[j][g]
+    const double y0 = g == 0 ? i0 : 0.0;
+    double y1 = fma(-l10, y0, g == 1 ? 1.0 : 0.0) * i1;
+    double y2 = fma(-l21, y1, fma(-l20, y0, g == 2 ? 1.0 : 0.0)) * i2;
+    double y3 = fma(-l32, y2, fma(-l31, y1, fma(-l30, y0, g == 3 ? 1.0 : 0.0))) * i3;
+    asm volatile("" : "+v"(y1), "+v"(y2), "+v"(y3));  // selects below, not branches around the chain
+    const double mv = j == 0 ? y0 : (j == 1 ? y1 : (j == 2 ? y2 : (j == 3 ? y3 : 0.0)));
+    const d4_t lp = __builtin_amdgcn_mfma_f64_16x16x4f64(mv, D[b], zero4(), 0, 0, 0);
+    const double l = j >= 4 * b + g ? lp[0] : 0.0;  // L[j][4b + g], 0 above the diagonal
+    Lt[b] = l;
+    if (b < 3) D = __builtin_amdgcn_mfma_f64_16x16x4f64(-l, l, D, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);  // D, which the next columns wait for, first
+    const d4_t yp = __builtin_amdgcn_mfma_f64_16x16x4f64(mv, Y[b], zero4(), 0, 0, 0);
+    X[b] = yp[0];                                   // (L^-1)[4b + g][j]
+    if (b < 3) Y = __builtin_amdgcn_mfma_f64_16x16x4f64(-l, yp[0], Y, 0, 0, 0);
   }
   st_c(a.L + ((size_t)kk * a.nb + kk) * 256, Lt, lane);  // L_kk column-major
   st_c(a.Di + (size_t)kk * 256, X, lane);
   st_row_slot(sX, X, lane);
   if (lane == 0) {
     sProd[kk] = prod;
-    if (bad) sFlag[0] = 1;
+    if (bad) __hip_atomic_fetch_or(&sFlag[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
 
@@ -302,7 +332,7 @@ __device__ inline void diag_solve(const NllArgs& a, int kk, const double* sX, co
 #pragma unroll
   for (int s = 0; s < 4; ++s) av[s] = rk[4 * s + g];
   ld_slot(sX, lane, bv);  // (L_kk^-1)^T as a B operand
-  const d4_t v = mma16(zero4(), av, bv);
+  const d4_t v = mma16_zero(av, bv);
   if (lane < 16) {
     sU[c] = v[0];
     a.u[16 * kk + c] = v[0];
@@ -310,16 +340,26 @@ __device__ inline void diag_solve(const NllArgs& a, int kk, const double* sX, co
   }
 }
 
-// The residual's update by a panel block: r_i -= L_ik u_k, with L_ik from its
-// row slot (lane (g, c) holds L_ik[c][4s + g]) and u_k in LDS.
-__device__ inline void resid_update(double* ri, const double* slot, const double* uk, int lane) {
+// The residual's update by column k of L: r_i -= L_ik u_k for i = from .. nb - 1,
+// with L_ik from its row slot (lane (g, c) holds L_ik[c][4s + g]) and u_k in
+// LDS; four blocks at a time, their reads first.
+__device__ inline void resid_update(double* sR, const double* pan, const double* uk, int from, int nb, int lane) {
   const int g = lane >> 4;
-  double lv[4];
-  ld_slot(slot, lane, lv);
-  double s = lv[0] * uk[g] + lv[1] * uk[4 + g] + lv[2] * uk[8 + g] + lv[3] * uk[12 + g];
-  s += __shfl_xor(s, 16);
-  s += __shfl_xor(s, 32);
-  if (lane < 16) ri[lane] -= s;
+  const double u[4] = {uk[g], uk[4 + g], uk[8 + g], uk[12 + g]};
+  for (int i0 = from; i0 < nb; i0 += 4) {
+    double lv[4][4], s[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ld_slot(pan + (size_t)min(i0 + q, nb - 1) * 256, lane, lv[q]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] = lv[q][0] * u[0] + lv[q][1] * u[1] + lv[q][2] * u[2] + lv[q][3] * u[3];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] += __shfl_xor(s[q], 16);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] += __shfl_xor(s[q], 32);
+    // group q takes block i0 + q
+    const double mine = g == 0 ? s[0] : (g == 1 ? s[1] : (g == 2 ? s[2] : s[3]));
+    if (i0 + g < nb) sR[16 * i0 + lane] -= mine;
+  }
 }
 
 // ---- kernel A: the Cholesky factor L and the inverses of its diagonal blocks --
@@ -331,236 +371,337 @@ __device__ inline void resid_update(double* ri, const double* slot, const double
 // prefix of its share, so each step's work is balanced and the first kRes
 // blocks of a share, the longest-lived, stay in registers for the whole
 // factorization (the others go through memory each step).
-constexpr int kRes = 8;
+//
+// Bound: late steps by wave 0's chain (block update, factor and inverse, about
+// 6000 cycles a step), early ones by the workers' updates on three SIMDs'
+// matrix units.  m = 256, one launch: 83 us when the workers kept 8 blocks in
+// registers, wave 0 took part in every step's barrier and made u as well, and
+// a block was factored a column at a time; 67 us now (m = 300: 120 -> 98).  20
+// resident blocks are all of a share up to m = 256.  Of the 160,000 cycles
+// 19,000 pass before the first step: 280 KB of K come to one CU.
+constexpr int kRes = 20;
+
+// f(0), f(1), ... (as constants) until one is false.
+template <typename F, int... N>
+__device__ inline void while_true(F&& f, std::integer_sequence<int, N...>) {
+  (void)(f(std::integral_constant<int, N>()) && ...);
+}
 
 __global__ __launch_bounds__(kNllThreads) void nll_factor_kernel(NllArgs a) {
   extern __shared__ __align__(16) double sm[];
   const int nb = a.nb, d = a.d;
-  double* sPan = sm;                          // 2 x nb row slots: the panels of columns k and k + 1
-  double* sX = sPan + (size_t)2 * nb * 256;   // row slot: the inverse of the newest diagonal factor
-  double* sDiag = sX + 256;                   // 2 x 256: the next diagonal blocks as updated (C layout)
-  double* sProd = sDiag + 512;                // per diagonal block: product of its pivots
-  double* sR = sProd + SCOOT_MAX_OBS / 16;    // nb x 16: r, then the forward substitution's residual
-  double* sU = sR + (size_t)nb * 16;          // 2 x 16: u_k, by k % 2
-  // [0] a pivot not above its floor, [1] the last diagonal block factored,
-  // [2] a wait for it ran out
-  int* sFlag = reinterpret_cast<int*>(sU + 32);
-  int* sSimd = sFlag + 4;                     // kNllWaves: the SIMD each wave runs on
-  int* sList = sSimd + kNllWaves;             // the worker blocks, (i << 8) | j
+  double* sPan = sm;                                // 2 x (nb - 1) row slots: the panels of two columns, rows 1 ..
+  double* sX = sPan + (size_t)2 * (nb - 1) * 256;   // 3 row slots: the inverse of diagonal factor k, by k % 3
+  double* sDiag = sX + 768;                         // the next diagonal block as updated (column slot)
+  double* sOff = sDiag + 256;                       // the block left of it as updated, transposed (column slot)
+  double* sProd = sOff + 256;                       // per diagonal block: product of its pivots
+  double* sR = sProd + SCOOT_MAX_OBS / 16;          // nb x 16: r, then the forward substitution's residual
+  double* sU = sR + (size_t)nb * 16;                // 16: u_k
+  // [0] bit 0: a pivot not above its floor, bit 1: a wait ran out; [1] the last
+  // diagonal block factored; [2] arrivals at the steps' barriers; [3] blocks
+  // handed to wave 0
+  int* sFlag = reinterpret_cast<int*>(sU + 16);
+  int* sSimd = sFlag + 4;                           // kNllWaves: the SIMD each wave runs on
+  int* sList = sSimd + kNllWaves;                   // the worker blocks, (i << 8) | j
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (lane == 0) sSimd[wave] = (int)((__builtin_amdgcn_s_getreg((31 << 11) | 4) >> 4) & 3);  // HW_ID.SIMD_ID
-  if (tid < 4) sFlag[tid] = 0;
-  for (int i = tid; i < nb * 16; i += kNllThreads) sR[i] = a.r[i];
-  const int n_list = nb > 1 ? nb * (nb - 1) / 2 - 1 : 0;
-  for (int n = tid; n < n_list; n += kNllThreads) {
-    int start = 0;
-    for (int j = nb - 1; j >= 1; --j) {
-      const int lo = j == 1 ? 2 : j, cnt = nb - lo;
-      if (n < start + cnt) {
-        sList[n] = ((lo + n - start) << 8) | j;
+  if (tid < 4) sFlag[tid] = tid == 1 ? -1 : 0;
+  lds_barrier();
+
+  // Every wait ends: when the flag is there, when something has failed (false),
+  // or after a bounded number of looks (false).
+  auto flag = [&](int f) { return __hip_atomic_load(&sFlag[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+  auto wait = [&](int f, int value) {
+    bool alive = true;
+    for (int looks = 0;; ++looks) {
+      const int now = flag(f), failed = flag(0);
+      alive = __builtin_amdgcn_readfirstlane(failed) == 0;
+      if (__builtin_amdgcn_readfirstlane(now) >= value || !alive) break;
+      if (looks > (1 << 21)) {
+        if (lane == 0) __hip_atomic_fetch_or(&sFlag[0], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        alive = false;
         break;
       }
-      start += cnt;
+      __builtin_amdgcn_s_sleep(1);
     }
-  }
-  const double s2 = exp(a.theta[d]), tau2 = exp(a.theta[d + 1]);
-  // A pivot that is not above 1e-13 of its original diagonal entry (s2 + tau2)
-  // means K is not numerically positive definite (the host factor's rule).
-  const double floor = 1e-13 * (s2 + tau2);
-  lds_barrier();
+    wave_lds_sync();
+    return alive;
+  };
+  auto signal = [&](int f) {  // after this wave's LDS writes
+    wave_lds_sync();
+    if (lane == 0) __hip_atomic_fetch_add(&sFlag[f], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  // The n-th barrier (from 1) of all waves but wave 0, which runs ahead.
+  auto step_barrier = [&](int n) {
+    signal(2);
+    return wait(2, (kNllWaves - 1) * n);
+  };
+  auto panel = [&](int k) { return sPan + ((size_t)(k & 1) * (nb - 1)) * 256 - 256; };  // of column k, by row
+  auto inverse = [&](int k) { return sX + (size_t)(k % 3) * 256; };
+
   // The trailing update goes to the waves that do not share wave 0's SIMD:
   // its vector ALU and the matrix unit are one datapath, so a neighbour's
   // matrix instructions would stall the factorization.
-  int worker = -1, W = 0;
-  for (int w = 1; w < kNllWaves; ++w)
+  // One that does (wave 0 itself if there is none) makes u.
+  int worker = -1, W = 0, solver = 0;
+  for (int w = kNllWaves - 1; w >= 1; --w)
     if (sSimd[w] != sSimd[0]) {
       if (w == wave) worker = W;
       ++W;
+    } else {
+      solver = w;
     }
   if (W == 0) {  // every wave on one SIMD: all but wave 0 work
     worker = wave - 1;
     W = kNllWaves - 1;
+    solver = 0;
   }
+  worker = __builtin_amdgcn_readfirstlane(worker);
+  W = __builtin_amdgcn_readfirstlane(W);
+  solver = __builtin_amdgcn_readfirstlane(solver);
   // a worker's blocks among the first S of the list; the blocks with j >= c
   // are the first (nb - c)(nb - c + 1) / 2 (less (1, 1) when c = 1)
-  auto mine_below = [&](int S) { return S > worker ? (S - 1 - worker) / W + 1 : 0; };
+  const unsigned inv_W = 65536u / (unsigned)W + 1;  // x / W = x inv_W >> 16 for the list's x < 2^10
+  auto mine_below = [&](int S) { return S > worker ? (int)(((unsigned)(S - 1 - worker) * inv_W) >> 16) + 1 : 0; };
   auto from_col = [&](int c) { return (nb - c) * (nb - c + 1) / 2 - (c <= 1 ? 1 : 0); };
+  auto solve = [&](int k) {  // u_k
+    diag_solve(a, k, inverse(k), sR + 16 * k, sU, lane);
+    wave_lds_sync();
+  };
+  auto solve_step = [&](int k) {
+    solve(k);
+    resid_update(sR, panel(k), sU, k + 1, nb, lane);
+    wave_lds_sync();
+  };
+  if (wave == solver) {
+    for (int i = lane; i < nb * 16; i += 64) sR[i] = a.r[i];
+    wave_lds_sync();
+  }
 
   // ---- Cholesky factor, 16 columns per step --------------------------------
   // Before step k the panel of column k, L_ik (i > k), is in row slots and
-  // L_kk^-1 in sX.  Step k: wave 0 updates block (k+1, k+1), factors and
-  // inverts it; the workers apply column k to their blocks with j >= k+1,
-  // A_ij^T -= L_jk L_ik^T (block (k+2, k+2) also to wave 0 through LDS), and
-  // once wave 0 has published the new inverse turn their blocks of column
-  // k+1 into the panel, L_i,k+1^T = L_k+1,k+1^-1 A_i,k+1^T.  The waves share
-  // data through LDS only (a worker reads back only blocks it wrote), so the
-  // one barrier per step does not wait for global stores.
-  constexpr int kCol0 = (SCOOT_MAX_OBS / 16 - 1 + kNllWaves - 2) / (kNllWaves - 1);  // column-0 blocks per wave
-  double c0[kCol0][4];
-  d4_t res[kRes];  // a worker's first kRes blocks (transposed, C layout)
-  int rij[kRes];
-  const int n_share = worker >= 0 ? mine_below(n_list) : 0;
-#pragma unroll
-  for (int s = 0; s < kRes; ++s) rij[s] = s < n_share ? __builtin_amdgcn_readfirstlane(sList[worker + W * s]) : 0;
+  // L_kk^-1 in sX.  Step k: the workers apply column k to their blocks with
+  // j >= k+1, A_ij^T -= L_jk L_ik^T, hand blocks (k+2, k+2) and (k+2, k+1) to
+  // wave 0 through LDS, and once wave 0 has published the new inverse turn
+  // their blocks of column k+1 into the panel,
+  // L_i,k+1^T = L_k+1,k+1^-1 A_i,k+1^T; the solver takes u_k = L_kk^-1 r_k and
+  // column k's term off the residuals below.  Wave 0 makes L_k+1,k for itself
+  // from the blocks handed over one step earlier, applies it to block
+  // (k+1, k+1), factors and inverts that block, takes the next two blocks and
+  // publishes the inverse; so it never waits for a panel, and the workers'
+  // writes of a step (after the previous inverse) meet no read of the
+  // step before.  An inverse is read by the solver one step later, while wave
+  // 0 may be one step ahead: three slots.  The waves share data through LDS
+  // only (a worker reads back only blocks it wrote), so no wait covers global
+  // stores.  Every role has a loop of its own, so that the workers' resident
+  // blocks hold no registers where wave 0 factors.
   if (wave == 0) {
-    diag_factor(a, 0, ld_c(a.L, lane), sX, sProd, sFlag, floor, lane);
-    wave_lds_sync();
-    diag_solve(a, 0, sX, sR, sU, lane);
+    const double s2 = exp(a.theta[d]), tau2 = exp(a.theta[d + 1]);
+    // A pivot that is not above 1e-13 of its original diagonal entry (s2 + tau2)
+    // means K is not numerically positive definite (the host factor's rule).
+    const double floor = 1e-13 * (s2 + tau2);
+    d4_t D = ld_c(a.L, lane), Dn = zero4();
+    double off[4] = {0.0, 0.0, 0.0, 0.0};
+    if (nb > 1) {  // blocks (1, 1) and (1, 0): the covariance itself
+      Dn = ld_c(a.L + ((size_t)nb + 1) * 256, lane);
+      ld_cols(a.L + (size_t)nb * 256, lane, off);
+    }
+    bool alive = true;
+    for (int k = 0; k < nb && alive; ++k) {
+      diag_factor(a, k, D, inverse(k), sProd, sFlag, floor, lane);
+      if (k >= 1 && k + 1 < nb) {  // blocks (k+1, k+1) and (k+1, k), column k-1 applied
+        alive = wait(3, 2 * k);
+        double dv[4];
+        ld_slot(sDiag, lane, dv);
+        ld_slot(sOff, lane, off);
+        Dn = d4_t{dv[0], dv[1], dv[2], dv[3]};
+      }
+      wave_lds_sync();  // the inverse is in LDS, the blocks are read
+      if (lane == 0) __hip_atomic_store(&sFlag[1], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (k + 1 < nb) {
+        double xv[4];
+        ld_slot(inverse(k), lane, xv);
+        const d4_t v = mma16_zero(xv, off);  // L_k+1,k^T: both operands of its product as it stands
+        const double av[4] = {-v[0], -v[1], -v[2], -v[3]}, bv[4] = {v[0], v[1], v[2], v[3]};
+        D = Dn + mma16_zero(av, bv);
+        if (solver == 0) {
+          alive = wait(2, (kNllWaves - 1) * (k + 1)) && alive;  // the panel of column k is made
+          solve_step(k);
+        }
+      }
+    }
   } else {
-    // the blocks of column 0, while wave 0 factors block (0, 0)
+    constexpr int kCol0 = (SCOOT_MAX_OBS / 16 - 1 + kNllWaves - 2) / (kNllWaves - 1);  // column-0 blocks per wave
+    double c0[kCol0][4];
+    d4_t res[kRes];  // a worker's first kRes blocks (transposed, C layout)
+    unsigned rij[kRes / 2];  // their (i << 8) | j, two to a register
+    const int n_list = nb > 1 ? nb * (nb - 1) / 2 - 1 : 0;
+    const int n_share = worker >= 0 ? mine_below(n_list) : 0;
+    // while wave 0 factors block (0, 0): column 0, the list, the resident blocks
 #pragma unroll
     for (int t = 0; t < kCol0; ++t) {
       const int i = wave + (kNllWaves - 1) * t;
       if (i < nb) ld_cols(a.L + (size_t)i * nb * 256, lane, c0[t]);  // A_i0^T as a B operand
     }
-  }
-  lds_barrier();
-  // the panel of column 0: L_i0^T = L_00^-1 A_i0^T (C layout, so column-major
-  // to memory and a row slot of L_i0 as it stands)
-  if (wave != 0) {
-    double xv[4];
-    ld_slot(sX, lane, xv);
-#pragma unroll
-    for (int t = 0; t < kCol0; ++t) {
-      const int i = wave + (kNllWaves - 1) * t;
-      if (i < nb) {
-        const d4_t v = mma16(zero4(), xv, c0[t]);
-        st_c(a.L + (size_t)i * nb * 256, v, lane);
-        st_col_slot(sPan + (size_t)i * 256, v, lane);
+    int first = (1 << 8) | 1;  // lane e: the worker's entry e < 64 (a block that exists, past its share)
+    for (int e = lane; e < n_share; e += 64) {  // the worker's own entries
+      int n = worker + W * e;
+      for (int j = nb - 1; j >= 1; --j) {
+        const int lo = j == 1 ? 2 : j, cnt = nb - lo;
+        if (n < cnt) {
+          sList[worker + W * e] = ((lo + n) << 8) | j;
+          if (e == lane) first = ((lo + n) << 8) | j;
+          break;
+        }
+        n -= cnt;
       }
     }
-    // the worker's resident blocks
+    auto entry = [&](int e) {
+      return e < 64 ? __builtin_amdgcn_readlane(first, e) : __builtin_amdgcn_readfirstlane(sList[worker + W * e]);
+    };
 #pragma unroll
-    for (int s = 0; s < kRes; ++s)
-      if (s < n_share) res[s] = ld_c(a.L + ((size_t)(rij[s] >> 8) * nb + (rij[s] & 255)) * 256, lane);
-  }
-  lds_barrier();
-  int cur = 0;
-  for (int k = 0; k + 1 < nb; ++k, cur ^= 1) {
-    if (sFlag[0] || sFlag[2]) break;
-    const double* pc = sPan + (size_t)cur * nb * 256;  // panel of column k
-    double* pn = sPan + (size_t)(cur ^ 1) * nb * 256;  // panel of column k + 1, being made
-    if (wave == 0) {
-      const int i = k + 1;
-      // block (k+1, k+1) as the previous step's update left it (from its
-      // worker through LDS, buffer k % 2; at k = 0 the covariance itself)
-      const double* dg = sDiag + (k & 1) * 256;
-      d4_t acc = k == 0 ? ld_c(a.L + ((size_t)i * nb + i) * 256, lane)
-                        : d4_t{dg[lane], dg[64 + lane], dg[128 + lane], dg[192 + lane]};
-      double av[4], bv[4];
-      ld_slot(pc + (size_t)i * 256, lane, bv);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) av[s] = -bv[s];
-      acc = mma16(acc, av, bv);
-      diag_factor(a, i, acc, sX, sProd, sFlag, floor, lane);
-      wave_lds_sync();  // the inverse is in LDS
-      if (lane == 0) __hip_atomic_store(&sFlag[1], i, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-      // while the workers make the panel: the residual of block k+1 takes
-      // column k's last term (the other blocks' come from the workers this
-      // step), then u_k+1
-      resid_update(sR + 16 * i, pc + (size_t)i * 256, sU + (k & 1) * 16, lane);
-      diag_solve(a, i, sX, sR + 16 * i, sU + (i & 1) * 16, lane);
-    } else if (worker >= 0) {
-      const int n_trail = mine_below(from_col(k + 2));  // the share's blocks with j >= k+2
-      const int n_act = mine_below(from_col(k + 1));    // ... with j >= k+1
-      double* sNext = sDiag + ((k + 1) & 1) * 256;
-      // the inverse of block (k+1, k+1) from wave 0 (a bounded wait)
-      bool have_x = false;
+    for (int s = 0; s < kRes; ++s) {
+      const int ij = __builtin_amdgcn_readlane(first, s);
+      rij[s / 2] = s & 1 ? rij[s / 2] | (unsigned)ij << 16 : (unsigned)ij;
+      res[s] = zero4();
+      if (s < n_share) res[s] = ld_c(a.L + ((size_t)(ij >> 8) * nb + (ij & 255)) * 256, lane);
+    }
+    // all here: a register with a load in flight would make every later use of
+    // it, in the loop too, wait for the stores issued since
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    // the panel of column 0: L_i0^T = L_00^-1 A_i0^T (C layout, so column-major
+    // to memory and a row slot of L_i0 as it stands)
+    wait(1, 0);
+    {
       double xv[4];
-      auto wait_x = [&]() {
-        if (have_x) return;
-        for (int spins = 0; __hip_atomic_load(&sFlag[1], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < k + 1;) {
-          if (++spins > (1 << 22)) {
-            if (lane == 0) sFlag[2] = 1;
-            break;
-          }
-          __builtin_amdgcn_s_sleep(2);
+      ld_slot(inverse(0), lane, xv);
+#pragma unroll
+      for (int t = 0; t < kCol0; ++t) {
+        const int i = wave + (kNllWaves - 1) * t;
+        if (i < nb) {
+          const d4_t v = mma16_zero(xv, c0[t]);
+          st_c(a.L + (size_t)i * nb * 256, v, lane);
+          st_col_slot(panel(0) + (size_t)i * 256, v, lane);
         }
-        wave_lds_sync();
-        ld_slot(sX, lane, xv);
-        have_x = true;
+      }
+    }
+    bool alive = step_barrier(1);
+    for (int k = 0; k + 1 < nb && alive; ++k) {
+      if (wave == solver) solve_step(k);
+      const double* pc = panel(k);
+      double* pn = panel(k + 1);  // being made
+      const int n_trail = worker >= 0 ? mine_below(from_col(k + 2)) : 0;  // the share's blocks with j >= k+2
+      const int n_act = worker >= 0 ? mine_below(from_col(k + 1)) : 0;    // ... with j >= k+1
+      // block (k+2, k+2), the first of its column, is entry e_diag of the share
+      const int at_diag = from_col(k + 3) - worker;
+      const int e_diag = k + 2 < nb && at_diag >= 0 && (mine_below(from_col(k + 3) + 1) - 1) * W == at_diag
+                             ? mine_below(from_col(k + 3) + 1) - 1 : -1;
+      // Updated block e of the share: those of column k+1 wait in the new
+      // panel's slots, (k+2, k+2) and (k+2, k+1) go to wave 0 as well.
+      auto updated = [&](int e, int i, const d4_t& v) {
+        if (e >= n_trail && e < n_act && i > k + 1) {
+          st_col_slot(pn + (size_t)i * 256, v, lane);
+          if (i == k + 2) {
+            st_col_slot(sOff, v, lane);
+            signal(3);
+          }
+        }
+        if (e == e_diag) {
+          st_col_slot(sDiag, v, lane);
+          signal(3);
+        }
       };
-      // resident blocks: the update
+      // resident blocks, two at a time (block (k+1, k+1) and a block that has
+      // died are updated to no effect); the first pair past the share ends it,
+      // so that a late step does not step over every dead pair
+      auto update_pair = [&](auto pair) {
+        constexpr int s = 2 * decltype(pair)::value;
+        if (s >= n_act) return false;
+        double av[2][4], bv[2][4];
 #pragma unroll
-      for (int s = 0; s < kRes; ++s) {
-        const int i = rij[s] >> 8, j = rij[s] & 255;
-        if (s < n_act && !(i == k + 1 && j == k + 1)) {
-          double av[4], bv[4];
-          ld_slot(pc + (size_t)j * 256, lane, av);
-          ld_slot(pc + (size_t)i * 256, lane, bv);
+        for (int u = 0; u < 2; ++u) {
+          ld_slot(pc + (size_t)((rij[s / 2] >> (16 * u)) & 255) * 256, lane, av[u]);
+          ld_slot(pc + (size_t)((rij[s / 2] >> (16 * u + 8)) & 255) * 256, lane, bv[u]);
+        }
 #pragma unroll
-          for (int q = 0; q < 4; ++q) av[q] = -av[q];
-          res[s] = mma16(res[s], av, bv);
-          if (i == k + 2 && j == k + 2) st_c(sNext, res[s], lane);
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            res[s + u] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[u][q], bv[u][q], res[s + u], 0, 0, 0);
+        if (s + 1 >= n_trail || s == (e_diag & ~1)) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u) updated(s + u, (rij[s / 2] >> (16 * u + 8)) & 255, res[s + u]);
         }
         __builtin_amdgcn_sched_barrier(0);  // a block's operands loaded where it is updated
-      }
-      // column k's term of the forward substitution for the blocks below k+1,
-      // r_i -= L_ik u_k, round robin over the workers
-      for (int i = k + 2 + worker; i < nb; i += W) resid_update(sR + 16 * i, pc + (size_t)i * 256, sU + (k & 1) * 16, lane);
-      // the others, four at a time, their loads first: the blocks with
-      // j >= k+2 back to memory, then those of column k+1 into the panel
+        return true;
+      };
+      while_true(update_pair, std::make_integer_sequence<int, kRes / 2>());
+      // the others, four at a time, their loads first; the blocks with
+      // j >= k+2 go back to memory
       for (int e0 = kRes; e0 < n_act; e0 += 4) {
         d4_t acc[4];
         int ij[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          ij[u] = __builtin_amdgcn_readfirstlane(sList[worker + W * (e0 + u < n_act ? e0 + u : e0)]);
+          ij[u] = entry(e0 + u < n_act ? e0 + u : e0);
           acc[u] = ld_c(a.L + ((size_t)(ij[u] >> 8) * nb + (ij[u] & 255)) * 256, lane);
         }
+        // all four here, used or not: registers with a load in flight would make
+        // later code wait for every store too
+        __builtin_amdgcn_s_waitcnt(0x0f70);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int i = ij[u] >> 8, j = ij[u] & 255;
-          if (e0 + u < n_act && !(i == k + 1 && j == k + 1)) {
+          if (e0 + u < n_act) {
             double av[4], bv[4];
             ld_slot(pc + (size_t)j * 256, lane, av);
             ld_slot(pc + (size_t)i * 256, lane, bv);
 #pragma unroll
             for (int q = 0; q < 4; ++q) av[q] = -av[q];
             acc[u] = mma16(acc[u], av, bv);
-            if (e0 + u < n_trail) {
-              st_c(a.L + ((size_t)i * nb + j) * 256, acc[u], lane);
-              if (i == k + 2 && j == k + 2) st_c(sNext, acc[u], lane);
-            }
-          }
-        }
-        if (e0 + 3 >= n_trail) {  // a block of column k+1 among the four
-          wait_x();
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int i = ij[u] >> 8;
-            if (e0 + u >= n_trail && e0 + u < n_act && i != k + 1) {
-              const double tv[4] = {acc[u][0], acc[u][1], acc[u][2], acc[u][3]};
-              const d4_t v = mma16(zero4(), xv, tv);
-              st_c(a.L + ((size_t)i * nb + k + 1) * 256, v, lane);
-              st_col_slot(pn + (size_t)i * 256, v, lane);
-            }
+            if (e0 + u < n_trail) st_c(a.L + ((size_t)i * nb + j) * 256, acc[u], lane);
+            updated(e0 + u, i, acc[u]);
           }
         }
       }
-      // resident blocks of column k+1: the panel
-      if (n_trail < kRes && n_trail < n_act) {
-        wait_x();
-#pragma unroll
-        for (int s = 0; s < kRes; ++s) {
-          const int i = rij[s] >> 8;
-          if (s >= n_trail && s < n_act && i != k + 1) {
-            const double tv[4] = {res[s][0], res[s][1], res[s][2], res[s][3]};
-            const d4_t v = mma16(zero4(), xv, tv);
-            st_c(a.L + ((size_t)i * nb + k + 1) * 256, v, lane);
-            st_col_slot(pn + (size_t)i * 256, v, lane);
-          }
-          __builtin_amdgcn_sched_barrier(0);
+      // the panel of column k+1, two blocks at a time, the blocks' own reads
+      // before the wait for the inverse
+      double xv[4];
+      bool have_x = false;
+      for (int e = n_trail; e < n_act; e += 2) {
+        const int i0 = entry(e) >> 8, i1 = entry(e + 1 < n_act ? e + 1 : e) >> 8;
+        double t0[4], t1[4];
+        ld_slot(pn + (size_t)i0 * 256, lane, t0);
+        ld_slot(pn + (size_t)i1 * 256, lane, t1);
+        if (!have_x) {
+          if (i0 == k + 1 && (e + 1 == n_act || i1 == k + 1)) continue;  // block (k+1, k+1) alone
+          wait(1, k + 1);
+          ld_slot(inverse(k + 1), lane, xv);
+          have_x = true;
+        }
+        const d4_t v0 = mma16_zero(xv, t0), v1 = mma16_zero(xv, t1);
+        if (i0 != k + 1) {
+          st_col_slot(pn + (size_t)i0 * 256, v0, lane);
+          st_c(a.L + ((size_t)i0 * nb + k + 1) * 256, v0, lane);
+        }
+        if (i1 != i0) {
+          st_col_slot(pn + (size_t)i1 * 256, v1, lane);
+          st_c(a.L + ((size_t)i1 * nb + k + 1) * 256, v1, lane);
         }
       }
+      alive = step_barrier(k + 2);
     }
-    lds_barrier();
   }
+  if (wave == solver) {
+    if (wait(1, nb - 1)) solve(nb - 1);
+  }
+  lds_barrier();  // all waves
   // status: 1 factored, 0 not positive definite, 2 a wait ran out (reported as
   // a device failure)
-  const double status = sFlag[2] ? 2.0 : (sFlag[0] ? 0.0 : 1.0);
+  const int failed = flag(0);
+  const double status = (failed & 2) ? 2.0 : (failed ? 0.0 : 1.0);
   if (tid == 0) {
     a.out[1] = status;
     a.hout[0] = status;
@@ -857,7 +998,7 @@ class DeviceNll {
         hipMemcpyAsync(rd, rp.data(), mp * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return fail(SCOOT_ERR_DEVICE, std::string("gp nll: upload failed: ") + hipGetErrorString(hipGetLastError()));
-    lds_ = ((size_t)nb_ * 512 + 256 + 512 + SCOOT_MAX_OBS / 16 + (size_t)nb_ * 16 + 32) * sizeof(double) +
+    lds_ = ((size_t)(nb_ - 1) * 512 + 768 + 512 + SCOOT_MAX_OBS / 16 + (size_t)nb_ * 16 + 16) * sizeof(double) +
            (4 + kNllWaves + (size_t)nb_ * (nb_ - 1) / 2) * sizeof(int);
 
     int rc = allow_full_lds((const void*)nll_factor_kernel, "gp nll");
