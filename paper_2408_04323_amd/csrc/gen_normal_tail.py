@@ -9,8 +9,17 @@ to follow the 1 / x^2 tail), minimising the relative error: linearised least
 squares iterated on the previous denominator (Sanathanan-Koerner), then
 reweighted towards the largest errors (Lawson).  Prints the two coefficient
 lists and the achieved relative error in double and in float32 Horner
-evaluation.  Run: python gen_normal_tail.py
+evaluation.
+
+For the fp64 kernels phi(0) g(x) (x + K)^2 is expanded in Chebyshev polynomials
+of y, r = 1 / (x + K) mapped linearly from x = 0 .. 39 to 1 .. -1 (the rational
+variable with which Shepherd and Laframboise, Math. Comp. 36 (1981), expand
+erfcx), in 60 digits, and printed as powers of y.  K = 5 gives the fastest
+decay: the first term left out is below 1e-17 of the value.
+
+Run: python gen_normal_tail.py
 """
+import mpmath as mp
 import numpy as np
 from scipy.special import erfcx
 
@@ -54,7 +63,37 @@ def eval_f32(p, q, x):
     return (P / Q).astype(np.float32)
 
 
+K64, X64, DEG64 = 5, 39, 24
+
+
+def fit64():
+    mp.mp.dps = 60
+    r0, r1 = mp.mpf(1) / (X64 + K64), mp.mpf(1) / K64
+    n = DEG64 + 16
+    c = [mp.mpf(0)] * (DEG64 + 1)
+    for i in range(n):
+        a = mp.pi * (2 * i + 1) / (2 * n)
+        r = (r0 + r1) / 2 + (r1 - r0) / 2 * mp.cos(a)
+        x = 1 / r - K64
+        g = 1 - x * mp.sqrt(mp.pi / 2) * mp.exp(x * x / 2) * mp.erfc(x / mp.sqrt(2))
+        for k in range(DEG64 + 1):
+            c[k] += (2 if k else 1) * g / r ** 2 / mp.sqrt(2 * mp.pi) * mp.cos(k * a) / n
+    power = [mp.mpf(0)] * (DEG64 + 1)
+    t0, t1 = [mp.mpf(1)], [mp.mpf(0), mp.mpf(1)]  # T_k in powers of y
+    for k in range(DEG64 + 1):
+        for e, v in enumerate(t0):
+            power[e] += c[k] * v
+        nxt = [mp.mpf(0)] + [2 * v for v in t1]
+        for e, v in enumerate(t0):
+            nxt[e] -= v
+        t0, t1 = t1, nxt
+    return 2 / (r1 - r0), -(r1 + r0) / (r1 - r0), power
+
+
 if __name__ == "__main__":
+    a64, b64, power64 = fit64()
+    print("fp64: y = a r + b, a, b =", mp.nstr(a64, 20), mp.nstr(b64, 20))
+    print("powers of y:", ", ".join(mp.nstr(v, 20) for v in power64))
     x, y, p, q, e = fit()
     e32 = np.max(np.abs((eval_f32(p, q, x).astype(np.float64) - y) / y))
     assert np.min(np.polyval(q[::-1], x / SCALE)) >= 1.0

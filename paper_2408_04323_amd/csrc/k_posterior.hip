@@ -34,6 +34,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "normal.h"
 
 namespace scoot {
 
@@ -45,9 +46,7 @@ typedef double d4_t __attribute__((ext_vector_type(4)));
 // E[(c - Y)^+] for Y ~ N(mu, sd^2), in double (epilogue only).
 __device__ inline double partial_expectation_d(double c, double mu, double sd) {
   if (!(sd > 0)) return fmax(c - mu, 0.0);
-  double u = (c - mu) / sd;
-  return sd * (u * 0.5 * erfc(-u * 0.70710678118654752440) +
-               0.39894228040143267794 * exp(-0.5 * u * u));
+  return sd * h_normal((c - mu) / sd);
 }
 
 // ---------------------------------------------------------------------------
@@ -394,7 +393,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
     }
   }
   // The EI of the candidates whose mean and deviation this lane has written;
-  // in a loop of its own, so that the constants of erfc and exp hold no
+  // in a loop of its own, so that the constants of the tail and exp hold no
   // registers beside the accumulators.
   if (ei_out && wave == 0) {
     for (tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {

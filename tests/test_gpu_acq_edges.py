@@ -1,0 +1,47 @@
+"""The fp64 normal partial expectation behind EI and EHVI: EI against 60-digit
+arithmetic over the whole range of u = (best + xi - mu) / sigma, from where the
+density underflows to where it no longer matters, either side of every end of
+the approximation, and at the special values."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+mp = pytest.importorskip("mpmath")
+
+import paper_2408_04323_amd as S  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _ei(mu, sd, best, dtype):
+    out = S.acq_ei(torch.tensor(mu, dtype=dtype, device="cuda:0"), torch.tensor(sd, dtype=dtype, device="cuda:0"),
+                   best, xi=0.0)
+    torch.cuda.synchronize()
+    return out.cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("lo,hi", [(-37.0, -20.0), (-20.0, -5.5), (-5.5, -4.5), (-4.5, -1.0), (-1.0, 1.0), (1.0, 6.0),
+                                   (6.0, 60.0)])
+def test_ei_f64_relative_error(lo, hi):
+    print("[case] ei", lo, hi, flush=True)
+    mp.mp.dps = 400
+    u = np.concatenate([np.random.default_rng(int(lo * 10) & 255).uniform(lo, hi, 301), [lo, hi, 0.5 * (lo + hi)]])
+    got = _ei(-u, np.ones_like(u), 0.0, torch.float64)  # best - mu = u exactly, sd = 1
+    want = [mp.mpf(v) * mp.erfc(-mp.mpf(v) / mp.sqrt(2)) / 2 + mp.exp(-mp.mpf(v) ** 2 / 2) / mp.sqrt(2 * mp.pi)
+            for v in u]
+    err = max(abs(float((mp.mpf(float(a)) - b) / b)) for a, b in zip(got, want))
+    # polynomial, exp and four products: below ten half-ulps
+    assert err < 10 * 2.0 ** -53, err
+
+
+def test_ei_f64_special_values():
+    print("[case] ei special", flush=True)
+    inf, nan = np.inf, np.nan
+    mu = np.array([0.0, -3.0, 3.0, inf, -inf, nan, 1.0, 39.0, 45.0, -45.0])
+    sd = np.array([1.0, 0.0, 0.0, 1.0, 1.0, 1.0, nan, 1.0, 1.0, 1.0])
+    got = _ei(mu, sd, 0.0, torch.float64)
+    assert got[0] == pytest.approx(0.3989422804014327, rel=1e-15)
+    assert got[1] == 3.0 and got[2] == 0.0          # sd = 0: max(0, best - mu)
+    assert got[3] == 0.0 and got[4] == inf and np.isnan(got[5])
+    assert got[6] == 0.0                            # a NaN sd counts as 0
+    assert 0.0 <= got[7] < 1e-300 and got[8] == 0.0 and got[9] == 45.0
