@@ -88,27 +88,29 @@ __global__ __launch_bounds__(kStripThreads) void ehvi_strip_kernel(const T* __re
 // mask byte form its key in registers (select.h), each wave keeps a running
 // best-q list over its chunks of 64 candidates (a chunk enters the list only
 // when some key beats the list's q-th entry), and at the end the workgroup's
-// sixteen lists are merged into one: part_keys [grid x q] and part_count
+// lists, one per wave, are merged into one: part_keys [grid x q] and part_count
 // [grid] (eligible candidates) go to stage 2.  The EHVI scores are still
 // written.  Workgroups of sixteen waves keep the lists stage 2 reads few
 // (n / 1024 x q) while every wave still scores a single chunk of 64 at the
-// pool sizes of the workloads, as in the plain EHVI kernel.
-constexpr int kStripSelThreads = 1024;
-constexpr int kStripSelWaves = kStripSelThreads / 64;
-
-template <typename T, typename K, int P, typename Table>
-__global__ __launch_bounds__(kStripSelThreads) void ehvi_strip_select_kernel(
+// pool sizes of the workloads, as in the plain EHVI kernel; pools that would
+// leave compute units without such a workgroup get smaller ones, and about as
+// many lists as a pool that fills the chip: eight waves, 131,072 candidates in
+// fp64 50 -> 32 us, a pass of 100,003 candidates in fp32 114.6 -> 109.7, one of
+// four waves 113.1 (more lists for stage 2 than it saves).
+template <typename T, typename K, int P, int THREADS, typename Table>
+__global__ __launch_bounds__(THREADS) void ehvi_strip_select_kernel(
     const T* __restrict__ mu0, const T* __restrict__ mu1, const T* __restrict__ sd0, const T* __restrict__ sd1,
     const Table hi, int n_boxes, int64_t n, T* __restrict__ out, const uint8_t* __restrict__ mask, int q,
     K* __restrict__ part_keys, int32_t* __restrict__ part_count) {
-  __shared__ K wave_lists[kStripSelWaves * SCOOT_MAX_Q];
-  __shared__ int32_t wave_valid[kStripSelWaves];
+  constexpr int WAVES = THREADS / 64;
+  __shared__ K wave_lists[WAVES * SCOOT_MAX_Q];
+  __shared__ int32_t wave_valid[WAVES];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   K list{};
   int32_t valid = 0;
-  for (int64_t base = ((int64_t)blockIdx.x * kStripSelWaves + wave) * 64; base < n;
-       base += (int64_t)gridDim.x * kStripSelThreads) {
+  for (int64_t base = ((int64_t)blockIdx.x * WAVES + wave) * 64; base < n;
+       base += (int64_t)gridDim.x * THREADS) {
     const int64_t c = base + lane;
     const bool live = c < n;
     const int64_t ci = live ? c : n - 1;
@@ -129,19 +131,19 @@ __global__ __launch_bounds__(kStripSelThreads) void ehvi_strip_select_kernel(
   if (lane == 0) wave_valid[wave] = valid;
   __syncthreads();
   if (wave != 0) return;
-  K keys[kStripSelWaves];  // kStripSelWaves x q <= kStripSelWaves x 64 entries
+  K keys[WAVES];  // WAVES x q <= WAVES x 64 entries
 #pragma unroll
-  for (int j = 0; j < kStripSelWaves; ++j) {
+  for (int j = 0; j < WAVES; ++j) {
     const int i = j * 64 + lane;
-    keys[j] = i < kStripSelWaves * q ? wave_lists[i] : K{};
+    keys[j] = i < WAVES * q ? wave_lists[i] : K{};
   }
   K merged{};
-  wave_select<K, kStripSelWaves>(keys, merged, q);
+  wave_select<K, WAVES>(keys, merged, q);
   if (lane < q) part_keys[(int64_t)blockIdx.x * q + lane] = merged;
   if (lane == 0) {
     int32_t sum = 0;
 #pragma unroll
-    for (int w = 0; w < kStripSelWaves; ++w) sum += wave_valid[w];
+    for (int w = 0; w < WAVES; ++w) sum += wave_valid[w];
     part_count[blockIdx.x] = sum;
   }
 }
@@ -225,17 +227,23 @@ struct StripSelect {
   int q;
   void* part_keys;
   int32_t* part_count;
-  int blocks;
+  int threads, blocks;
 };
 
 template <typename T, int P, typename Table>
 void launch_strip(const T* m0, const T* m1, const T* s0, const T* s1, const Table& tab, int nbx, int64_t n, T* out,
                   const StripSelect* sel, int64_t blocks, hipStream_t s) {
   typedef typename std::conditional<std::is_same<T, float>::value, Key64, Key128>::type K;
-  if (sel)
-    hipLaunchKernelGGL((ehvi_strip_select_kernel<T, K, P, Table>), dim3((unsigned)sel->blocks),
-                       dim3(kStripSelThreads), 0, s, m0, m1, s0, s1, tab, nbx, n, out, sel->mask, sel->q,
-                       (K*)sel->part_keys, sel->part_count);
+  auto select = [&](auto threads) {
+    constexpr int THREADS = decltype(threads)::value;
+    hipLaunchKernelGGL((ehvi_strip_select_kernel<T, K, P, THREADS, Table>), dim3((unsigned)sel->blocks), dim3(THREADS),
+                       0, s, m0, m1, s0, s1, tab, nbx, n, out, sel->mask, sel->q, (K*)sel->part_keys,
+                       sel->part_count);
+  };
+  if (sel && sel->threads == 1024)
+    select(std::integral_constant<int, 1024>());
+  else if (sel)
+    select(std::integral_constant<int, 512>());
   else
     hipLaunchKernelGGL((ehvi_strip_kernel<T, P, Table>), dim3((unsigned)blocks), dim3(kStripThreads), 0, s, m0, m1,
                        s0, s1, tab, nbx, n, out);
@@ -349,14 +357,20 @@ int launch_ehvi_topq(const void* const* mu, const void* const* sigma, int p, int
   }
   hipStream_t s = (hipStream_t)stream;
   // One chunk of 64 per wave up to 512 workgroups (larger pools loop), and at
-  // most kSelMaxKeys2 keys for stage 2.
-  int64_t blocks = (n + kStripSelThreads - 1) / kStripSelThreads;
-  blocks = std::max<int64_t>(1, std::min<int64_t>({blocks, 512, kSelMaxKeys2 / q}));
+  // most kSelMaxKeys2 keys for stage 2.  Workgroups of sixteen waves, or of
+  // eight where a compute unit would go without one, as long as stage 2, one
+  // workgroup that reads every list, is not given more than 4096 keys for it.
+  int dev = 0, cus = 256;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const int64_t most = std::min<int64_t>(512, kSelMaxKeys2 / q);
+  const int threads = (n + 1023) / 1024 < cus && (n + 511) / 512 * q <= 4096 ? 512 : 1024;
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n + threads - 1) / threads, most));
   const size_t ksz = dt == SCOOT_F32 ? sizeof(Key64) : sizeof(Key128);
   const size_t kbytes = ((size_t)blocks * q * ksz + 255) / 256 * 256;
   unsigned char* ws = (unsigned char*)device_scratch(kbytes + (size_t)blocks * 4, 3);
   if (!ws) return fail(SCOOT_ERR_NO_MEMORY, "ehvi: selection scratch allocation failed");
-  const StripSelect sel{mask, q, ws, reinterpret_cast<int32_t*>(ws + kbytes), (int)blocks};
+  const StripSelect sel{mask, q, ws, reinterpret_cast<int32_t*>(ws + kbytes), threads, (int)blocks};
   const int rc = dt == SCOOT_F32 ? run_ehvi_strip<float>(mu, sigma, p, n, bt, ehvi, s, &sel)
                                  : run_ehvi_strip<double>(mu, sigma, p, n, bt, ehvi, s, &sel);
   if (rc != SCOOT_OK) return rc;

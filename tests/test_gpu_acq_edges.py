@@ -45,3 +45,23 @@ def test_ei_f64_special_values():
     assert got[3] == 0.0 and got[4] == inf and np.isnan(got[5])
     assert got[6] == 0.0                            # a NaN sd counts as 0
     assert 0.0 <= got[7] < 1e-300 and got[8] == 0.0 and got[9] == 45.0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n,q", [(1, 1), (511, 3), (513, 8), (5000, 64), (261120, 5), (261121, 5), (262145, 64)])
+def test_selection_beside_ehvi(n, q, dtype):
+    """The picks that the fused pass makes in its EHVI kernel, with workgroups of
+    eight and of sixteen waves, are those of the selection by itself."""
+    print("[case] select", n, q, dtype, flush=True)
+    rng = np.random.default_rng(n)
+    X, Y = rng.random((24, 4)), rng.standard_normal((24, 2))
+    gps = [S.gp_fit(X, Y[:, j], np.full(4, 0.4), 1.0, 1e-2, dtype=dtype) for j in range(2)]
+    forest = S.forest_create(np.array([0, 0, 0], np.int32), np.array([0.7, 0, 0], np.float32),
+                             np.array([1, -1, -1], np.int32), np.array([2, -1, -1], np.int32),
+                             np.array([0, 65536, 0], np.int32), np.array([0, 3], np.int64), 4)
+    Xc = torch.tensor(rng.random((n, 4), dtype=np.float32), device="cuda:0")
+    b = S.score_pool(gps, forest, Xc, q, Y_obs=Y, ref=Y.max(0) + 0.1)
+    idx, score, n_valid = S.suggest_topq(b.acq, b.mask, q)
+    torch.cuda.synchronize()
+    assert b.idx.tolist() == idx.tolist() and int(b.n_valid) == int(n_valid) == int(b.mask.sum())
+    assert torch.equal(b.score.nan_to_num(-1), score.nan_to_num(-1))
