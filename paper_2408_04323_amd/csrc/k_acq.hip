@@ -154,21 +154,33 @@ __global__ __launch_bounds__(THREADS) void ehvi_strip_select_kernel(
 // of column i (i = 0 .. n0 - 2); the boxes of a column start at j = 0.  The
 // records arrive through wave-uniform (scalar) loads, four boxes per load in
 // the unrolled loop.
+//
+// A workgroup is kEhviWaves waves over the same kEhviThreads candidates: the
+// tables are (n1 + n2) x 64 values whatever the number of waves, 46 KB at a
+// front of 90, so that a compute unit holds three workgroups and one wave each
+// would leave a SIMD idle and the others without a second wave.  The waves
+// share the tables' rows and the columns (ranges of about equal cost, chosen
+// on the host).  Bound: issue, about 50 instructions per partial expectation
+// and nine per box.  2^20 candidates, fronts of 90 (900 boxes): one wave 556
+// us, four 228.
+constexpr int kEhviWaves = 4;
 struct Ehvi3Args {
   int64_t n;
   int n0, n1, n2;
+  int col[kEhviWaves + 1];  // wave w takes columns col[w] .. col[w + 1] - 1
 };
 
 template <typename T>
-__global__ __launch_bounds__(kEhviThreads) void ehvi3_kernel(
+__global__ __launch_bounds__(kEhviThreads* kEhviWaves) void ehvi3_kernel(
     const T* __restrict__ mu0, const T* __restrict__ mu1, const T* __restrict__ mu2,
     const T* __restrict__ sd0, const T* __restrict__ sd1, const T* __restrict__ sd2,
     const T* __restrict__ coords, const uint32_t* __restrict__ rec, const uint32_t* __restrict__ col_end,
     T* __restrict__ out, const Ehvi3Args a) {
   extern __shared__ __align__(16) unsigned char smem[];
   T* g = reinterpret_cast<T*>(smem);  // [n1 + n2][kEhviThreads]: G_1 then G_2
-  const int tid = threadIdx.x;
-  int64_t c = (int64_t)blockIdx.x * kEhviThreads + tid;
+  const int lane = threadIdx.x & (kEhviThreads - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kEhviThreads);
+  int64_t c = (int64_t)blockIdx.x * kEhviThreads + lane;
   const bool live = c < a.n;
   if (!live) c = a.n - 1;
   const T m0 = mu0[c], s0 = sd0[c], r0 = reciprocal(s0);
@@ -177,30 +189,37 @@ __global__ __launch_bounds__(kEhviThreads) void ehvi3_kernel(
   const T* c0 = coords;
   const T* c1 = coords + a.n0;
   const T* c2 = c1 + a.n1;
-  g[tid] = T(0);  // -inf
-  for (int q = 1; q < a.n1; ++q) g[q * kEhviThreads + tid] = partial_expectation<T>(c1[q], m1, s1, r1);
-  g[a.n1 * kEhviThreads + tid] = T(0);
-  for (int q = 1; q < a.n2; ++q)
-    g[(a.n1 + q) * kEhviThreads + tid] = partial_expectation<T>(c2[q], m2, s2, r2);
-  // Each thread reads only its own column: no barrier needed.
-  T acc = T(0), g0_prev = T(0);
-  int b = 0;
-  for (int i = 0; i + 1 < a.n0; ++i) {
+  for (int q = wave; q < a.n1; q += kEhviWaves)  // row 0: -inf
+    g[q * kEhviThreads + lane] = q ? partial_expectation<T>(c1[q], m1, s1, r1) : T(0);
+  for (int q = kEhviWaves - 1 - wave; q < a.n2; q += kEhviWaves)
+    g[(a.n1 + q) * kEhviThreads + lane] = q ? partial_expectation<T>(c2[q], m2, s2, r2) : T(0);
+  __syncthreads();
+  const int first = a.col[wave], last = a.col[wave + 1];
+  T acc = T(0), g0_prev = first > 0 && first < last ? partial_expectation<T>(c0[first], m0, s0, r0) : T(0);
+  int b = first > 0 ? (int)col_end[first - 1] : 0;
+  for (int i = first; i < last; ++i) {
     const T g0 = partial_expectation<T>(c0[i + 1], m0, s0, r0);
     const int end = (int)col_end[i];
     T col = T(0), g1_prev = T(0);
 #pragma unroll 4
     for (; b < end; ++b) {
       const uint32_t r = rec[b];
-      const T g1 = g[(r & 0xFFFFu) * kEhviThreads + tid];
-      const T g2 = g[(r >> 16) * kEhviThreads + tid];
+      const T g1 = g[(r & 0xFFFFu) * kEhviThreads + lane];
+      const T g2 = g[(r >> 16) * kEhviThreads + lane];
       col += (g1 - g1_prev) * g2;
       g1_prev = g1;
     }
     acc += (g0 - g0_prev) * col;
     g0_prev = g0;
   }
-  if (live) out[c] = acc;
+  __syncthreads();  // the tables (four rows and more) are read: the waves' sums take their place
+  g[wave * kEhviThreads + lane] = acc;
+  __syncthreads();
+  if (wave == 0 && live) {
+#pragma unroll
+    for (int w = 1; w < kEhviWaves; ++w) acc += g[w * kEhviThreads + lane];
+    out[c] = acc;
+  }
 }
 
 int launch_ei(const void* mu, const void* sigma, int64_t n, scoot_dtype dt, double c, void* ei,
@@ -328,6 +347,12 @@ int run_ehvi3(const void* const* mu, const void* const* sigma, int64_t n, const 
   }
   if (nb == 0 || col != ncol - 1 || j_next != a.n1 - 1) return fail(SCOOT_ERR_DEVICE, "ehvi: unexpected box layout");
   ce[col] = (uint32_t)nb;
+  // Columns to waves, by boxes and six boxes' worth for a column's G_0.
+  for (int w = 1, i = 0; w <= kEhviWaves; ++w) {
+    const int64_t target = (int64_t)(nb + 6 * ncol) * w / kEhviWaves;
+    while (i < ncol && (w == kEhviWaves || (int64_t)ce[i] + 6 * (i + 1) <= target)) ++i;
+    a.col[w] = i;
+  }
   void* dev = device_scratch(blob.size(), 1);
   if (!dev) return fail(SCOOT_ERR_NO_MEMORY, "ehvi: device scratch allocation failed");
   int rc = upload_async(dev, blob.data(), blob.size(), 0, s);
@@ -338,7 +363,7 @@ int run_ehvi3(const void* const* mu, const void* const* sigma, int64_t n, const 
   const unsigned grid = (unsigned)((n + kEhviThreads - 1) / kEhviThreads);
   rc = allow_full_lds((const void*)ehvi3_kernel<T>, "ehvi");
   if (rc != SCOOT_OK) return rc;
-  hipLaunchKernelGGL(ehvi3_kernel<T>, dim3(grid), dim3(kEhviThreads), lds, s, (const T*)mu[0], (const T*)mu[1],
+  hipLaunchKernelGGL(ehvi3_kernel<T>, dim3(grid), dim3(kEhviThreads * kEhviWaves), lds, s, (const T*)mu[0], (const T*)mu[1],
                      (const T*)mu[2], (const T*)sigma[0], (const T*)sigma[1], (const T*)sigma[2], coords, recs,
                      col_end, (T*)out, a);
   hipError_t err = hipGetLastError();

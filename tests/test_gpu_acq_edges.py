@@ -65,3 +65,28 @@ def test_selection_beside_ehvi(n, q, dtype):
     torch.cuda.synchronize()
     assert b.idx.tolist() == idx.tolist() and int(b.n_valid) == int(n_valid) == int(b.mask.sum())
     assert torch.equal(b.score.nan_to_num(-1), score.nan_to_num(-1))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64], ids=["f32", "f64"])
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 7, 40])
+def test_ehvi_three_objectives_few_columns(m, dtype):
+    """Fronts of as many columns as the workgroup has waves, fewer and more, at
+    pools around a workgroup's 64 candidates, against the oracle."""
+    from oracle.hypervolume import ehvi, nondominated
+
+    rng = np.random.default_rng(m)
+    Y = rng.random((m, 3))
+    Y /= Y.sum(1, keepdims=True)  # every point on the front
+    ref = np.full(3, 1.1)
+    for n in (1, 63, 64, 65, 200):
+        print("[case] ehvi3", m, n, dtype, flush=True)
+        mu, sd = rng.random((n, 3)), np.abs(rng.normal(0, 0.3, (n, 3)))
+        sd[0] = 0.0
+        mu, sd = ([torch.tensor(v[:, j], dtype=dtype, device="cuda:0") for j in range(3)] for v in (mu, sd))
+        got = S.acq_ehvi(mu, sd, Y, ref).cpu().numpy().astype(np.float64)
+        held = [np.stack([v.cpu().numpy().astype(np.float64) for v in a], axis=1) for a in (mu, sd)]
+        want = ehvi(held[0], held[1], nondominated(Y, ref), ref)
+        eps = 2.0 ** (-24 if dtype == torch.float32 else -53)
+        # three factors good to about eight eps of themselves (the float partial
+        # expectation to 4e-7), whose differences telescope over at most m + 1 columns
+        assert np.max(np.abs(got - want)) <= 24 * eps * (m + 3) * np.max(want)
