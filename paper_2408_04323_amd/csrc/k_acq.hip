@@ -15,9 +15,9 @@
 //   each cut along the second axis into consecutive ranges [b_j, b_k] over
 //   which the open region is [-inf, h] on the third.  Per column the EHVI
 //   term is (G_0(a_{i+1}) - G_0(a_i)) * sum over its boxes of
-//   (G_1(b_k) - G_1(b_j)) * G_2(h): each thread tabulates G_1 and G_2 at
-//   their axes' coordinates in its own LDS column, evaluates G_0 once per
-//   column, carries G_1 from one box to the next (the ranges are
+//   (G_1(b_k) - G_1(b_j)) * G_2(h): the waves tabulate G_1 and G_2 at
+//   their axes' coordinates in a candidate's LDS column, evaluate G_0 once per
+//   column, carry G_1 from one box to the next (the ranges are
 //   consecutive), so a box costs two table reads, a subtraction and an fma;
 //   the box records (k, h) arrive through wave-uniform loads.
 #include <hip/hip_runtime.h>
