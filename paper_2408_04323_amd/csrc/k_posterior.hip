@@ -164,6 +164,10 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
   constexpr int CT = 4 / RS;      // 16-candidate tiles whose K* this wave makes
   constexpr int NP = 2 * CT;      // pieces of that work, two observations each
   constexpr int PPS = (NP + NBW - 1) / NBW;  // pieces beside a slot, in order
+  // A wave of one slot and one tile of 16 candidates to generate has little to
+  // hide the chain of distances behind: it runs under the product's first
+  // instructions (m = 128, n = 3000 8.4 -> 7.9 us; more slots: slower).
+  constexpr bool EARLY = CT == 1 && NBW == 1;
   const NegPairs neg;
   __shared__ PostLds<S, RS> sm;
   const int tid = threadIdx.x;
@@ -233,13 +237,16 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
   d4_t cr;
   float m_part;
   unsigned pk[3][2];
+  auto distances = [&](int q) {
+    cr = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      cr = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], sm.bq[wave * CT + q][s][lane], cr, 0, 0, 0);
+  };
   auto piece = [&](int p, int to_buf) {
     const int q = p >> 1, h = p & 1;
     if (h == 0) {
-      cr = d4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int s = 0; s < S; ++s)
-        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], sm.bq[wave * CT + q][s][lane], cr, 0, 0, 0);
+      if constexpr (!EARLY) distances(q);
       m_part = 0.0f;
     }
     float kv[2];
@@ -281,6 +288,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
 #pragma unroll
   for (int k = 0; k < KA; ++k) load_unit(k, first_unit(k));
   operands();
+  if constexpr (EARLY) distances(0);
 #pragma unroll
   for (int p = 0; p < NP; ++p) piece(p, 0);
   int buf = 0;  // the buffer that holds K* of the block being multiplied
@@ -327,6 +335,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
         noff = 0;
         nlive = a.nb32;
       }
+      if constexpr (EARLY) distances(0);
 #pragma unroll
       for (int t = 0; t < NBW; ++t) {
         if (r + RS * t < live) {
@@ -762,6 +771,19 @@ int run32(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, f
 template <int S>
 int run32_by_rows(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, float* ei, const Post32& a,
                   hipStream_t s) {
+  // Two waves share a tile where the pool fills the chip, four where it does
+  // not: a tile alone takes them half the time, m = 128, n = 3000 12.1 -> 7.9
+  // us, m = 224 20.0 -> 13.0.  The line: two-wave workgroups come four to a CU
+  // (six up to m = 128), and four waves are the faster ones up to about three
+  // tiles per CU (n = 48,000, m = 256 35.7 -> 30.3, but 64,000 38.6 -> 40.1), and
+  // at m <= 128 up to the start of the second round of six (n = 100,000, m = 128
+  // 31.0 -> 27.4, but 262,144 54.5 -> 58.1).
+  int dev = 0, cus = 256;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const int64_t tiles = (n + kPostTile - 1) / kPostTile;
+  if (a.nb32 <= 4 && tiles <= 7 * (int64_t)cus) return run32<S, 4, 1, 1, 2>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 8 && tiles <= 3 * (int64_t)cus) return run32<S, 4, 2, 2, 2>(g, Xc, n, mu, sd, ei, a, s);
   if (a.nb32 <= 4) return run32<S, 2, 2, 2, 3>(g, Xc, n, mu, sd, ei, a, s);
   if (a.nb32 <= 8) return run32<S, 2, 4, 3, 2>(g, Xc, n, mu, sd, ei, a, s);
   if (a.nb32 <= 16) return run32<S, 4, 4, 4, 2>(g, Xc, n, mu, sd, ei, a, s);
