@@ -149,13 +149,14 @@ GPDevice describe(const FitHost& f, const double* warp_a, const double* warp_b, 
   g.s2 = f.s2;
   g.tau2 = f.tau2;
   g.c = f.c;
+  g.s2_exp = f.s2_exp;
   for (int k = 0; k < SCOOT_MAX_DIM; ++k) {
     g.scale64[k] = k < f.d ? f.scale[k] : 0.0;
     g.scale32[k] = (float)g.scale64[k];
   }
   for (int i = 0; i < 3; ++i) {
     g.coef64[i] = f.coef[i];
-    g.coef32[i] = (float)f.coef[i];
+    g.coef32[i] = (float)std::ldexp(f.coef[i], -2 * g.s2_exp);
   }
   g.warp = warp_a != nullptr;
   for (int k = 0; k < SCOOT_MAX_DIM; ++k) {
@@ -228,7 +229,7 @@ int gp_from_fit(const FitHost& f, const double* warp_a, const double* warp_b, sc
     std::memcpy(img.data() + L.xs, xs.data(), xs.size() * 8);
     std::memcpy(img.data() + L.alpha, f.alpha.data(), sizeof(double) * m);
     for (int i = 0; i < m; ++i) {
-      const float av = (float)f.alpha[i];
+      const float av = (float)std::ldexp(f.alpha[i], 2 * g.s2_exp);
       std::memcpy(img.data() + L.alpha32 + (size_t)i * 4, &av, 4);
     }
     hipError_t e = hipMalloc(&g.buf, img.size());
@@ -255,7 +256,7 @@ int gp_from_factor(const FitHost& f, const double* warp_a, const double* warp_b,
     if (hipMalloc(&g.buf, L.bytes) != hipSuccess)
       return fail(SCOOT_ERR_NO_MEMORY, "gp fit: device allocation failed");
     L.place(g);
-    int rc = launch_pack_f32(Xi, nbf, alpha, f.m, f.nb, g.buf, (double*)g.alpha, (float*)g.alpha32, stream);
+    int rc = launch_pack_f32(Xi, nbf, alpha, f.m, f.nb, g.s2_exp, g.buf, (double*)g.alpha, (float*)g.alpha32, stream);
     if (rc == SCOOT_OK) {
       hipError_t e = hipMemcpyAsync((void*)g.xs, xs.data(), xs.size() * 8, hipMemcpyHostToDevice, (hipStream_t)stream);
       if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);

@@ -63,6 +63,8 @@ int fit_setup(const double* X, const double* y, int m, int d, scoot_kernel kerne
   f.s2 = s2;
   f.tau2 = tau2;
   f.c = c;
+  const int e = std::ilogb(s2);
+  f.s2_exp = (e - (e & 1)) / 2;
   const double root = kernel == SCOOT_MATERN52 ? kSqrt5 : kSqrt3;  // sqrt(2 nu)
   f.coef[0] = s2;
   f.coef[1] = s2 * kLn2;
@@ -136,11 +138,12 @@ int fit_host(const double* X, const double* y, int m, int d, scoot_kernel kernel
 // observation block j = 0 .. ceil(m / 16) - 1 outermost, then row blocks P =
 // nb - 1 down to j / 2.  Every entry is the sum of three bfloat16 values
 // (rounded to nearest, each the next one's remainder: 24 bits and more of the
-// double), a part per 1 KiB: lane l holds L^-1[32P + l % 32][16j + 8 (l / 32) + i],
+// double), a part per 1 KiB: lane l holds 2^s2_exp L^-1[32P + l % 32][16j + 8 (l / 32) + i],
 // i = 0..7, as four words of two,
 //   word index = ((unit * 3 + part) * 64 + l) * 4 + i / 2, the low half first.
 void pack_linv_f32(const FitHost& f, std::vector<float>& out) {
   const int nb = f.nb, m = f.m, nj = (m + 15) / 16;
+  const double times = std::ldexp(1.0, f.s2_exp);
   out.assign((size_t)post_units(nj, nb) * 3 * 64 * 4, 0.0f);
   unsigned char* units = reinterpret_cast<unsigned char*>(out.data());
   // a row block's units are its own, so row blocks run in parallel
@@ -152,7 +155,7 @@ void pack_linv_f32(const FitHost& f, std::vector<float>& out) {
           const int c0 = 16 * j + 8 * half, cols = std::min(8, row + 1 - c0);
           if (cols <= 0) continue;
           double v[8] = {};
-          std::memcpy(v, &f.Linv[(size_t)row * m + c0], sizeof(double) * cols);
+          for (int i = 0; i < cols; ++i) v[i] = f.Linv[(size_t)row * m + c0 + i] * times;
           uint16_t h[3][8];
           for (int part = 0; part < 3; ++part)
             for (int i = 0; i < 8; ++i) {

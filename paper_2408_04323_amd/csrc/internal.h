@@ -191,6 +191,7 @@ struct FitHost {
   int m = 0, d = 0, m_pad = 0, nb = 0;     // nb = m_pad / 32
   scoot_kernel kernel = SCOOT_MATERN52;
   double s2 = 1, tau2 = 0, c = 0;
+  int s2_exp = 0;                          // s2 in [1, 4) times 4^s2_exp
   std::vector<double> L;                   // m x m row-major lower factor
   std::vector<double> Linv;                // m x m row-major lower inverse factor
   std::vector<double> alpha;               // m
@@ -320,14 +321,19 @@ struct GPDevice {
   int m = 0, d = 0, m_pad = 0, nb = 0;
   double s2 = 1, tau2 = 0, c = 0;
   void* buf = nullptr;        // one allocation holding everything below
-  const void* linv = nullptr; // packed L^-1 (float or double)
+  const void* linv = nullptr; // packed L^-1 (fp32: times 2^s2_exp, as three-part bfloat16 splits; fp64: double)
   const void* xs = nullptr;   // fp32: the augmented observation rows (pack_obs_f32, double);
                               // fp64: m_pad x kXsStride scaled rows, alpha_i in column d when d < kXsStride
   const double* alpha = nullptr;  // m_pad
-  const float* alpha32 = nullptr; // m_pad, float copy
+  const float* alpha32 = nullptr; // m_pad, float copy of alpha times 4^s2_exp
   float scale32[SCOOT_MAX_DIM];
   double scale64[SCOOT_MAX_DIM];
-  float coef32[3];
+  // fp32, s2_exp as in FitHost: covariances are held divided by 4^s2_exp and
+  // L^-1 multiplied by 2^s2_exp, so that neither overflows, nor do the
+  // low parts of their splits leave bfloat16's range, whatever the signal
+  // variance; powers of two, so that no other result depends on it.
+  int s2_exp = 0;
+  float coef32[3];                // divided by 4^s2_exp
   double coef64[3];
   bool warp = false;              // candidates go through kumaraswamy(x, warp_a, warp_b) first
   double warp_a[SCOOT_MAX_DIM];
@@ -363,8 +369,8 @@ int launch_posterior(const GPDevice& g, const float* Xc, int64_t n, void* mu, vo
                      void* stream, bool xc_warped = false);
 // The units of pack_linv_f32 and alpha's two copies (m_pad entries), from a
 // factorization's L^-1 blocks on the device.
-int launch_pack_f32(const double* Xi, int nbf, const double* alpha, int m, int nb32, void* linv, double* alpha64,
-                    float* alpha32, void* stream);
+int launch_pack_f32(const double* Xi, int nbf, const double* alpha, int m, int nb32, int s2_exp, void* linv,
+                    double* alpha64, float* alpha32, void* stream);
 int launch_warp_pool(const GPDevice& g, const float* Xc, int64_t n, float* out, void* stream);
 int launch_ei(const void* mu, const void* sigma, int64_t n, scoot_dtype dt, double c, void* ei,
               void* stream);

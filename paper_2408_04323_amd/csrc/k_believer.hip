@@ -64,7 +64,8 @@ struct KbGp {
   float* sd_out;              // n
   double scale[SCOOT_MAX_DIM];
   double c0d, c1d, c2d, s2, tau2;
-  float c0, c1, c2;
+  double vscale, bscale;  // 2^-s2_exp for products with linv, 4^s2_exp for beta beside covariances
+  float c0, c1, c2;       // divided by 4^s2_exp
   int m, nj, nb32, m_pad, S;
 };
 struct KbArgs {
@@ -85,7 +86,7 @@ __device__ inline double kb_obs(const KbGp& g, int i, int k) {
   const int r = i & 15, t = 4 * (r & 3) + (r >> 2);
   return 0.5 * g.xq[((size_t)(i >> 4) * g.S + (k >> 2)) * 64 + 16 * (k & 3) + t];
 }
-// Eight consecutive entries of a row of L^-1 (the lane's, of one unit).
+// Eight consecutive entries of a row of 2^s2_exp L^-1 (the lane's, of one unit).
 __device__ inline void kb_unit(const KbGp& g, int unit, int lane, double (&a)[8]) {
   const u4_t* at = reinterpret_cast<const u4_t*>(g.linv + (size_t)unit * 3 * 64 * 16) + lane;
   const u4_t p0 = at[0], p1 = at[64], p2 = at[128];
@@ -162,7 +163,8 @@ __global__ __launch_bounds__(256) void kb_v_kernel(const KbArgs a, int k) {
   acc += __shfl_xor(acc, 32);
   if (lane < 32) part[wave][lane] = acc;
   __syncthreads();
-  if (tid < 32) g.v[32 * P + tid] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+  if (tid < 32)
+    g.v[32 * P + tid] = g.vscale * ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]));
 }
 
 // beta_k = L^-T v, one block of 16 columns per workgroup.
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(256) void kb_beta_kernel(const KbArgs a, int k) {
   __syncthreads();
   if (tid < 16)
     g.beta[(size_t)k * g.m_pad + 16 * j + tid] =
-        (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+        g.vscale * ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]));
 }
 
 // Row k of L_S.  C_p(x_k) = k(x_k, x_p) - beta_p . k(X, x_k), where
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
   if constexpr (!LIST) {
     for (int i = tid; i < g.nj * 16 * kPicks; i += 256) {
       const int j = i / (16 * kPicks), p = (i / 16) % kPicks;
-      beta_l[i] = p < kn ? g.beta[(size_t)(k0 + p) * g.m_pad + 16 * j + (i & 15)] : 0.0;
+      beta_l[i] = p < kn ? g.bscale * g.beta[(size_t)(k0 + p) * g.m_pad + 16 * j + (i & 15)] : 0.0;
     }
     __syncthreads();
   }
@@ -339,8 +341,11 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
 #pragma unroll
     for (int p = 0; p < kPicks; ++p) {
       if (p < kn) {
-        const d4_t b = LIST ? *reinterpret_cast<const d4_t*>(g.beta + (size_t)(k0 + p) * g.m_pad + 16 * j + 4 * gr)
-                            : *reinterpret_cast<const d4_t*>(beta_l + (j * kPicks + p) * 16 + 4 * gr);
+        d4_t b;
+        if constexpr (LIST)
+          b = g.bscale * *reinterpret_cast<const d4_t*>(g.beta + (size_t)(k0 + p) * g.m_pad + 16 * j + 4 * gr);
+        else
+          b = *reinterpret_cast<const d4_t*>(beta_l + (j * kPicks + p) * 16 + 4 * gr);
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -614,6 +619,8 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
     o.c0d = g[j]->coef64[0];
     o.c1d = g[j]->coef64[1];
     o.c2d = g[j]->coef64[2];
+    o.vscale = std::ldexp(1.0, -g[j]->s2_exp);
+    o.bscale = std::ldexp(1.0, 2 * g[j]->s2_exp);
     o.c0 = g[j]->coef32[0];
     o.c1 = g[j]->coef32[1];
     o.c2 = g[j]->coef32[2];

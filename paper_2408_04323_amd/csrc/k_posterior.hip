@@ -107,8 +107,8 @@ struct Post32 {
   int nj, nb32;  // observation blocks of 16, row blocks of 32
   int d;
   double scale[SCOOT_MAX_DIM];
-  float c0, c1, c2;
-  double s2, prior, ei_c;
+  float c0, c1, c2;  // K* is made divided by 4^s2_exp
+  double s2, vscale, prior, ei_c;  // vscale = 4^s2_exp: a squared norm times it is part of the variance
 };
 
 constexpr int kUnitBytes = 3 * 64 * 16;   // a unit's three parts in A-operand order
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
       double sq = 0.0;
 #pragma unroll
       for (int w = 0; w < RS; ++w) sq += sm.sq[w][lane];
-      const double sd = sqrt(fmax(a.s2 - sq, 0.0));
+      const double sd = sqrt(fmax(a.s2 - a.vscale * sq, 0.0));
       const double mu = a.prior + sm.mu[lane];
       mu_out[cand] = (float)mu;
       sd_out[cand] = (float)sd;
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void posterior_f64_kernel(
 // and the upload (m = 300: 0.7 MiB down and 0.33 MiB up).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void pack_f32_kernel(const double* __restrict__ Xi, int nbf,
-                                                      const double* __restrict__ alpha, int m, int nb32,
+                                                      const double* __restrict__ alpha, int m, int nb32, double lscale,
                                                       u4_t* __restrict__ linv, double* __restrict__ alpha64,
                                                       float* __restrict__ alpha32) {
   const int j = blockIdx.x, P = blockIdx.y, lane = threadIdx.x;
@@ -665,7 +665,7 @@ __global__ __launch_bounds__(64) void pack_f32_kernel(const double* __restrict__
     for (int i = lane; i < nb32 * 32; i += 64) {
       const double v = i < m ? alpha[i] : 0.0;
       alpha64[i] = v;
-      alpha32[i] = (float)v;
+      alpha32[i] = (float)(v * lscale * lscale);
     }
   }
   if (P < j / 2) return;
@@ -679,7 +679,8 @@ __global__ __launch_bounds__(64) void pack_f32_kernel(const double* __restrict__
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const int c = col + 2 * i + q;
-      v[q] = row < m && c <= row ? Xi[((size_t)(row >> 4) * nbf + (c >> 4)) * 256 + (row & 15) * 16 + (c & 15)] : 0.0;
+      const double* blk = Xi + ((size_t)(row >> 4) * nbf + (c >> 4)) * 256;
+      v[q] = row < m && c <= row ? lscale * blk[(row & 15) * 16 + (c & 15)] : 0.0;
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
@@ -693,10 +694,11 @@ __global__ __launch_bounds__(64) void pack_f32_kernel(const double* __restrict__
   for (int p = 0; p < 3; ++p) linv[((size_t)unit * 3 + p) * 64 + lane] = part[p];
 }
 
-int launch_pack_f32(const double* Xi, int nbf, const double* alpha, int m, int nb32, void* linv, double* alpha64,
-                    float* alpha32, void* stream) {
+int launch_pack_f32(const double* Xi, int nbf, const double* alpha, int m, int nb32, int s2_exp, void* linv,
+                    double* alpha64, float* alpha32, void* stream) {
   hipLaunchKernelGGL(pack_f32_kernel, dim3((unsigned)((m + 15) / 16), (unsigned)nb32), dim3(64), 0,
-                     (hipStream_t)stream, Xi, nbf, alpha, m, nb32, (u4_t*)linv, alpha64, alpha32);
+                     (hipStream_t)stream, Xi, nbf, alpha, m, nb32, std::ldexp(1.0, s2_exp), (u4_t*)linv, alpha64,
+                     alpha32);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(SCOOT_ERR_DEVICE, std::string("gp fit: pack launch: ") + hipGetErrorString(err));
   return SCOOT_OK;
@@ -842,6 +844,7 @@ int launch_posterior(const GPDevice& g, const float* Xc, int64_t n, void* mu, vo
     a.c1 = g.coef32[1];
     a.c2 = g.coef32[2];
     a.s2 = g.s2;
+    a.vscale = std::ldexp(1.0, 2 * g.s2_exp);
     a.prior = g.c;
     a.ei_c = ei_c ? *ei_c : 0.0;
     float* e = ei_c ? (float*)ei : nullptr;
