@@ -25,15 +25,25 @@
 // the workloads (2^20 candidates, front of about 30) that is tens to a few
 // thousand candidates per pick instead of the pool: a suggestion of eight
 // took 12.4 ms when every pick streamed V = L^-1 K*^T (4.3 GB) from memory.
+//
+// Where many candidates score alike the list is long.  A bound that equals the
+// best score cannot beat it, nor win the tie from a higher index, so such a
+// candidate is not listed (all scores zero, or a pool far from every
+// observation).  A list longer than kListed is not scored: a sample of it is,
+// whose best is a better guess, and a second list holds what can still win
+// against that.  Everything that decides is a set, so that the order in which
+// the lists fill does not show.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
 #include "internal.h"
+#include "select.h"
 
 namespace scoot {
 
@@ -43,9 +53,12 @@ typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef double d4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kTop = 8;     // candidates a selection returns: the pick and the next round's first guesses
+constexpr int kTop = 8;     // candidates of a selection: the pick and the next round's first guesses
 constexpr int kPicks = 8;   // picks whose covariances one pass over the observations makes
-constexpr int kListed = 16384;   // list entries scored without waiting for their count
+constexpr int kListed = 16384;   // the longest list scored without waiting for its length
+// More candidates than this are taken 64 to a wave: a workgroup of that form for
+// every compute unit.
+constexpr int64_t kWide = 65536;
 constexpr double kSlack = 1e-4;  // of the best score, against rounding of the bounds
 
 // One objective: its GP, the pool as the GP sees it, and what the picks left.
@@ -110,17 +123,24 @@ struct KbInfo {
   float score, mu[SCOOT_MAX_OBJECTIVES];
 };
 
-// After a selection: the pick joins the list of picks and leaves the pool, the
-// host's figures are gathered, and the list is emptied.
+// The pick, of a selection (idx given) or of the best key that scoring the
+// guesses and a list has found, unless that list was too long to be scored: it
+// joins the list of picks and leaves the pool, the host's figures are gathered,
+// and the list is emptied.
 __global__ void kb_pick_kernel(const KbArgs a, const int64_t* __restrict__ idx, const float* __restrict__ score,
-                               int k, uint8_t* __restrict__ elig, int64_t* __restrict__ picks,
-                               KbInfo* __restrict__ info, int32_t* __restrict__ count) {
-  const int64_t pick = idx[0];
+                               const unsigned long long* __restrict__ top, int64_t cap, int k,
+                               uint8_t* __restrict__ elig, int64_t* __restrict__ picks, KbInfo* __restrict__ info,
+                               int32_t* __restrict__ count) {
   const int t = threadIdx.x;
+  const int32_t listed = count[0];
+  const Key64 key{*top};
+  int64_t pick = idx ? idx[0] : (key.zero() ? -1 : key_index(key));
+  if (listed > cap) pick = -1;
+  __syncthreads();  // the count is read
   if (t == 0) {
     info->pick = pick;
-    info->count = count[0];
-    info->score = score[0];
+    info->count = listed;
+    info->score = idx ? score[0] : key_score(key);
     count[0] = 0;
     if (pick >= 0) {
       picks[k] = pick;
@@ -130,9 +150,6 @@ __global__ void kb_pick_kernel(const KbArgs a, const int64_t* __restrict__ idx, 
   if (t < a.p && pick >= 0) info->mu[t] = a.g[t].mu[pick];
 }
 __global__ void kb_zero_kernel(int32_t* count) { count[0] = 0; }
-__global__ void kb_unpick_kernel(const int64_t* __restrict__ picks, int k, uint8_t* __restrict__ elig) {
-  elig[picks[k]] = 1;
-}
 
 // v = L^-1 k(X, x_k), one row block of 32 per workgroup.
 __global__ __launch_bounds__(256) void kb_v_kernel(const KbArgs a, int k) {
@@ -167,11 +184,9 @@ __global__ __launch_bounds__(256) void kb_v_kernel(const KbArgs a, int k) {
     g.v[32 * P + tid] = g.vscale * ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]));
 }
 
-// beta_k = L^-T v, one block of 16 columns per workgroup.
-__global__ __launch_bounds__(256) void kb_beta_kernel(const KbArgs a, int k) {
-  const KbGp& g = a.g[blockIdx.y];
+// beta_k = L^-T v, a block of 16 columns.
+__device__ inline void kb_beta(const KbGp& g, int j, int k) {
   __shared__ double part[4][16];
-  const int j = blockIdx.x;
   if (j >= g.nj) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double acc[8] = {};
@@ -195,8 +210,7 @@ __global__ __launch_bounds__(256) void kb_beta_kernel(const KbArgs a, int k) {
 
 // Row k of L_S.  C_p(x_k) = k(x_k, x_p) - beta_p . k(X, x_k), where
 // k(X, x_k) . beta_p = (L v_k) . (L^-T v_p): the covariances are made again.
-__global__ __launch_bounds__(256) void kb_chol_kernel(const KbArgs a, int k) {
-  const KbGp& g = a.g[blockIdx.x];
+__device__ inline void kb_chol(const KbArgs& a, const KbGp& g, int k) {
   __shared__ double ks[SCOOT_MAX_OBS + 32];
   __shared__ double row[SCOOT_MAX_Q + 1];
   __shared__ double var[4];
@@ -249,30 +263,38 @@ __global__ __launch_bounds__(256) void kb_chol_kernel(const KbArgs a, int k) {
   }
 }
 
+// Both need v and not each other: the last workgroup of a row takes the latter.
+__global__ __launch_bounds__(256) void kb_join_kernel(const KbArgs a, int k) {
+  const KbGp& g = a.g[blockIdx.y];
+  if (blockIdx.x + 1 < gridDim.x) kb_beta(g, (int)blockIdx.x, k);
+  else kb_chol(a, g, k);
+}
+
 // sigma after the picks k0 + kn (those before k0 through their stored w).
-// LIST: 16 list entries per workgroup, its four waves sharing the
-// observations, min(n, *live) entries (live nullable); otherwise 64 candidates per wave, four per workgroup.  K* as
-// in the posterior (distances on the fp64 matrix cores), the dot products in
-// double.  Bound (whole pool, m = 512, eight picks): the covariances, as in
-// the posterior.
-template <int S, bool LIST>
+// Of a list (list or list64 given; the results go beside it) or of the pool: n
+// entries or (live given) *live, none if that is more than n.  NARROW: 16
+// candidates per workgroup, its four waves sharing the observations; otherwise
+// 64 candidates per wave.  K* as in the posterior (distances on the fp64 matrix
+// cores), the dot products in double.  Bound (whole pool, m = 512, eight
+// picks): the covariances, as in the posterior.
+template <int S, bool NARROW>
 __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const int32_t* __restrict__ list,
                                                           const int64_t* __restrict__ list64,
                                                           const int32_t* __restrict__ live, int64_t n, int k0, int kn,
                                                           int last) {
-  constexpr int NT = LIST ? 1 : 4;
+  constexpr int NT = NARROW ? 1 : 4;
   const KbGp& g = a.g[blockIdx.y];
   if (g.S != S) return;
   extern __shared__ __align__(16) unsigned char smem[];
-  double* beta_l = reinterpret_cast<double*>(smem);  // [nj][kPicks][16]; LIST: [4 waves][16][kPicks]
+  double* beta_l = reinterpret_cast<double*>(smem);  // [nj][kPicks][16]; NARROW: [4 waves][16][kPicks]
   const int tid = threadIdx.x, lane = tid & 63, gr = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t base = LIST ? (int64_t)blockIdx.x * 16 : (int64_t)blockIdx.x * 256 + wave * 64;
-  if constexpr (LIST) {
-    if (live) n = min(n, (int64_t)*live);
+  const int64_t base = NARROW ? (int64_t)blockIdx.x * 16 : (int64_t)blockIdx.x * 256 + wave * 64;
+  if constexpr (NARROW) {
+    if (live) n = *live <= n ? *live : 0;
     if (base >= n) return;
   }
-  if constexpr (!LIST) {
+  if constexpr (!NARROW) {
     for (int i = tid; i < g.nj * 16 * kPicks; i += 256) {
       const int j = i / (16 * kPicks), p = (i / 16) % kPicks;
       beta_l[i] = p < kn ? g.bscale * g.beta[(size_t)(k0 + p) * g.m_pad + 16 * j + (i & 15)] : 0.0;
@@ -285,7 +307,8 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
   for (int t = 0; t < NT; ++t) {
     const int64_t e = min(base + t * 16 + c, n - 1);
     cand[t] = e;
-    if constexpr (LIST) cand[t] = max(list64 ? list64[e] : (int64_t)list[e], (int64_t)0);
+    if (list64) cand[t] = max(list64[e], (int64_t)0);
+    else if (list) cand[t] = list[e];
     double nrm = 0.0;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -306,7 +329,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int p = 0; p < kPicks; ++p) acc[t][p] = 0.0;
-  if constexpr (LIST) {
+  if constexpr (NARROW) {
     // k(x, x_p), one pick per lane group (the waves' sums are added below)
     const int p = wave * 4 + gr;
     if (p < kn) {
@@ -322,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
       for (int q = 0; q < kPicks; ++q) acc[0][q] = q == p ? kx : 0.0;
     }
   }
-  for (int j = LIST ? wave : 0; j < g.nj; j += LIST ? 4 : 1) {
+  for (int j = NARROW ? wave : 0; j < g.nj; j += NARROW ? 4 : 1) {
     double aq[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) aq[s] = (g.xq + (size_t)j * S * 64)[(unsigned)(s * 64 + lane)];
@@ -342,7 +365,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
     for (int p = 0; p < kPicks; ++p) {
       if (p < kn) {
         d4_t b;
-        if constexpr (LIST)
+        if constexpr (NARROW)
           b = g.bscale * *reinterpret_cast<const d4_t*>(g.beta + (size_t)(k0 + p) * g.m_pad + 16 * j + 4 * gr);
         else
           b = *reinterpret_cast<const d4_t*>(beta_l + (j * kPicks + p) * 16 + 4 * gr);
@@ -353,7 +376,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
       }
     }
   }
-  // the lane groups' shares; LIST: the waves' too
+  // the lane groups' shares; NARROW: the waves' too
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -363,7 +386,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
     }
   double C[kPicks];
   int64_t e, x;
-  if constexpr (LIST) {
+  if constexpr (NARROW) {
     if (gr == 0)
 #pragma unroll
       for (int p = 0; p < kPicks; ++p) beta_l[(wave * 16 + c) * kPicks + p] = acc[0][p];
@@ -382,6 +405,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
       C[p] = gr == 0 ? acc[0][p] : (gr == 1 ? acc[NT > 1 ? 1 : 0][p] : (gr == 2 ? acc[NT > 2 ? 2 : 0][p] : acc[NT - 1][p]));
     e = base + lane;
     x = min(e, n - 1);
+    if (list) x = list[x];
   }
   if (e >= n) return;
   const double s0 = (double)g.sd0[x];
@@ -395,7 +419,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
     if (p < kn) {
       const double* l = g.ls + (size_t)(k0 + p) * a.q;
       double w = C[p];
-      if constexpr (!LIST) {
+      if constexpr (!NARROW) {
         const float* xr = g.xc + x * a.d;
         const float* xp = g.xc + a.picks[k0 + p] * a.d;
         double r2 = 0.0;
@@ -415,7 +439,7 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
   }
   if (last) {
     const float sd = (float)sqrt(fmax(var, 0.0));
-    if constexpr (LIST) {
+    if (list || list64) {
       g.sd_list[e] = sd;
       g.mu_list[e] = g.mu[x];
     } else {
@@ -424,43 +448,118 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
   }
 }
 
-// Lists the candidates that can still win: eligible, and a bound that reaches
-// the best score of the first guesses (less the slack).
+// The largest key of a wave, on every lane.
+__device__ inline unsigned long long kb_wave_max(unsigned long long key) {
+  for (int o = 32; o >= 1; o >>= 1) {
+    const unsigned long long other = __shfl_xor(key, o);
+    key = other > key ? other : key;
+  }
+  return key;
+}
+
+// Lists the candidates that can still win: eligible, and a bound that beats the
+// best of the first guesses (kTop - 1, at idx) or comes within the slack of it,
+// but for exact ties.  !FIRST: a bound that beats top, the best key that scoring
+// the guesses and the sample has found, and a hash of the index of at most limit.
+// Entries past cap are counted only.  One addition to the count per workgroup
+// and 1024 candidates: with one per wave, where every wave lists something, the
+// additions to one address were the kernel's time (n = 2^20: 65-120 us, now 8).
+constexpr int kCompact = 4;  // candidates per thread
+template <bool FIRST>
 __global__ __launch_bounds__(256) void kb_compact_kernel(const float* __restrict__ bound,
                                                          const uint8_t* __restrict__ elig, int64_t n,
                                                          const int64_t* __restrict__ idx,
-                                                         const float* __restrict__ first, int n_first,
-                                                         int32_t* __restrict__ list, int32_t* __restrict__ count) {
-  const int lane = threadIdx.x & 63;
+                                                         const float* __restrict__ first, uint32_t limit,
+                                                         unsigned long long* __restrict__ top,
+                                                         int32_t* __restrict__ list, int64_t cap,
+                                                         int32_t* __restrict__ count) {
+  __shared__ int in_wave[4];
+  __shared__ int start;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  unsigned long long key = 0;
   float best = -INFINITY;
-  if (lane < n_first && idx[lane] >= 0) best = first[lane] >= best ? first[lane] : best;
-  for (int o = 32; o >= 1; o >>= 1) best = fmaxf(best, __shfl_xor(best, o));
-  const float thr = best - (float)kSlack * fabsf(best);
-  const bool any = best > -INFINITY;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i - lane < n; i += (int64_t)gridDim.x * 256) {
-    const bool in = i < n && elig[i] != 0 && (any ? bound[i] >= thr : bound[i] == bound[i]);
-    const uint64_t m = __ballot(in);
-    if (m == 0) continue;
-    int at = 0;
-    if (lane == 0) at = atomicAdd(count, __popcll(m));
-    at = __shfl(at, 0);
-    if (in) list[at + __popcll(m & ((1ull << lane) - 1))] = (int32_t)i;
+  if (FIRST) {
+    if (lane < kTop - 1 && idx[lane] >= 0 && first[lane] == first[lane]) {
+      best = first[lane];
+      key = make_key(best, idx[lane], true).v;
+    }
+    key = kb_wave_max(key);
+    for (int o = 32; o >= 1; o >>= 1) best = fmaxf(best, __shfl_xor(best, o));
+    if (blockIdx.x == 0 && threadIdx.x == 0) *top = 0;  // scoring raises it
+  } else {
+    key = *top;
+  }
+  const float thr = fabsf(best) < INFINITY ? best - (float)kSlack * fabsf(best) : best;
+  for (int64_t c0 = (int64_t)blockIdx.x * 256 * kCompact; c0 < n; c0 += (int64_t)gridDim.x * 256 * kCompact) {
+    const int64_t i = c0 + (int64_t)threadIdx.x * kCompact;
+    float b[kCompact] = {};
+    uint8_t e[kCompact] = {};
+    if (i + kCompact <= n) {  // both arrays are 256-byte aligned
+      *reinterpret_cast<f4_t*>(b) = *reinterpret_cast<const f4_t*>(bound + i);
+      *reinterpret_cast<uint32_t*>(e) = *reinterpret_cast<const uint32_t*>(elig + i);
+    } else {
+      for (int t = 0; t < kCompact && i + t < n; ++t) {
+        b[t] = bound[i + t];
+        e[t] = elig[i + t];
+      }
+    }
+    unsigned in = 0;
+#pragma unroll
+    for (int t = 0; t < kCompact; ++t) {
+      const uint32_t x = (uint32_t)i + t;
+      if (e[t] != 0 && b[t] == b[t] && (make_key(b[t], i + t, true).v > key || (FIRST && b[t] >= thr && b[t] != best)) &&
+          (FIRST || x * 2654435761u <= limit))
+        in |= 1u << t;
+    }
+    int at = __popc(in);  // entries up to this lane's last
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(at, o);
+      if (lane >= o) at += v;
+    }
+    if (lane == 63) in_wave[wave] = at;
+    __syncthreads();
+    const int sum = in_wave[0] + in_wave[1] + in_wave[2] + in_wave[3];
+    if (threadIdx.x == 0 && sum) start = atomicAdd(count, sum);
+    __syncthreads();
+    int64_t to = (int64_t)at - __popc(in);
+    if (sum) {
+      to += start;
+      for (int w = 0; w < wave; ++w) to += in_wave[w];
+    }
+#pragma unroll
+    for (int t = 0; t < kCompact; ++t)
+      if ((in >> t & 1u) && to < cap) list[to++] = (int32_t)(i + t);
+    __syncthreads();  // in_wave and start are read
   }
 }
 
+// The scores of the list (as many entries as kb_sigma takes), and of the first
+// guesses (idx given), become their candidates' bounds, and the best of them top.
 __global__ __launch_bounds__(256) void kb_scatter_kernel(const int32_t* __restrict__ list,
                                                          const int32_t* __restrict__ live, int n,
-                                                         const float* __restrict__ val, float* __restrict__ bound) {
+                                                         const float* __restrict__ val,
+                                                         const int64_t* __restrict__ idx,
+                                                         const float* __restrict__ first, float* __restrict__ bound,
+                                                         unsigned long long* __restrict__ top) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (live) n = min(n, *live);
-  if (i < n) bound[list[i]] = val[i];
+  if (live) n = *live <= n ? *live : 0;
+  unsigned long long key = 0;
+  auto set = [&](int64_t x, float score) {
+    bound[x] = score;
+    const unsigned long long mine = make_key(score, x, true).v;
+    key = mine > key ? mine : key;
+  };
+  if (idx && i < kTop - 1 && idx[i] >= 0) set(idx[i], first[i]);  // a guess on the list: the same score twice
+  if (i < n) set(list[i], val[i]);
+  key = kb_wave_max(key);
+  if ((threadIdx.x & 63) == 0 && key) atomicMax(top, key);
 }
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 struct KbLayout {
   size_t mu, sd, bound, elig, votes, list, mu_list, sd_list, val, w, xw;  // of the pool's size
-  size_t idx, score, nvalid, picks, info, count, v, beta, ls;             // small
+  size_t idx, score, first, nvalid, picks, info, count, top, v, beta, ls;  // small
   size_t total;
 };
 
@@ -490,10 +589,12 @@ KbLayout kb_layout(const GPDevice* const* g, int p, int64_t n, int q) {
   L.xw = take(xw);
   L.idx = take(kTop * 8);
   L.score = take(kTop * 4);
+  L.first = take(kTop * 4);
   L.nvalid = take(4);
   L.picks = take((size_t)q * 8);
   L.info = take(sizeof(KbInfo));
   L.count = take(4);
+  L.top = take(8);
   L.v = take((size_t)p * m_pad * 8);
   L.beta = take((size_t)p * q * m_pad * 8);
   L.ls = take((size_t)p * q * q * 8);
@@ -501,35 +602,40 @@ KbLayout kb_layout(const GPDevice* const* g, int p, int64_t n, int q) {
   return L;
 }
 
-template <int S, bool LIST>
+template <int S, bool NARROW>
 int launch_sigma_s(const KbArgs& a, const int32_t* list, const int64_t* list64, const int32_t* live, int64_t n, int k0,
                    int kn, bool last, hipStream_t s) {
-  auto kern = kb_sigma_kernel<S, LIST>;
+  auto kern = kb_sigma_kernel<S, NARROW>;
   int nj = 0;
   for (int j = 0; j < a.p; ++j) nj = std::max(nj, a.g[j].nj);
-  const size_t lds = LIST ? (size_t)4 * 16 * kPicks * 8 : (size_t)nj * 16 * kPicks * 8;
+  const size_t lds = NARROW ? (size_t)4 * 16 * kPicks * 8 : (size_t)nj * 16 * kPicks * 8;
   const int rc = allow_full_lds((const void*)kern, "believer");
   if (rc != SCOOT_OK) return rc;
-  const int64_t blocks = LIST ? (n + 15) / 16 : (n + 255) / 256;
+  const int64_t blocks = NARROW ? (n + 15) / 16 : (n + 255) / 256;
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)a.p), dim3(256), lds, s, a, list, list64, live, n, k0,
                      kn, last ? 1 : 0);
   return SCOOT_OK;
 }
 
-template <bool LIST>
 int launch_sigma(const KbArgs& a, const int32_t* list, const int64_t* list64, const int32_t* live, int64_t n, int picks,
                  hipStream_t s) {
   if (n == 0) return SCOOT_OK;
+  const bool narrow = live || list64 || n <= kWide;
   for (int k0 = 0; k0 < picks; k0 += kPicks) {
     const int kn = std::min(kPicks, picks - k0);
     const bool last = k0 + kn == picks;
+    auto launch = [&](auto S) {
+      constexpr int s_ = decltype(S)::value;
+      return narrow ? launch_sigma_s<s_, true>(a, list, list64, live, n, k0, kn, last, s)
+                    : launch_sigma_s<s_, false>(a, list, list64, live, n, k0, kn, last, s);
+    };
     int rc;
     switch (a.g[0].S) {  // the GPs share d
-      case 1: rc = launch_sigma_s<1, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
-      case 2: rc = launch_sigma_s<2, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
-      case 3: rc = launch_sigma_s<3, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
-      case 4: rc = launch_sigma_s<4, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
-      default: rc = launch_sigma_s<5, LIST>(a, list, list64, live, n, k0, kn, last, s); break;
+      case 1: rc = launch(std::integral_constant<int, 1>()); break;
+      case 2: rc = launch(std::integral_constant<int, 2>()); break;
+      case 3: rc = launch(std::integral_constant<int, 3>()); break;
+      case 4: rc = launch(std::integral_constant<int, 4>()); break;
+      default: rc = launch(std::integral_constant<int, 5>()); break;
     }
     if (rc != SCOOT_OK) return rc;
   }
@@ -576,10 +682,12 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
   float* val = (float*)(w + L.val);
   int64_t* idx = (int64_t*)(w + L.idx);
   float* score = (float*)(w + L.score);
+  float* first = (float*)(w + L.first);
   int32_t* nvalid = (int32_t*)(w + L.nvalid);
   int64_t* picks_d = (int64_t*)(w + L.picks);
   KbInfo* info_d = (KbInfo*)(w + L.info);
   int32_t* count_d = (int32_t*)(w + L.count);
+  unsigned long long* top = (unsigned long long*)(w + L.top);
   const int64_t nl = std::max<int64_t>(n, kTop);
   int m_pad = 0;
   for (int j = 0; j < p; ++j) m_pad = std::max(m_pad, g[j]->m_pad);
@@ -658,49 +766,61 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
     rc = build_boxes(front.data(), (int)(front.size() / p), p, ref, bt);
     if (rc != SCOOT_OK) return rc;
     KbInfo info{};
-    // One read-back per selection: what the next round needs of the pick is
-    // made meanwhile.
-    auto pick = [&]() {
-      hipLaunchKernelGGL(kb_pick_kernel, dim3(1), dim3(64), 0, s, a, idx, score, k, elig, picks_d, info_d, count_d);
+    // One read-back per pick: what the next round needs of it is made while the
+    // host builds that round's boxes.
+    auto pick = [&](const int64_t* selected, int64_t cap) {
+      hipLaunchKernelGGL(kb_pick_kernel, dim3(1), dim3(64), 0, s, a, selected, score, top, cap, k, elig, picks_d, info_d,
+                         count_d);
       hipError_t e = hipGetLastError();
       if (e == hipSuccess) e = hipMemcpyAsync(&info, info_d, sizeof info, hipMemcpyDeviceToHost, s);
       if (e == hipSuccess) e = hipStreamSynchronize(s);
-      return e;
+      return e == hipSuccess ? SCOOT_OK : device_error(e);
     };
     if (k == 0) {
       hipLaunchKernelGGL(kb_zero_kernel, dim3(1), dim3(1), 0, s, count_d);
       rc = launch_ehvi_topq(mus, sds, p, n, SCOOT_F32, bt, bound, elig, kTop, idx, score, nvalid, stream);
-      if (rc != SCOOT_OK) return rc;
-      const hipError_t e = pick();
-      if (e != hipSuccess) return device_error(e);
+      if (rc == SCOOT_OK) rc = pick(idx, n);
     } else {
-      // the first guesses: the other candidates of the last selection
-      rc = launch_sigma<true>(a, nullptr, idx + 1, nullptr, kTop - 1, k, s);
-      if (rc == SCOOT_OK) rc = launch_ehvi(mul, sdl, p, kTop - 1, SCOOT_F32, bt, val, stream);
+      const dim3 blocks((unsigned)std::min<int64_t>((n + 256 * kCompact - 1) / (256 * kCompact), 2048));
+      auto score_list = [&](const int32_t* live, int64_t entries, const int64_t* guesses) {
+        int rc = launch_sigma(a, list, nullptr, live, entries, k, s);
+        if (rc == SCOOT_OK) rc = launch_ehvi(mul, sdl, p, entries, SCOOT_F32, bt, val, stream);
+        if (rc == SCOOT_OK && entries > 0)
+          hipLaunchKernelGGL(kb_scatter_kernel, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, s, list, live,
+                             (int)entries, val, guesses, first, bound, top);
+        return rc;
+      };
+      // A second list, of what beats top: limit of 2^32 - 1 of it.
+      auto second_list = [&](uint32_t limit, int64_t most) {
+        hipLaunchKernelGGL(kb_compact_kernel<false>, blocks, dim3(256), 0, s, bound, elig, n, nullptr, nullptr, limit,
+                           top, list, most, count_d);
+      };
+      // The first guesses: the best bounds after the last pick.  The length of
+      // the list that they leave stays on the device until the pick.
+      const int64_t cap = std::min<int64_t>(n, kListed);
+      rc = launch_sigma(a, nullptr, idx + 1, nullptr, kTop - 1, k, s);
+      if (rc == SCOOT_OK) rc = launch_ehvi(mul, sdl, p, kTop - 1, SCOOT_F32, bt, first, stream);
       if (rc != SCOOT_OK) return rc;
-      const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 2048));
-      hipLaunchKernelGGL(kb_compact_kernel, dim3((unsigned)blocks), dim3(256), 0, s, bound, elig, n, idx + 1, val,
-                         kTop - 1, list, count_d);
-      // The list's length stays on the device; the few lists that are longer
-      // than kListed are scored whole in a second turn.
-      int64_t cap = std::min<int64_t>(n, kListed);
-      const int32_t* live = count_d;
-      for (;;) {
-        rc = launch_sigma<true>(a, list, nullptr, live, cap, k, s);
-        if (rc == SCOOT_OK) rc = launch_ehvi(mul, sdl, p, cap, SCOOT_F32, bt, val, stream);
+      hipLaunchKernelGGL(kb_compact_kernel<true>, blocks, dim3(256), 0, s, bound, elig, n, idx + 1, first, 0u, top,
+                         list, cap, count_d);
+      rc = score_list(count_d, cap, idx + 1);
+      if (rc == SCOOT_OK) rc = pick(nullptr, cap);
+      if (rc == SCOOT_OK && info.count > cap) {
+        second_list((uint32_t)((uint64_t)cap * 0x80000000u / (uint64_t)info.count), cap);  // about cap / 2
+        rc = score_list(count_d, cap, nullptr);
         if (rc != SCOOT_OK) return rc;
-        hipLaunchKernelGGL(kb_scatter_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, list, live,
-                           (int)cap, val, bound);
-        rc = launch_topq(bound, elig, n, SCOOT_F32, kTop, idx, score, nvalid, stream);
-        if (rc != SCOOT_OK) return rc;
-        const hipError_t e = pick();
+        hipLaunchKernelGGL(kb_zero_kernel, dim3(1), dim3(1), 0, s, count_d);
+        second_list(UINT32_MAX, n);
+        int32_t count = 0;
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(&count, count_d, sizeof count, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return device_error(e);
-        if (info.count <= cap) break;
-        if (info.pick >= 0) hipLaunchKernelGGL(kb_unpick_kernel, dim3(1), dim3(1), 0, s, picks_d, k, elig);
-        cap = info.count;
-        live = nullptr;
+        rc = score_list(nullptr, count, nullptr);
+        if (rc == SCOOT_OK) rc = pick(nullptr, n);
       }
     }
+    if (rc != SCOOT_OK) return rc;
     if (info.pick < 0) break;
     picks[k] = info.pick;
     if (pick_acq) pick_acq[k] = info.score;
@@ -709,10 +829,13 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
     front = std::move(bt.front);
     for (int j = 0; j < p; ++j) front.push_back((double)info.mu[j]);
     hipLaunchKernelGGL(kb_v_kernel, dim3((unsigned)nb32, (unsigned)p), dim3(256), 0, s, a, k);
-    hipLaunchKernelGGL(kb_beta_kernel, dim3((unsigned)nj, (unsigned)p), dim3(256), 0, s, a, k);
-    hipLaunchKernelGGL(kb_chol_kernel, dim3((unsigned)p), dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL(kb_join_kernel, dim3((unsigned)nj + 1, (unsigned)p), dim3(256), 0, s, a, k);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return device_error(e);
+    if (k > 0) {
+      rc = launch_topq(bound, elig, n, SCOOT_F32, kTop - 1, idx + 1, score + 1, nvalid, stream);
+      if (rc != SCOOT_OK) return rc;
+    }
   }
   // the posterior the last scoring round saw (mu never moves; sigma carries
   // the picks before that round)
@@ -723,7 +846,7 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
     if (seen == 0) {
       e = hipMemcpyAsync(sigma_out, sd, (size_t)p * n * 4, hipMemcpyDeviceToDevice, s);
     } else {
-      rc = launch_sigma<false>(a, nullptr, nullptr, nullptr, n, seen, s);
+      rc = launch_sigma(a, nullptr, nullptr, nullptr, n, seen, s);
       if (rc != SCOOT_OK) return rc;
       e = hipGetLastError();
     }
