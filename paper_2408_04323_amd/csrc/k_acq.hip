@@ -360,12 +360,18 @@ int run_ehvi3(const void* const* mu, const void* const* sigma, int64_t n, const 
   const T* coords = reinterpret_cast<const T*>(dev);
   const uint32_t* recs = reinterpret_cast<const uint32_t*>((const unsigned char*)dev + coord_bytes);
   const uint32_t* col_end = reinterpret_cast<const uint32_t*>((const unsigned char*)dev + coord_bytes + rec_bytes);
-  const unsigned grid = (unsigned)((n + kEhviThreads - 1) / kEhviThreads);
   rc = allow_full_lds((const void*)ehvi3_kernel<T>, "ehvi");
   if (rc != SCOOT_OK) return rc;
-  hipLaunchKernelGGL(ehvi3_kernel<T>, dim3(grid), dim3(kEhviThreads * kEhviWaves), lds, s, (const T*)mu[0], (const T*)mu[1],
-                     (const T*)mu[2], (const T*)sigma[0], (const T*)sigma[1], (const T*)sigma[2], coords, recs,
-                     col_end, (T*)out, a);
+  // A launch holds fewer than 2^32 threads, four per candidate here: pools of
+  // 2^30 candidates and more take several.
+  constexpr int64_t kSpan = (int64_t)1 << 29;
+  for (int64_t at = 0; at < n; at += kSpan) {
+    a.n = std::min(kSpan, n - at);
+    const unsigned grid = (unsigned)((a.n + kEhviThreads - 1) / kEhviThreads);
+    hipLaunchKernelGGL(ehvi3_kernel<T>, dim3(grid), dim3(kEhviThreads * kEhviWaves), lds, s, (const T*)mu[0] + at,
+                       (const T*)mu[1] + at, (const T*)mu[2] + at, (const T*)sigma[0] + at, (const T*)sigma[1] + at,
+                       (const T*)sigma[2] + at, coords, recs, col_end, (T*)out + at, a);
+  }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(SCOOT_ERR_DEVICE, std::string("ehvi launch: ") + hipGetErrorString(err));
   return SCOOT_OK;
