@@ -384,10 +384,11 @@ int scoot_score_pool_ex(const scoot_gp* gps, int p, scoot_forest f, const uint8_
  * fantasy.  Ties go to the lowest index.
  *
  * gps: p fp32 handles (fp64: UNSUPPORTED) sharing d.  Xc [n*d] device.
- * Y_obs [m_obs*p], ref [p]: host.  workspace: device, at least the size
- * scoot_suggest_kb_workspace returns (about 4 (m + q) n p bytes, more than the
- * call touches); NULL: the library allocates what it needs, some 4 n (4 p + 4)
- * bytes up to nine picks and 4 n p more per pick above, and frees it in the call.
+ * Y_obs [m_obs*p], ref [p]: host.  workspace: device, at least the size that
+ * scoot_suggest_kb_workspace returns: about (16 p + 17) n bytes,
+ * 32 n p more for every eight picks from the tenth on, and 4 n d for every GP
+ * with input warping.  NULL: the library allocates as much and frees it in the
+ * call.
  * picks [q], pick_acq [q] (nullable), n_picked: HOST outputs — the call
  * synchronises `stream` after every pick.  Fewer than q feasible candidates:
  * *n_picked < q and the tail of picks is untouched.

@@ -861,16 +861,12 @@ int scoot_suggest_kb_ex(const scoot_gp* gps, int p, scoot_forest f, const uint8_
     rc = scoot_vote_threshold(delta, f->dev.n_trees, &vmin);
     if (rc != SCOOT_OK) return rc;
   }
-  // The reported size covers what is used but for pools of a few hundred
-  // candidates with many picks, which get an allocation of their own.
-  const size_t need = kb_needed_bytes(g, p, n, q), reported = kb_workspace_bytes(g, p, n, q);
-  if (workspace && workspace_bytes < reported) return fail(SCOOT_ERR_INVALID_ARG, "believer: workspace too small");
+  const size_t need = kb_workspace_bytes(g, p, n, q);
+  if (workspace && workspace_bytes < need) return fail(SCOOT_ERR_INVALID_ARG, "believer: workspace too small");
   void* ws = workspace;
-  bool own = false;
-  if (!ws || need > reported) {
-    if (hipMalloc(&ws, need) != hipSuccess) return fail(SCOOT_ERR_NO_MEMORY, "believer: workspace allocation failed");
-    own = true;
-  }
+  const bool own = !ws;
+  if (own && hipMalloc(&ws, need) != hipSuccess)
+    return fail(SCOOT_ERR_NO_MEMORY, "believer: workspace allocation failed");
   try {
     rc = run_kriging_believer(g, p, f ? &f->dev : nullptr, known, vmin, Xc, n, Y_obs, m_obs, ref, q, ws, picks, pick_acq,
                               n_picked, mu_out, sigma_out, stream);

@@ -71,7 +71,7 @@ struct KbGp {
   double* v;                  // m_pad: L^-1 k(X, x) of the newest pick
   double* beta;               // q x m_pad
   double* ls;                 // q x q: rows of L_S
-  float* w;                   // (q - 1) x ld: w of earlier chunks of picks
+  float* w;                   // kb_w_rows(q) x ld: w of earlier chunks of picks
   float* mu_list;             // outputs, per list entry
   float* sd_list;
   float* sd_out;              // n
@@ -563,6 +563,10 @@ struct KbLayout {
   size_t total;
 };
 
+// Rows of w that are kept: the last chunk of the at most q - 1 picks that a
+// score carries keeps none.
+int kb_w_rows(int q) { return q > 2 ? (q - 2) / kPicks * kPicks : 0; }
+
 KbLayout kb_layout(const GPDevice* const* g, int p, int64_t n, int q) {
   KbLayout L{};
   size_t off = 0;
@@ -585,7 +589,7 @@ KbLayout kb_layout(const GPDevice* const* g, int p, int64_t n, int q) {
   L.mu_list = take((size_t)p * std::max<int64_t>(n, kTop) * 4);
   L.sd_list = take((size_t)p * std::max<int64_t>(n, kTop) * 4);
   L.val = take((size_t)std::max<int64_t>(n, kTop) * 4);
-  L.w = take(q > kPicks + 1 ? (size_t)p * (q - 1) * std::max<int64_t>(n, kTop) * 4 : 0);
+  L.w = take((size_t)p * kb_w_rows(q) * std::max<int64_t>(n, kTop) * 4);
   L.xw = take(xw);
   L.idx = take(kTop * 8);
   L.score = take(kTop * 4);
@@ -644,26 +648,8 @@ int launch_sigma(const KbArgs& a, const int32_t* list, const int64_t* list64, co
 
 }  // namespace
 
-size_t kb_needed_bytes(const GPDevice* const* g, int p, int64_t n, int q) { return kb_layout(g, p, n, q).total; }
-
-// What scoot_suggest_kb_workspace reports and a caller's workspace is held to:
-// the size of the form that kept V of every objective (m_pad + q rows of the
-// pool's length), which programs may have stored; what is used is less.
 size_t kb_workspace_bytes(const GPDevice* const* g, int p, int64_t n, int q) {
-  size_t off = 0, vbytes = 0, xw = 0;
-  int rows_max = 0;
-  auto take = [&](size_t bytes) { off += align256(bytes); };
-  const int64_t ld = (n + 63) / 64 * 64;
-  for (int j = 0; j < p; ++j) {
-    vbytes += align256((size_t)(g[j]->m_pad + q) * ld * 4);
-    rows_max = std::max(rows_max, g[j]->m_pad + q);
-    xw += g[j]->warp ? align256((size_t)n * g[j]->d * 4) : 0;
-  }
-  take(vbytes);
-  for (size_t b : {(size_t)p * n * 4, (size_t)p * n * 4, (size_t)n * 4, (size_t)n, (size_t)n * 4, (size_t)8, (size_t)8,
-                   (size_t)4, (size_t)p * rows_max * 4, (size_t)p * 4, (size_t)(1 + SCOOT_MAX_OBJECTIVES) * 4, xw})
-    take(b);
-  return off;
+  return kb_layout(g, p, n, q).total;
 }
 
 int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f, const uint8_t* known,
@@ -719,7 +705,7 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
     o.v = (double*)(w + L.v) + (size_t)j * m_pad;
     o.beta = (double*)(w + L.beta) + (size_t)j * q * m_pad;
     o.ls = (double*)(w + L.ls) + (size_t)j * q * q;
-    o.w = (float*)(w + L.w) + (size_t)j * (q - 1) * nl;
+    o.w = (float*)(w + L.w) + (size_t)j * kb_w_rows(q) * nl;
     o.mu_list = (float*)(w + L.mu_list) + (size_t)j * nl;
     o.sd_list = (float*)(w + L.sd_list) + (size_t)j * nl;
     o.sd_out = sigma_out ? sigma_out + (size_t)j * n : nullptr;
