@@ -384,8 +384,8 @@ int scoot_score_pool_ex(const scoot_gp* gps, int p, scoot_forest f, const uint8_
  * fantasy.  Ties go to the lowest index.
  *
  * gps: p fp32 handles (fp64: UNSUPPORTED) sharing d.  Xc [n*d] device.
- * Y_obs [m_obs*p], ref [p]: host.  workspace: device, at least the size that
- * scoot_suggest_kb_workspace returns: about (16 p + 17) n bytes,
+ * Y_obs [m_obs*p], ref [p]: host.  workspace: device, at any address, at least
+ * the size that scoot_suggest_kb_workspace returns: about (16 p + 17) n bytes,
  * 32 n p more for every eight picks from the tenth on, and 4 n d for every GP
  * with input warping.  NULL: the library allocates as much and frees it in the
  * call.

@@ -37,6 +37,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 #include <type_traits>
 #include <utility>
@@ -555,7 +556,8 @@ __global__ __launch_bounds__(256) void kb_scatter_kernel(const int32_t* __restri
   if ((threadIdx.x & 63) == 0 && key) atomicMax(top, key);
 }
 
-size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+constexpr size_t kKbAlign = 256;
+size_t align256(size_t b) { return (b + kKbAlign - 1) / kKbAlign * kKbAlign; }
 
 struct KbLayout {
   size_t mu, sd, bound, elig, votes, list, mu_list, sd_list, val, w, xw;  // of the pool's size
@@ -648,8 +650,10 @@ int launch_sigma(const KbArgs& a, const int32_t* list, const int64_t* list64, co
 
 }  // namespace
 
+// With room to place the parts on 256-byte boundaries wherever the workspace
+// starts: they are read by 16 bytes and hold counters.
 size_t kb_workspace_bytes(const GPDevice* const* g, int p, int64_t n, int q) {
-  return kb_layout(g, p, n, q).total;
+  return kb_layout(g, p, n, q).total + kKbAlign - 1;
 }
 
 int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f, const uint8_t* known,
@@ -658,7 +662,7 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
                          float* mu_out, float* sigma_out, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   const KbLayout L = kb_layout(g, p, n, q);
-  unsigned char* w = (unsigned char*)ws;
+  unsigned char* w = (unsigned char*)(((uintptr_t)ws + kKbAlign - 1) / kKbAlign * kKbAlign);
   float* mu = (float*)(w + L.mu);
   float* sd = (float*)(w + L.sd);
   float* bound = (float*)(w + L.bound);

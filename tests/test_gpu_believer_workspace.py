@@ -1,5 +1,5 @@
 """The believer's workspace: the size that is reported is what the parts take,
-the call stays inside it, and a smaller one is refused."""
+the call stays inside it wherever it starts, and a smaller one is refused."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,7 @@ GUARD = 4096
 
 
 # n: narrow and wide lists; q: no, eight and sixteen kept rows
-@pytest.mark.parametrize("offset", [0])
+@pytest.mark.parametrize("offset", [0, 4, 1])
 @pytest.mark.parametrize("n,q,warped", [(5, 3, False), (300, 9, False), (300, 64, True), (70001, 10, False),
                                         (70001, 18, True)])
 def test_reported_size_is_what_the_call_uses(n, q, warped, offset):
