@@ -508,6 +508,9 @@ __global__ __launch_bounds__(kNllThreads) void nll_factor_kernel(NllArgs a) {
       Dn = ld_c(a.L + ((size_t)nb + 1) * 256, lane);
       ld_cols(a.L + (size_t)nb * 256, lane, off);
     }
+    // both here before the first inverse is published: the workers then write
+    // the panel over block (1, 0)
+    asm volatile("" : "+v"(Dn), "+v"(off[0]), "+v"(off[1]), "+v"(off[2]), "+v"(off[3]));
     bool alive = true;
     for (int k = 0; k < nb && alive; ++k) {
       diag_factor(a, k, D, inverse(k), sProd, sFlag, floor, lane);
