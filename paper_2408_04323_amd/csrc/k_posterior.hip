@@ -50,8 +50,9 @@ __device__ inline double partial_expectation_d(double c, double mu, double sd) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32.  A workgroup of RS waves owns a tile of 64 candidates; wave r owns the
-// row blocks (32 rows) of V that fall to it, for all 64.
+// fp32.  A workgroup of RS waves owns a tile of 64 candidates (32 in small
+// pools); wave r owns the row blocks (32 rows) of V that fall to it, for all of
+// them.
 //
 // Squared distances on the fp64 matrix cores: with augmented rows
 // A_i = (2 X_i, -|X_i|^2, -1) for the observations and B_x = (x, 1, |x|^2)
@@ -81,7 +82,8 @@ __device__ inline double partial_expectation_d(double c, double mu, double sd) {
 // resident for the whole tile.  Row block nb - 1 - s is slot s; wave r owns
 // slots r, r + RS, ..., so that at every j the live slots are the first ones
 // of every wave.  The waves share the generation: wave r makes K* of block
-// j + 1 for 64 / RS of the candidates while the product of block j runs, and
+// j + 1 for 64 / RS of the candidates (tiles of 32: the two waves whose slots
+// die first, for 16 each) while the product of block j runs, and
 // the parts go through LDS in the order of the product's B operand (lane l:
 // observations 8 (l / 32) .. + 7 of candidate l % 32), two buffers, one barrier
 // per j.  Executed matrix work is (nb32 + 1) / nb32 of the triangle's.
@@ -112,7 +114,6 @@ struct Post32 {
 };
 
 constexpr int kUnitBytes = 3 * 64 * 16;   // a unit's three parts in A-operand order
-constexpr int kPostTile = 64;             // candidates per workgroup and tile
 
 typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
@@ -144,32 +145,38 @@ __device__ inline void mfma_bf16(const u4_t& a, const u4_t& b, f16_t& c) {
 
 // LDS of a workgroup: K* parts, the candidates' augmented rows, the next
 // tile's coordinates, the reductions.
-template <int S, int RS>
+template <int S, int RS, int H>
 struct PostLds {
-  u4_t b[RS == 1 ? 1 : 2][2][3][64];  // [buffer][32-candidate tile][part][lane]
-  double bq[4][S][64];                // [16-candidate tile][step][lane]
-  float xb[4][S][64];
+  u4_t b[2][H][3][64];      // [buffer][32-candidate half][part][lane]
+  double bq[2 * H][S][64];  // [16-candidate tile][step][lane]
+  float xb[2 * H][S][64];
   double sq[RS][64], mu[64];
   double scale[S * 4];
 };
 
 // S: fp64 MFMA steps of the distances; RS: waves that share a tile's rows;
 // NBW: slots per wave; KA: register sets for units of L^-1; WPS: waves per SIMD
-// that the register budget is set for.
-template <int S, int RS, int NBW, int KA, int WPS>
+// that the register budget is set for; H: halves of 32 candidates in a tile.
+template <int S, int RS, int NBW, int KA, int WPS, int H>
 __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
     const float* __restrict__ Xc, const unsigned char* __restrict__ linv, const double* __restrict__ xq,
     const float* __restrict__ alpha, float* __restrict__ mu_out, float* __restrict__ sd_out,
     float* __restrict__ ei_out, const Post32 a) {
-  constexpr int CT = 4 / RS;      // 16-candidate tiles whose K* this wave makes
+  static_assert(RS == 4 || (RS == 2 && H == 2), "a wave makes whole tiles of K*");
+  constexpr int TILE = 32 * H;    // candidates per workgroup and tile
+  constexpr int GW = RS < 2 * H ? RS : 2 * H;  // waves that make K*
+  constexpr int CT = 2 * H / GW;  // 16-candidate tiles whose K* such a wave makes
   constexpr int NP = 2 * CT;      // pieces of that work, two observations each
-  constexpr int PPS = (NP + NBW - 1) / NBW;  // pieces beside a slot, in order
-  // A wave of one slot and one tile of 16 candidates to generate has little to
-  // hide the chain of distances behind: it runs under the product's first
-  // instructions (m = 128, n = 3000 8.4 -> 7.9 us; more slots: slower).
-  constexpr bool EARLY = CT == 1 && NBW == 1;
+  // A wave of one or two slots and one tile of 16 candidates to generate has
+  // little to hide its chain of distances, values and splits behind: the
+  // distances run before the product, and both pieces stand between the matrix
+  // instructions of the first slot, the last to die, four vector instructions
+  // after each.  Left to the compiler, the pieces follow the product (m = 128: n
+  // = 16,000 9.3 -> 8.8 us, 48,000 16.3 -> 15.0; m = 256: 24,000 21.6 -> 20.0).
+  constexpr bool EARLY = CT == 1 && NBW <= 2;
+  constexpr int PPS = EARLY ? NP : (NP + NBW - 1) / NBW;  // pieces beside a slot, in order
   const NegPairs neg;
-  __shared__ PostLds<S, RS> sm;
+  __shared__ PostLds<S, RS, H> sm;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int g = lane >> 4, c = lane & 15;
@@ -177,10 +184,10 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
   // Two workgroups of a CU own their slots in opposite orders, since the first
   // slots live longest (workgroups gridDim / 2 apart usually share a CU).
   const int r = blockIdx.x >= (gridDim.x + 1) / 2 ? RS - 1 - wave : wave;
-  const int64_t n_tiles = (a.n + kPostTile - 1) / kPostTile;
-  auto sync = [&]() {
-    if constexpr (RS > 1) __syncthreads();
-  };
+  const int64_t n_tiles = (a.n + TILE - 1) / TILE;
+  // K* is made by every wave, or by those whose slots are the first to die
+  const int gi = GW == RS ? wave : r - (RS - GW);
+  const bool gen = GW == RS || gi >= 0;
 
   if (tid < S * 4) sm.scale[tid] = tid < a.d ? a.scale[min(tid, SCOOT_MAX_DIM - 1)] : 0.0;
   __syncthreads();
@@ -191,7 +198,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
   auto load_x = [&](int64_t t) {
 #pragma unroll
     for (int q = 0; q < CT; ++q) {
-      const int64_t cand = min(t * kPostTile + (wave * CT + q) * 16 + c, a.n - 1);
+      const int64_t cand = min(t * TILE + (gi * CT + q) * 16 + c, a.n - 1);
 #pragma unroll
       for (int s = 0; s < S; ++s) xr[q][s] = Xc[cand * a.d + min(4 * s + g, a.d - 1)];
     }
@@ -200,7 +207,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
 #pragma unroll
     for (int q = 0; q < CT; ++q)
 #pragma unroll
-      for (int s = 0; s < S; ++s) sm.xb[wave * CT + q][s][lane] = xr[q][s];
+      for (int s = 0; s < S; ++s) sm.xb[gi * CT + q][s][lane] = xr[q][s];
   };
   auto operands = [&]() {
 #pragma unroll
@@ -208,7 +215,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
       double x[S], nrm = 0.0;
 #pragma unroll
       for (int s = 0; s < S; ++s) {
-        x[s] = (double)sm.xb[wave * CT + q][s][lane] * sm.scale[4 * s + g];
+        x[s] = (double)sm.xb[gi * CT + q][s][lane] * sm.scale[4 * s + g];
         if (4 * s + g < a.d) nrm = fma(x[s], x[s], nrm);
       }
       nrm += __shfl_xor(nrm, 16);
@@ -216,7 +223,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         const int k = 4 * s + g;
-        sm.bq[wave * CT + q][s][lane] = k < a.d ? x[s] : (k == a.d ? 1.0 : (k == a.d + 1 ? nrm : 0.0));
+        sm.bq[gi * CT + q][s][lane] = k < a.d ? x[s] : (k == a.d ? 1.0 : (k == a.d + 1 ? nrm : 0.0));
       }
     }
   };
@@ -241,7 +248,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
     cr = d4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int s = 0; s < S; ++s)
-      cr = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], sm.bq[wave * CT + q][s][lane], cr, 0, 0, 0);
+      cr = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], sm.bq[gi * CT + q][s][lane], cr, 0, 0, 0);
   };
   auto piece = [&](int p, int to_buf) {
     const int q = p >> 1, h = p & 1;
@@ -261,7 +268,7 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
     pk[2][h] = pack_bf16(kv[0], kv[1]);
     if (h == 1) {
       mu_acc[q] += (double)m_part;
-      const int ct = wave * CT + q;
+      const int ct = gi * CT + q;
       u4_t* to = &sm.b[to_buf][ct >> 1][0][(g >> 1) * 32 + (ct & 1) * 16 + c];
 #pragma unroll
       for (int part = 0; part < 3; ++part)
@@ -282,39 +289,45 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
   auto first_unit = [&](int k) { return min(r + RS * k, a.nb32 - 1); };
 
   int64_t tile = blockIdx.x;
-  load_x(tile);
-  store_x();
-  load_obs(0);
+  if (gen) {
+    load_x(tile);
+    store_x();
+    load_obs(0);
+  }
 #pragma unroll
   for (int k = 0; k < KA; ++k) load_unit(k, first_unit(k));
-  operands();
-  if constexpr (EARLY) distances(0);
+  if (gen) {
+    operands();
+    if constexpr (EARLY) distances(0);
 #pragma unroll
-  for (int p = 0; p < NP; ++p) piece(p, 0);
+    for (int p = 0; p < NP; ++p) piece(p, 0);
+    load_obs(a.nj > 1 ? 1 : 0);
+    load_x(tile + gridDim.x);
+    store_x();
+  }
   int buf = 0;  // the buffer that holds K* of the block being multiplied
-  load_obs(a.nj > 1 ? 1 : 0);
-  load_x(tile + gridDim.x);
-  store_x();
-  f16_t acc[NBW][2];
+  f16_t acc[NBW][H];
 
   for (; tile < n_tiles; tile += gridDim.x) {
-    const int64_t c0 = tile * kPostTile;
+    const int64_t c0 = tile * TILE;
 #pragma unroll
     for (int t = 0; t < NBW; ++t)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[t][0][i] = acc[t][1][i] = 0.0f;
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[t][h][i] = 0.0f;
 
     int off = 0;  // first unit of block j
 #pragma unroll 1
     for (int j = 0; j < a.nj; ++j) {
       const int live = a.nb32 - (j >> 1);
-      sync();  // K* of block j is in LDS
-      u4_t bc[2][3];
+      __syncthreads();  // K* of block j is in LDS
+      u4_t bc[H][3];
 #pragma unroll
       for (int part = 0; part < 3; ++part)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) bc[h][part] = sm.b[buf][h][part][lane];
-      if constexpr (RS > 1) buf ^= 1;
+        for (int h = 0; h < H; ++h) bc[h][part] = sm.b[buf][h][part][lane];
+      buf ^= 1;
       // block to generate beside this product, and the one after it
       int jn = j + 1;
       const int cur = off;
@@ -327,15 +340,16 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
         for (int q = 0; q < CT; ++q) {
           mu_acc[q] += __shfl_xor(mu_acc[q], 16);
           mu_acc[q] += __shfl_xor(mu_acc[q], 32);
-          if (g == 0) sm.mu[(wave * CT + q) * 16 + c] = mu_acc[q];
+          if (gen && g == 0) sm.mu[(gi * CT + q) * 16 + c] = mu_acc[q];
           mu_acc[q] = 0.0;
         }
-        operands();
+        if (gen) operands();
         jn = 0;
         noff = 0;
         nlive = a.nb32;
       }
-      if constexpr (EARLY) distances(0);
+      if constexpr (EARLY)
+        if (gen) distances(0);
 #pragma unroll
       for (int t = 0; t < NBW; ++t) {
         if (r + RS * t < live) {
@@ -343,38 +357,47 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
           // gaps between their instructions (3-4% per launch)
           __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][2], bc[h][0], acc[t][h]);
+          for (int h = 0; h < H; ++h) mfma_bf16(au[t % KA][2], bc[h][0], acc[t][h]);
 #pragma unroll
-          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][0], bc[h][2], acc[t][h]);
+          for (int h = 0; h < H; ++h) mfma_bf16(au[t % KA][0], bc[h][2], acc[t][h]);
 #pragma unroll
-          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][1], bc[h][1], acc[t][h]);
+          for (int h = 0; h < H; ++h) mfma_bf16(au[t % KA][1], bc[h][1], acc[t][h]);
 #pragma unroll
-          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][1], bc[h][0], acc[t][h]);
+          for (int h = 0; h < H; ++h) mfma_bf16(au[t % KA][1], bc[h][0], acc[t][h]);
 #pragma unroll
-          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][0], bc[h][1], acc[t][h]);
+          for (int h = 0; h < H; ++h) mfma_bf16(au[t % KA][0], bc[h][1], acc[t][h]);
 #pragma unroll
-          for (int h = 0; h < 2; ++h) mfma_bf16(au[t % KA][0], bc[h][0], acc[t][h]);
+          for (int h = 0; h < H; ++h) mfma_bf16(au[t % KA][0], bc[h][0], acc[t][h]);
           {
             const int k = t % KA, sn = r + RS * k;  // the set, and its first slot
             int unit = sn < nlive ? noff + sn : first_unit(k);
             if (t + KA < NBW && r + RS * (t + KA) < live) unit = cur + r + RS * (t + KA);
             load_unit(k, unit);
           }
+          if (gen) {
 #pragma unroll
-          for (int p = t * PPS; p < NP && p < (t + 1) * PPS; ++p) piece(p, buf);
+            for (int p = t * PPS; p < NP && p < (t + 1) * PPS; ++p) piece(p, buf);
+          }
+          if (EARLY && t == 0) {
+#pragma unroll
+            for (int i = 0; i < 6 * H; ++i) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a matrix instruction
+              __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // and four vector ones
+            }
+          }
           __builtin_amdgcn_s_setprio(0);
           asm volatile("; slot %0" ::"i"(t));  // keeps the two copies of the pieces apart
-        } else {
+        } else if (gen) {
 #pragma unroll
           for (int p = t * PPS; p < NP && p < (t + 1) * PPS; ++p) piece(p, buf);
         }
       }
-      load_obs(jn + 1 < a.nj ? jn + 1 : 0);
+      if (gen) load_obs(jn + 1 < a.nj ? jn + 1 : 0);
     }
     // ---- squared norms of the columns -----------------------------------------
-    load_x(tile + 2 * (int64_t)gridDim.x);
+    if (gen) load_x(tile + 2 * (int64_t)gridDim.x);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < H; ++h) {
       double sq = 0.0;
 #pragma unroll
       for (int t = 0; t < NBW; ++t) {
@@ -388,10 +411,10 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
       sq += __shfl_xor(sq, 32);
       if (lane < 32) sm.sq[wave][h * 32 + lane] = sq;
     }
-    store_x();
-    sync();
+    if (gen) store_x();
+    __syncthreads();
     const int64_t cand = c0 + lane;
-    if (wave == 0 && cand < a.n) {
+    if (wave == 0 && lane < TILE && cand < a.n) {
       double sq = 0.0;
 #pragma unroll
       for (int w = 0; w < RS; ++w) sq += sm.sq[w][lane];
@@ -406,8 +429,8 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
   // registers beside the accumulators.
   if (ei_out && wave == 0) {
     for (tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-      const int64_t cand = tile * kPostTile + lane;
-      if (cand < a.n) ei_out[cand] = (float)partial_expectation_d(a.ei_c, (double)mu_out[cand], (double)sd_out[cand]);
+      const int64_t cand = tile * TILE + lane;
+      if (lane < TILE && cand < a.n) ei_out[cand] = (float)partial_expectation_d(a.ei_c, (double)mu_out[cand], (double)sd_out[cand]);
     }
   }
 }
@@ -760,11 +783,11 @@ int64_t persistent_grid(const void* kern, int threads, size_t lds, int64_t tiles
   return std::min(tiles, (int64_t)cus * per_cu);
 }
 
-template <int S, int RS, int NBW, int KA, int WPS>
+template <int S, int RS, int NBW, int KA, int WPS, int H>
 int run32(const GPDevice& g, const float* Xc, int64_t n, float* mu, float* sd, float* ei, const Post32& a,
           hipStream_t s) {
-  auto kern = posterior_f32_kernel<S, RS, NBW, KA, WPS>;
-  const int64_t grid = persistent_grid((const void*)kern, RS * 64, 0, (n + kPostTile - 1) / kPostTile);
+  auto kern = posterior_f32_kernel<S, RS, NBW, KA, WPS, H>;
+  const int64_t grid = persistent_grid((const void*)kern, RS * 64, 0, (n + 32 * H - 1) / (32 * H));
   if (grid < 1) return fail(SCOOT_ERR_DEVICE, "posterior: workgroup does not fit on a compute unit");
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(RS * 64), 0, s, Xc, (const unsigned char*)g.linv,
                      (const double*)g.xs, g.alpha32, mu, sd, ei, a);
@@ -779,17 +802,27 @@ int run32_by_rows(const GPDevice& g, const float* Xc, int64_t n, float* mu, floa
   // (six up to m = 128), and four waves are the faster ones up to about three
   // tiles per CU (n = 48,000, m = 256 35.7 -> 30.3, but 64,000 38.6 -> 40.1), and
   // at m <= 128 up to the start of the second round of six (n = 100,000, m = 128
-  // 31.0 -> 27.4, but 262,144 54.5 -> 58.1).
+  // 31.0 -> 27.4, but 262,144 54.5 -> 58.1).  Tiles of 32 candidates, whose
+  // blocks take half the matrix time, as long as every one has a CU to itself (n =
+  // 8192: m = 64 6.4 -> 5.9, 128 8.7 -> 8.1, 192 12.2 -> 11.0, 256 15.2 -> 13.8);
+  // two on a CU read L^-1 twice and are slower than one of 64 (n = 12,000, m =
+  // 128 8.9 -> 10.0).  Registers for three waves per SIMD with two slots: n =
+  // 48,000, m = 256 31.0 -> 28.4, at d = 16 (five distance steps) they spill: n =
+  // 24,000 22.4 -> 24.4.
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  const int64_t tiles = (n + kPostTile - 1) / kPostTile;
-  if (a.nb32 <= 4 && tiles <= 7 * (int64_t)cus) return run32<S, 4, 1, 1, 2>(g, Xc, n, mu, sd, ei, a, s);
-  if (a.nb32 <= 8 && tiles <= 3 * (int64_t)cus) return run32<S, 4, 2, 2, 2>(g, Xc, n, mu, sd, ei, a, s);
-  if (a.nb32 <= 4) return run32<S, 2, 2, 2, 3>(g, Xc, n, mu, sd, ei, a, s);
-  if (a.nb32 <= 8) return run32<S, 2, 4, 3, 2>(g, Xc, n, mu, sd, ei, a, s);
-  if (a.nb32 <= 16) return run32<S, 4, 4, 4, 2>(g, Xc, n, mu, sd, ei, a, s);
-  return run32<S, 4, 5, 2, 2>(g, Xc, n, mu, sd, ei, a, s);
+  const int64_t tiles = (n + 63) / 64;
+  constexpr int WPS = S <= 4 ? 3 : 2;
+  const bool halves = (n + 31) / 32 <= cus;
+  if (a.nb32 <= 4 && halves) return run32<S, 4, 1, 1, 2, 1>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 8 && halves) return run32<S, 4, 2, 2, 2, 1>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 4 && tiles <= 7 * (int64_t)cus) return run32<S, 4, 1, 1, 2, 2>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 8 && tiles <= 3 * (int64_t)cus) return run32<S, 4, 2, 2, WPS, 2>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 4) return run32<S, 2, 2, 2, 3, 2>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 8) return run32<S, 2, 4, 3, 2, 2>(g, Xc, n, mu, sd, ei, a, s);
+  if (a.nb32 <= 16) return run32<S, 4, 4, 4, 2, 2>(g, Xc, n, mu, sd, ei, a, s);
+  return run32<S, 4, 5, 2, 2, 2>(g, Xc, n, mu, sd, ei, a, s);
 }
 
 template <int WAVES, int D>
