@@ -385,10 +385,10 @@ int scoot_score_pool_ex(const scoot_gp* gps, int p, scoot_forest f, const uint8_
  *
  * gps: p fp32 handles (fp64: UNSUPPORTED) sharing d.  Xc [n*d] device.
  * Y_obs [m_obs*p], ref [p]: host.  workspace: device, at any address, at least
- * the size that scoot_suggest_kb_workspace returns: about (16 p + 17) n bytes,
- * 32 n p more for every eight picks from the tenth on, and 4 n d for every GP
- * with input warping.  NULL: the library allocates as much and frees it in the
- * call.
+ * the size that scoot_suggest_kb_workspace returns: about (16 p + 17) n bytes, 4 n d
+ * more for every GP with input warping, and 4 n p for every pick before the last
+ * (large pools: 32 n p for every eight picks from the tenth on).  NULL: the
+ * library allocates as much and frees it in the call.
  * picks [q], pick_acq [q] (nullable), n_picked: HOST outputs — the call
  * synchronises `stream` after every pick.  Fewer than q feasible candidates:
  * *n_picked < q and the tail of picks is untouched.

@@ -26,6 +26,9 @@
 // thousand candidates per pick instead of the pool: a suggestion of eight
 // took 12.4 ms when every pick streamed V = L^-1 K*^T (4.3 GB) from memory.
 //
+// A small pool is scored whole at every pick: w of every pick is kept, so a pick
+// costs the covariances once more and a shorter chain of launches (kb_direct).
+//
 // Where many candidates score alike the list is long.  A bound that equals the
 // best score cannot beat it, nor win the tie from a higher index, so such a
 // candidate is not listed (all scores zero, or a pool far from every
@@ -60,6 +63,8 @@ constexpr int kListed = 16384;   // the longest list scored without waiting for 
 // More candidates than this are taken 64 to a wave: a workgroup of that form for
 // every compute unit.
 constexpr int64_t kWide = 65536;
+// The same for a pass of one pick, all objectives counted: 160 of 256 compute units.
+constexpr int64_t kWideOne = 40960;
 constexpr double kSlack = 1e-4;  // of the best score, against rounding of the bounds
 
 // One objective: its GP, the pool as the GP sees it, and what the picks left.
@@ -72,7 +77,7 @@ struct KbGp {
   double* v;                  // m_pad: L^-1 k(X, x) of the newest pick
   double* beta;               // q x m_pad
   double* ls;                 // q x q: rows of L_S
-  float* w;                   // kb_w_rows(q) x ld: w of earlier chunks of picks
+  float* w;                   // kb_w_rows x ld: w of earlier picks
   float* mu_list;             // outputs, per list entry
   float* sd_list;
   float* sd_out;              // n
@@ -230,32 +235,46 @@ __device__ inline void kb_chol(const KbArgs& a, const KbGp& g, int k) {
   for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
   if (lane == 0) var[wave] = s;
   __syncthreads();
-  for (int p = wave; p < k; p += 4) {
+  // sixteen lanes to a pick: the dot product, and a dimension of the distance each
+  static_assert(SCOOT_MAX_DIM <= 16, "a lane per dimension");
+  const int c = tid & 15;
+  for (int p = tid >> 4; p < k; p += 16) {
     const double* beta = g.beta + (size_t)p * g.m_pad;
     double dot = 0.0;
-    for (int i = lane; i < g.m; i += 64) dot = fma(beta[i], ks[i], dot);
-    for (int o = 32; o >= 1; o >>= 1) dot += __shfl_xor(dot, o);
-    if (lane == 0) {
-      const float* y = g.xc + a.picks[p] * a.d;
-      double r2 = 0.0;
-      for (int q = 0; q < a.d; ++q) {
-        const double t = ((double)x[q] - (double)y[q]) * g.scale[q];
-        r2 = fma(t, t, r2);
-      }
-      row[p] = kb_cov(g, r2) - dot;
+#pragma unroll 4
+    for (int i = c; i < g.m; i += 16) dot = fma(beta[i], ks[i], dot);
+    const double t = c < a.d ? ((double)x[c] - (double)g.xc[a.picks[p] * a.d + c]) * g.scale[c] : 0.0;
+    double r2 = t * t;
+    for (int o = 8; o >= 1; o >>= 1) {
+      dot += __shfl_xor(dot, o);
+      r2 += __shfl_xor(r2, o);
     }
+    if (c == 0) row[p] = kb_cov(g, r2) - dot;
   }
   __syncthreads();
   if (wave != 0) return;
-  // forward substitution against the rows before, one wave
-  double mine = 0.0;  // lane t: entry t of the new row, once known
-  double sum2 = 0.0;
-  for (int p = 0; p < k; ++p) {
-    double t = lane < p ? mine * g.ls[(size_t)p * a.q + lane] : 0.0;
-    for (int o = 32; o >= 1; o >>= 1) t += __shfl_xor(t, o);
-    const double l = (row[p] - t) / g.ls[(size_t)p * a.q + p];
-    if (lane == p) mine = l;
-    sum2 = fma(l, l, sum2);
+  // Forward substitution against the rows before, one wave: lane t holds what is
+  // left of entry t, and entry p, once known, is taken off the later ones.  The
+  // columns come eight at a time, ahead of their use.
+  const double* lr = g.ls + (size_t)min(lane, max(k - 1, 0)) * a.q;
+  double rest = lane < k ? row[lane] : 0.0;
+  const double inv = lane < k ? 1.0 / lr[lane] : 0.0;
+  double mine = 0.0, sum2 = 0.0;
+  for (int p0 = 0; p0 < k; p0 += 8) {
+    double col[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) col[u] = lane < k && lane > p0 + u ? lr[p0 + u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (p0 + u < k) {
+        const double y = rest * inv;
+        const double l = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(y), p0 + u),
+                                          __builtin_amdgcn_readlane(__double2loint(y), p0 + u));
+        if (lane == p0 + u) mine = l;
+        rest = fma(-l, col[u], rest);
+        sum2 = fma(l, l, sum2);
+      }
+    }
   }
   if (lane < k) g.ls[(size_t)k * a.q + lane] = mine;
   if (lane == 0) {
@@ -271,36 +290,32 @@ __global__ __launch_bounds__(256) void kb_join_kernel(const KbArgs a, int k) {
   else kb_chol(a, g, k);
 }
 
-// sigma after the picks k0 + kn (those before k0 through their stored w).
-// Of a list (list or list64 given; the results go beside it) or of the pool: n
-// entries or (live given) *live, none if that is more than n.  NARROW: 16
-// candidates per workgroup, its four waves sharing the observations; otherwise
-// 64 candidates per wave.  K* as in the posterior (distances on the fp64 matrix
-// cores), the dot products in double.  Bound (whole pool, m = 512, eight
+// sigma after the picks below k1, of a list (list or list64 given; the results
+// go beside it) or of the pool: n entries or (live given) *live, none if that is
+// more than n.  KP picks to a pass over the observations: kPicks from pick 0 on,
+// or one, k1 - 1, with the w of the picks before it in rows, where its own joins
+// them.  NARROW: 16 candidates per workgroup, its four waves sharing the
+// observations (and the rows), w in LDS; otherwise 64 candidates per wave, w
+// stored where a pass follows.  K* as in the posterior (distances on the fp64
+// matrix cores), the dot products in double.  Bound (whole pool, m = 512, eight
 // picks): the covariances, as in the posterior.
-template <int S, bool NARROW>
+template <int S, bool NARROW, int KP>
 __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const int32_t* __restrict__ list,
                                                           const int64_t* __restrict__ list64,
-                                                          const int32_t* __restrict__ live, int64_t n, int k0, int kn,
-                                                          int last) {
+                                                          const int32_t* __restrict__ live, int64_t n, int k1) {
   constexpr int NT = NARROW ? 1 : 4;
+  constexpr int NP = KP == 1 && NARROW ? 2 : KP;  // sums: KP covariances, and with rows sum w^2
   const KbGp& g = a.g[blockIdx.y];
   if (g.S != S) return;
   extern __shared__ __align__(16) unsigned char smem[];
-  double* beta_l = reinterpret_cast<double*>(smem);  // [nj][kPicks][16]; NARROW: [4 waves][16][kPicks]
+  double* beta_l = reinterpret_cast<double*>(smem);  // [nj][KP][16]; NARROW: [4 waves][16][NP]
+  double* w_l = beta_l + 4 * 16 * NP;                // NARROW: [picks][16]
   const int tid = threadIdx.x, lane = tid & 63, gr = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t base = NARROW ? (int64_t)blockIdx.x * 16 : (int64_t)blockIdx.x * 256 + wave * 64;
   if constexpr (NARROW) {
     if (live) n = *live <= n ? *live : 0;
     if (base >= n) return;
-  }
-  if constexpr (!NARROW) {
-    for (int i = tid; i < g.nj * 16 * kPicks; i += 256) {
-      const int j = i / (16 * kPicks), p = (i / 16) % kPicks;
-      beta_l[i] = p < kn ? g.bscale * g.beta[(size_t)(k0 + p) * g.m_pad + 16 * j + (i & 15)] : 0.0;
-    }
-    __syncthreads();
   }
   int64_t cand[NT];
   double bq[NT][S];
@@ -325,127 +340,159 @@ __global__ __launch_bounds__(256, 2) void kb_sigma_kernel(const KbArgs a, const 
       if (k >= a.d) bq[t][s] = k == a.d ? 1.0 : (k == a.d + 1 ? nrm : 0.0);
     }
   }
-  double acc[NT][kPicks];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int p = 0; p < kPicks; ++p) acc[t][p] = 0.0;
+  // the candidate that this lane finishes; wide: lane group gr finishes tile gr
+  const int64_t e = NARROW ? base + c : base + lane;
+  int64_t x;
   if constexpr (NARROW) {
-    // k(x, x_p), one pick per lane group (the waves' sums are added below)
-    const int p = wave * 4 + gr;
-    if (p < kn) {
-      const float* xr = g.xc + cand[0] * a.d;
-      const float* xp = g.xc + a.picks[k0 + p] * a.d;
-      double r2 = 0.0;
-      for (int q = 0; q < a.d; ++q) {
-        const double t = ((double)xr[q] - (double)xp[q]) * g.scale[q];
-        r2 = fma(t, t, r2);
-      }
-      const double kx = kb_cov(g, r2);
-#pragma unroll
-      for (int q = 0; q < kPicks; ++q) acc[0][q] = q == p ? kx : 0.0;
-    }
-  }
-  for (int j = NARROW ? wave : 0; j < g.nj; j += NARROW ? 4 : 1) {
-    double aq[S];
-#pragma unroll
-    for (int s = 0; s < S; ++s) aq[s] = (g.xq + (size_t)j * S * 64)[(unsigned)(s * 64 + lane)];
-    double kv[NT][4];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      d4_t cr = d4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int s = 0; s < S; ++s) cr = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], bq[t][s], cr, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float u = __builtin_amdgcn_sqrtf(fmaxf((float)(-cr[r]), 0.0f));
-        kv[t][r] = (double)(fmaf(u, fmaf(u, g.c2, g.c1), g.c0) * __builtin_amdgcn_exp2f(-u));
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < kPicks; ++p) {
-      if (p < kn) {
-        d4_t b;
-        if constexpr (NARROW)
-          b = g.bscale * *reinterpret_cast<const d4_t*>(g.beta + (size_t)(k0 + p) * g.m_pad + 16 * j + 4 * gr);
-        else
-          b = *reinterpret_cast<const d4_t*>(beta_l + (j * kPicks + p) * 16 + 4 * gr);
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[t][p] = fma(-b[r], kv[t][r], acc[t][p]);
-      }
-    }
-  }
-  // the lane groups' shares; NARROW: the waves' too
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int p = 0; p < kPicks; ++p) {
-      acc[t][p] += __shfl_xor(acc[t][p], 16);
-      acc[t][p] += __shfl_xor(acc[t][p], 32);
-    }
-  double C[kPicks];
-  int64_t e, x;
-  if constexpr (NARROW) {
-    if (gr == 0)
-#pragma unroll
-      for (int p = 0; p < kPicks; ++p) beta_l[(wave * 16 + c) * kPicks + p] = acc[0][p];
-    __syncthreads();
-    if (wave != 0 || gr != 0) return;
-#pragma unroll
-    for (int p = 0; p < kPicks; ++p)
-      C[p] = (beta_l[c * kPicks + p] + beta_l[(16 + c) * kPicks + p]) +
-             (beta_l[(32 + c) * kPicks + p] + beta_l[(48 + c) * kPicks + p]);
-    e = base + c;
     x = cand[0];
   } else {
-    // lane group gr finishes tile gr
-#pragma unroll
-    for (int p = 0; p < kPicks; ++p)
-      C[p] = gr == 0 ? acc[0][p] : (gr == 1 ? acc[NT > 1 ? 1 : 0][p] : (gr == 2 ? acc[NT > 2 ? 2 : 0][p] : acc[NT - 1][p]));
-    e = base + lane;
     x = min(e, n - 1);
     if (list) x = list[x];
   }
-  if (e >= n) return;
-  const double s0 = (double)g.sd0[x];
-  double var = s0 * s0;
-  for (int t = 0; t < k0; ++t) {
-    const double w = (double)g.w[(size_t)t * a.ld + e];
-    var = fma(-w, w, var);
+  const bool mine = e < n && (!NARROW || (wave == 0 && gr == 0));
+  double var = 0.0;
+  if (mine) {
+    const double s0 = (double)g.sd0[x];
+    var = s0 * s0;
   }
+  for (int b = KP == 1 ? k1 - 1 : 0; b < k1; b += KP) {
+    const int kn = min(KP, k1 - b);
+    if (KP > 1 && b > 0) __syncthreads();  // the pass before: its sums or beta are read, its w is written
+    if constexpr (!NARROW) {
+      for (int i = tid; i < g.nj * 16 * KP; i += 256) {
+        const int j = i / (16 * KP), p = (i / 16) % KP;
+        beta_l[i] = p < kn ? g.bscale * g.beta[(size_t)(b + p) * g.m_pad + 16 * j + (i & 15)] : 0.0;
+      }
+      __syncthreads();
+    }
+    double acc[NT][NP];
 #pragma unroll
-  for (int p = 0; p < kPicks; ++p) {
-    if (p < kn) {
-      const double* l = g.ls + (size_t)(k0 + p) * a.q;
-      double w = C[p];
-      if constexpr (!NARROW) {
-        const float* xr = g.xc + x * a.d;
-        const float* xp = g.xc + a.picks[k0 + p] * a.d;
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) acc[t][p] = 0.0;
+    if constexpr (NARROW) {
+      // k(x, x_p), one pick per lane group (the waves' sums are added below)
+      const int p = wave * 4 + gr;
+      if (p < kn) {
+        const float* xr = g.xc + cand[0] * a.d;
+        const float* xp = g.xc + a.picks[b + p] * a.d;
         double r2 = 0.0;
         for (int q = 0; q < a.d; ++q) {
           const double t = ((double)xr[q] - (double)xp[q]) * g.scale[q];
           r2 = fma(t, t, r2);
         }
-        w += kb_cov(g, r2);
-      }
-      for (int t = 0; t < k0; ++t) w = fma(-l[t], (double)g.w[(size_t)t * a.ld + e], w);
+        const double kx = kb_cov(g, r2);
 #pragma unroll
-      for (int t = 0; t < p; ++t) w = fma(-l[k0 + t], C[t], w);
-      C[p] = w / l[k0 + p];
-      var = fma(-C[p], C[p], var);
-      if (!last) g.w[(size_t)(k0 + p) * a.ld + e] = (float)C[p];
+        for (int q = 0; q < KP; ++q) acc[0][q] = q == p ? kx : 0.0;
+      }
+      // the earlier picks' w, one per lane group
+      const int64_t at = min(base + c, n - 1);
+      for (int t = p; t < b; t += 16) {
+        const double w = KP == 1 ? (double)g.w[(size_t)t * a.ld + at] : w_l[t * 16 + c];
+#pragma unroll
+        for (int q = 0; q < KP; ++q)
+          if (q < kn) acc[0][q] = fma(-g.ls[(size_t)(b + q) * a.q + t], w, acc[0][q]);
+        if constexpr (KP == 1) acc[0][1] = fma(-w, w, acc[0][1]);
+      }
+    }
+    for (int j = NARROW ? wave : 0; j < g.nj; j += NARROW ? 4 : 1) {
+      double aq[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) aq[s] = (g.xq + (size_t)j * S * 64)[(unsigned)(s * 64 + lane)];
+      double kv[NT][4];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        d4_t cr = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < S; ++s) cr = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[s], bq[t][s], cr, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float u = __builtin_amdgcn_sqrtf(fmaxf((float)(-cr[r]), 0.0f));
+          kv[t][r] = (double)(fmaf(u, fmaf(u, g.c2, g.c1), g.c0) * __builtin_amdgcn_exp2f(-u));
+        }
+      }
+#pragma unroll
+      for (int p = 0; p < KP; ++p) {
+        if (p < kn) {
+          d4_t bv;
+          if constexpr (NARROW)
+            bv = g.bscale * *reinterpret_cast<const d4_t*>(g.beta + (size_t)(b + p) * g.m_pad + 16 * j + 4 * gr);
+          else
+            bv = *reinterpret_cast<const d4_t*>(beta_l + (j * KP + p) * 16 + 4 * gr);
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[t][p] = fma(-bv[r], kv[t][r], acc[t][p]);
+        }
+      }
+    }
+    // the lane groups' shares; NARROW: the waves' too
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        acc[t][p] += __shfl_xor(acc[t][p], 16);
+        acc[t][p] += __shfl_xor(acc[t][p], 32);
+      }
+    double C[NP];
+    if constexpr (NARROW) {
+      if (gr == 0)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) beta_l[(wave * 16 + c) * NP + p] = acc[0][p];
+      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        C[p] = (beta_l[c * NP + p] + beta_l[(16 + c) * NP + p]) + (beta_l[(32 + c) * NP + p] + beta_l[(48 + c) * NP + p]);
+    } else {
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        C[p] = gr == 0 ? acc[0][p]
+                       : (gr == 1 ? acc[NT > 1 ? 1 : 0][p] : (gr == 2 ? acc[NT > 2 ? 2 : 0][p] : acc[NT - 1][p]));
+    }
+    if (!mine) continue;
+    if constexpr (KP == 1 && NARROW) var += C[1];
+#pragma unroll
+    for (int p = 0; p < KP; ++p) {
+      if (p < kn) {
+        const double* l = g.ls + (size_t)(b + p) * a.q;
+        double w = C[p];
+        if constexpr (!NARROW) {
+          const float* xr = g.xc + x * a.d;
+          const float* xp = g.xc + a.picks[b + p] * a.d;
+          double r2 = 0.0;
+          for (int q = 0; q < a.d; ++q) {
+            const double t = ((double)xr[q] - (double)xp[q]) * g.scale[q];
+            r2 = fma(t, t, r2);
+          }
+          w += kb_cov(g, r2);
+          for (int t0 = 0; t0 < b; t0 += 8) {  // eight loads in flight
+            float wt[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) wt[t] = g.w[(size_t)min(t0 + t, b - 1) * a.ld + e];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+              const double wd = t0 + t < b ? (double)wt[t] : 0.0;
+              w = fma(-l[min(t0 + t, b - 1)], wd, w);
+              if constexpr (KP == 1) var = fma(-wd, wd, var);
+            }
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < p; ++t) w = fma(-l[b + t], C[t], w);
+        C[p] = w / l[b + p];
+        var = fma(-C[p], C[p], var);
+        if constexpr (NARROW && KP > 1) w_l[(b + p) * 16 + c] = C[p];
+        if (KP == 1 || (!NARROW && b + KP < k1)) g.w[(size_t)(b + p) * a.ld + e] = (float)C[p];
+      }
     }
   }
-  if (last) {
-    const float sd = (float)sqrt(fmax(var, 0.0));
-    if (list || list64) {
-      g.sd_list[e] = sd;
-      g.mu_list[e] = g.mu[x];
-    } else {
-      g.sd_out[e] = sd;
-    }
+  if (!mine) return;
+  const float sd = (float)sqrt(fmax(var, 0.0));
+  if (list || list64) {
+    g.sd_list[e] = sd;
+    g.mu_list[e] = g.mu[x];
+  } else {
+    g.sd_out[e] = sd;
   }
 }
 
@@ -565,9 +612,24 @@ struct KbLayout {
   size_t total;
 };
 
-// Rows of w that are kept: the last chunk of the at most q - 1 picks that a
-// score carries keeps none.
-int kb_w_rows(int q) { return q > 2 ? (q - 2) / kPicks * kPicks : 0; }
+// Whether every pick scores the whole pool, in a chain of six launches.  The
+// other way's twelve cost some 30 us a pick more whatever the pool, and the
+// first guesses and the list go over all the picks before; a pool's pass costs
+// the covariances and about 64 of them more per candidate and objective for the
+// scores and w.  Both sides, ms: p = 1, m = 256, n = 131,072, q = 4 0.34 and
+// 0.41, q = 32 2.4 and 4.0; p = 3, m = 64, n = 262,144, q = 9 1.23 and 1.12, q =
+// 64 9.3 and 10.1; p = 2, m = 512, n = 262,144, q = 32 8.3 and 6.2.
+bool kb_direct(const GPDevice* const* g, int p, int64_t n, int q) {
+  int64_t each = 0;
+  for (int j = 0; j < p; ++j) each += (g[j]->m + 15) / 16 * 16 + 64;
+  return n <= ((int64_t)(72 + 5 * q / 2) << 20) / each;
+}
+// Rows of w that are kept: of every pick that a score carries, or of those but
+// for the last chunk.
+int kb_w_rows(const GPDevice* const* g, int p, int64_t n, int q) {
+  if (kb_direct(g, p, n, q)) return q - 1;
+  return q > 2 ? (q - 2) / kPicks * kPicks : 0;
+}
 
 KbLayout kb_layout(const GPDevice* const* g, int p, int64_t n, int q) {
   KbLayout L{};
@@ -591,7 +653,7 @@ KbLayout kb_layout(const GPDevice* const* g, int p, int64_t n, int q) {
   L.mu_list = take((size_t)p * std::max<int64_t>(n, kTop) * 4);
   L.sd_list = take((size_t)p * std::max<int64_t>(n, kTop) * 4);
   L.val = take((size_t)std::max<int64_t>(n, kTop) * 4);
-  L.w = take((size_t)p * kb_w_rows(q) * std::max<int64_t>(n, kTop) * 4);
+  L.w = take((size_t)p * kb_w_rows(g, p, n, q) * std::max<int64_t>(n, kTop) * 4);
   L.xw = take(xw);
   L.idx = take(kTop * 8);
   L.score = take(kTop * 4);
@@ -608,44 +670,41 @@ KbLayout kb_layout(const GPDevice* const* g, int p, int64_t n, int q) {
   return L;
 }
 
-template <int S, bool NARROW>
-int launch_sigma_s(const KbArgs& a, const int32_t* list, const int64_t* list64, const int32_t* live, int64_t n, int k0,
-                   int kn, bool last, hipStream_t s) {
-  auto kern = kb_sigma_kernel<S, NARROW>;
+template <int S, bool NARROW, int KP>
+int launch_sigma_s(const KbArgs& a, const int32_t* list, const int64_t* list64, const int32_t* live, int64_t n, int k1,
+                   hipStream_t s) {
+  auto kern = kb_sigma_kernel<S, NARROW, KP>;
   int nj = 0;
   for (int j = 0; j < a.p; ++j) nj = std::max(nj, a.g[j].nj);
-  const size_t lds = NARROW ? (size_t)4 * 16 * kPicks * 8 : (size_t)nj * 16 * kPicks * 8;
+  // [4 waves][16][sums] and w, or beta
+  const size_t lds = NARROW ? (size_t)(4 * 16 * (KP == 1 ? 2 : KP) + (KP == 1 ? 0 : k1 * 16)) * 8 : (size_t)nj * 16 * KP * 8;
   const int rc = allow_full_lds((const void*)kern, "believer");
   if (rc != SCOOT_OK) return rc;
   const int64_t blocks = NARROW ? (n + 15) / 16 : (n + 255) / 256;
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)a.p), dim3(256), lds, s, a, list, list64, live, n, k0,
-                     kn, last ? 1 : 0);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)a.p), dim3(256), lds, s, a, list, list64, live, n, k1);
   return SCOOT_OK;
 }
 
-int launch_sigma(const KbArgs& a, const int32_t* list, const int64_t* list64, const int32_t* live, int64_t n, int picks,
-                 hipStream_t s) {
+// one: pick k1 - 1 over the whole pool, from the rows of w before it.
+int launch_sigma(const KbArgs& a, const int32_t* list, const int64_t* list64, const int32_t* live, int64_t n, int k1,
+                 bool one, hipStream_t s) {
   if (n == 0) return SCOOT_OK;
-  const bool narrow = live || list64 || n <= kWide;
-  for (int k0 = 0; k0 < picks; k0 += kPicks) {
-    const int kn = std::min(kPicks, picks - k0);
-    const bool last = k0 + kn == picks;
-    auto launch = [&](auto S) {
-      constexpr int s_ = decltype(S)::value;
-      return narrow ? launch_sigma_s<s_, true>(a, list, list64, live, n, k0, kn, last, s)
-                    : launch_sigma_s<s_, false>(a, list, list64, live, n, k0, kn, last, s);
-    };
-    int rc;
-    switch (a.g[0].S) {  // the GPs share d
-      case 1: rc = launch(std::integral_constant<int, 1>()); break;
-      case 2: rc = launch(std::integral_constant<int, 2>()); break;
-      case 3: rc = launch(std::integral_constant<int, 3>()); break;
-      case 4: rc = launch(std::integral_constant<int, 4>()); break;
-      default: rc = launch(std::integral_constant<int, 5>()); break;
-    }
-    if (rc != SCOOT_OK) return rc;
+  const bool narrow = live || list64 || (one ? a.p * n <= kWideOne : n <= kWide);
+  auto launch = [&](auto S) {
+    constexpr int s_ = decltype(S)::value;
+    if (one)
+      return narrow ? launch_sigma_s<s_, true, 1>(a, list, list64, live, n, k1, s)
+                    : launch_sigma_s<s_, false, 1>(a, list, list64, live, n, k1, s);
+    return narrow ? launch_sigma_s<s_, true, kPicks>(a, list, list64, live, n, k1, s)
+                  : launch_sigma_s<s_, false, kPicks>(a, list, list64, live, n, k1, s);
+  };
+  switch (a.g[0].S) {  // the GPs share d
+    case 1: return launch(std::integral_constant<int, 1>());
+    case 2: return launch(std::integral_constant<int, 2>());
+    case 3: return launch(std::integral_constant<int, 3>());
+    case 4: return launch(std::integral_constant<int, 4>());
+    default: return launch(std::integral_constant<int, 5>());
   }
-  return SCOOT_OK;
 }
 
 }  // namespace
@@ -679,6 +738,7 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
   int32_t* count_d = (int32_t*)(w + L.count);
   unsigned long long* top = (unsigned long long*)(w + L.top);
   const int64_t nl = std::max<int64_t>(n, kTop);
+  const bool direct = kb_direct(g, p, n, q);
   int m_pad = 0;
   for (int j = 0; j < p; ++j) m_pad = std::max(m_pad, g[j]->m_pad);
 
@@ -709,10 +769,11 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
     o.v = (double*)(w + L.v) + (size_t)j * m_pad;
     o.beta = (double*)(w + L.beta) + (size_t)j * q * m_pad;
     o.ls = (double*)(w + L.ls) + (size_t)j * q * q;
-    o.w = (float*)(w + L.w) + (size_t)j * kb_w_rows(q) * nl;
+    o.w = (float*)(w + L.w) + (size_t)j * kb_w_rows(g, p, n, q) * nl;
     o.mu_list = (float*)(w + L.mu_list) + (size_t)j * nl;
     o.sd_list = (float*)(w + L.sd_list) + (size_t)j * nl;
-    o.sd_out = sigma_out ? sigma_out + (size_t)j * n : nullptr;
+    // where every pick scores the pool: sigma after the picks, beside no list
+    o.sd_out = direct ? o.sd_list : sigma_out ? sigma_out + (size_t)j * n : nullptr;
     for (int k = 0; k < SCOOT_MAX_DIM; ++k) o.scale[k] = g[j]->scale64[k];
     o.c0d = g[j]->coef64[0];
     o.c1d = g[j]->coef64[1];
@@ -768,12 +829,15 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
     };
     if (k == 0) {
       hipLaunchKernelGGL(kb_zero_kernel, dim3(1), dim3(1), 0, s, count_d);
-      rc = launch_ehvi_topq(mus, sds, p, n, SCOOT_F32, bt, bound, elig, kTop, idx, score, nvalid, stream);
+      rc = launch_ehvi_topq(mus, sds, p, n, SCOOT_F32, bt, bound, elig, direct ? 1 : kTop, idx, score, nvalid, stream);
+      if (rc == SCOOT_OK) rc = pick(idx, n);
+    } else if (direct) {
+      rc = launch_ehvi_topq(mus, sdl, p, n, SCOOT_F32, bt, bound, elig, 1, idx, score, nvalid, stream);
       if (rc == SCOOT_OK) rc = pick(idx, n);
     } else {
       const dim3 blocks((unsigned)std::min<int64_t>((n + 256 * kCompact - 1) / (256 * kCompact), 2048));
       auto score_list = [&](const int32_t* live, int64_t entries, const int64_t* guesses) {
-        int rc = launch_sigma(a, list, nullptr, live, entries, k, s);
+        int rc = launch_sigma(a, list, nullptr, live, entries, k, false, s);
         if (rc == SCOOT_OK) rc = launch_ehvi(mul, sdl, p, entries, SCOOT_F32, bt, val, stream);
         if (rc == SCOOT_OK && entries > 0)
           hipLaunchKernelGGL(kb_scatter_kernel, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, s, list, live,
@@ -788,7 +852,7 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
       // The first guesses: the best bounds after the last pick.  The length of
       // the list that they leave stays on the device until the pick.
       const int64_t cap = std::min<int64_t>(n, kListed);
-      rc = launch_sigma(a, nullptr, idx + 1, nullptr, kTop - 1, k, s);
+      rc = launch_sigma(a, nullptr, idx + 1, nullptr, kTop - 1, k, false, s);
       if (rc == SCOOT_OK) rc = launch_ehvi(mul, sdl, p, kTop - 1, SCOOT_F32, bt, first, stream);
       if (rc != SCOOT_OK) return rc;
       hipLaunchKernelGGL(kb_compact_kernel<true>, blocks, dim3(256), 0, s, bound, elig, n, idx + 1, first, 0u, top,
@@ -822,10 +886,12 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
     hipLaunchKernelGGL(kb_join_kernel, dim3((unsigned)nj + 1, (unsigned)p), dim3(256), 0, s, a, k);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return device_error(e);
-    if (k > 0) {
+    rc = SCOOT_OK;
+    if (direct)
+      rc = launch_sigma(a, nullptr, nullptr, nullptr, n, k + 1, true, s);
+    else if (k > 0)
       rc = launch_topq(bound, elig, n, SCOOT_F32, kTop - 1, idx + 1, score + 1, nvalid, stream);
-      if (rc != SCOOT_OK) return rc;
-    }
+    if (rc != SCOOT_OK) return rc;
   }
   // the posterior the last scoring round saw (mu never moves; sigma carries
   // the picks before that round)
@@ -833,10 +899,12 @@ int run_kriging_believer(const GPDevice* const* g, int p, const ForestDevice* f,
   if (mu_out) e = hipMemcpyAsync(mu_out, mu, (size_t)p * n * 4, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess && sigma_out) {
     const int seen = *n_picked == q ? q - 1 : *n_picked;
-    if (seen == 0) {
-      e = hipMemcpyAsync(sigma_out, sd, (size_t)p * n * 4, hipMemcpyDeviceToDevice, s);
+    if (seen == 0 || direct) {
+      for (int j = 0; j < p && e == hipSuccess; ++j)
+        e = hipMemcpyAsync(sigma_out + (size_t)j * n, seen ? a.g[j].sd_list : a.g[j].sd0, (size_t)n * 4,
+                           hipMemcpyDeviceToDevice, s);
     } else {
-      rc = launch_sigma(a, nullptr, nullptr, nullptr, n, seen, s);
+      rc = launch_sigma(a, nullptr, nullptr, nullptr, n, seen, false, s);
       if (rc != SCOOT_OK) return rc;
       e = hipGetLastError();
     }

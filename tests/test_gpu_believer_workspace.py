@@ -13,10 +13,12 @@ DEV = "cuda:0"
 GUARD = 4096
 
 
-# n: narrow and wide lists; q: no, eight and sixteen kept rows
+# n: pools scored whole at every pick, by the narrow and the wide kernel, which keep a row per pick; larger ones,
+# which keep none, eight or sixteen rows
 @pytest.mark.parametrize("offset", [0, 4, 1])
 @pytest.mark.parametrize("n,q,warped", [(5, 3, False), (300, 9, False), (300, 64, True), (70001, 10, False),
-                                        (70001, 18, True)])
+                                        (1048579, 9, False), (1048579, 10, False),
+                                        (1048579, 18, True)])
 def test_reported_size_is_what_the_call_uses(n, q, warped, offset):
     print("[case] believer workspace", n, q, warped, offset, flush=True)
     d, p, m = 3, 2, 40
@@ -27,8 +29,8 @@ def test_reported_size_is_what_the_call_uses(n, q, warped, offset):
     pool = torch.from_numpy(rng.random((n, d)).astype(np.float32)).to(DEV)
     ref = Y.max(0) + 0.2
     size = S.suggest_kb_workspace(gps, n, q)
-    # per candidate; (q - 2) / 8 chunks of eight rows; the factors of q picks; rounding to 256 bytes
-    rows = (q - 2) // 8 * 8
+    # per candidate; the rows; the factors of q picks; rounding to 256 bytes
+    rows = q - 1 if n < 100000 else (q - 2) // 8 * 8
     most = n * (16 * p + 17 + 4 * p * rows + (4 * d * p if warped else 0))
     small = p * (q + 1) * 64 * 8 + p * q * q * 8 + 8 * q
     assert size <= most + small + 32 * 256 + 32 * p * 8
