@@ -158,7 +158,8 @@ __global__ __launch_bounds__(THREADS) void ehvi_strip_select_kernel(
 // A workgroup is kEhviWaves waves over the same kEhviThreads candidates: the
 // tables are (n1 + n2) x 64 values whatever the number of waves, 46 KB at a
 // front of 90, so that a compute unit holds three workgroups and one wave each
-// would leave a SIMD idle and the others without a second wave.  The waves
+// would leave a SIMD idle and the others without a second wave (one wave alone
+// for large pools and small fronts).  The waves
 // share the tables' rows and the columns (ranges of about equal cost, chosen
 // on the host).  Bound: issue, about 50 instructions per partial expectation
 // and nine per box.  2^20 candidates, fronts of 90 (900 boxes): one wave 556
@@ -170,8 +171,8 @@ struct Ehvi3Args {
   int col[kEhviWaves + 1];  // wave w takes columns col[w] .. col[w + 1] - 1
 };
 
-template <typename T>
-__global__ __launch_bounds__(kEhviThreads* kEhviWaves) void ehvi3_kernel(
+template <typename T, int WAVES>
+__global__ __launch_bounds__(kEhviThreads* WAVES) void ehvi3_kernel(
     const T* __restrict__ mu0, const T* __restrict__ mu1, const T* __restrict__ mu2,
     const T* __restrict__ sd0, const T* __restrict__ sd1, const T* __restrict__ sd2,
     const T* __restrict__ coords, const uint32_t* __restrict__ rec, const uint32_t* __restrict__ col_end,
@@ -189,11 +190,11 @@ __global__ __launch_bounds__(kEhviThreads* kEhviWaves) void ehvi3_kernel(
   const T* c0 = coords;
   const T* c1 = coords + a.n0;
   const T* c2 = c1 + a.n1;
-  for (int q = wave; q < a.n1; q += kEhviWaves)  // row 0: -inf
+  for (int q = wave; q < a.n1; q += WAVES)  // row 0: -inf
     g[q * kEhviThreads + lane] = q ? partial_expectation<T>(c1[q], m1, s1, r1) : T(0);
-  for (int q = kEhviWaves - 1 - wave; q < a.n2; q += kEhviWaves)
+  for (int q = WAVES - 1 - wave; q < a.n2; q += WAVES)
     g[(a.n1 + q) * kEhviThreads + lane] = q ? partial_expectation<T>(c2[q], m2, s2, r2) : T(0);
-  __syncthreads();
+  if constexpr (WAVES > 1) __syncthreads();
   const int first = a.col[wave], last = a.col[wave + 1];
   T acc = T(0), g0_prev = first > 0 && first < last ? partial_expectation<T>(c0[first], m0, s0, r0) : T(0);
   int b = first > 0 ? (int)col_end[first - 1] : 0;
@@ -212,14 +213,15 @@ __global__ __launch_bounds__(kEhviThreads* kEhviWaves) void ehvi3_kernel(
     acc += (g0 - g0_prev) * col;
     g0_prev = g0;
   }
-  __syncthreads();  // the tables (four rows and more) are read: the waves' sums take their place
-  g[wave * kEhviThreads + lane] = acc;
-  __syncthreads();
-  if (wave == 0 && live) {
+  if constexpr (WAVES > 1) {
+    __syncthreads();  // the tables (four rows and more) are read: the waves' sums take their place
+    g[wave * kEhviThreads + lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
 #pragma unroll
-    for (int w = 1; w < kEhviWaves; ++w) acc += g[w * kEhviThreads + lane];
-    out[c] = acc;
+    for (int w = 1; w < WAVES; ++w) acc += g[w * kEhviThreads + lane];
   }
+  if (live) out[c] = acc;
 }
 
 int launch_ei(const void* mu, const void* sigma, int64_t n, scoot_dtype dt, double c, void* ei,
@@ -347,10 +349,21 @@ int run_ehvi3(const void* const* mu, const void* const* sigma, int64_t n, const 
   }
   if (nb == 0 || col != ncol - 1 || j_next != a.n1 - 1) return fail(SCOOT_ERR_DEVICE, "ehvi: unexpected box layout");
   ce[col] = (uint32_t)nb;
+  // One wave where its tables are small enough for a compute unit to hold many
+  // such workgroups and the pool has that many: the barriers and the shared sums
+  // are saved.  fp32, one and four waves: 2^20 candidates, fronts of 1 10 and 17
+  // us, of 6 22 and 30, of 10 39 and 43, of 15 61 and 54; 131,072, of 3 4.4 and
+  // 5.2, of 10 10.1 and 8.6; 65,536, of 3 4.9 and 4.1.
+  int device = 0, cus = 256;
+  (void)hipGetDevice(&device);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
+  const int64_t tiles = (n + kEhviThreads - 1) / kEhviThreads;
+  const bool one = (lds <= 6144 && tiles >= 16 * (int64_t)cus) || (lds <= 3072 && tiles >= 8 * (int64_t)cus);
+  const int waves = one ? 1 : kEhviWaves;
   // Columns to waves, by boxes and six boxes' worth for a column's G_0.
-  for (int w = 1, i = 0; w <= kEhviWaves; ++w) {
-    const int64_t target = (int64_t)(nb + 6 * ncol) * w / kEhviWaves;
-    while (i < ncol && (w == kEhviWaves || (int64_t)ce[i] + 6 * (i + 1) <= target)) ++i;
+  for (int w = 1, i = 0; w <= waves; ++w) {
+    const int64_t target = (int64_t)(nb + 6 * ncol) * w / waves;
+    while (i < ncol && (w == waves || (int64_t)ce[i] + 6 * (i + 1) <= target)) ++i;
     a.col[w] = i;
   }
   void* dev = device_scratch(blob.size(), 1);
@@ -360,16 +373,17 @@ int run_ehvi3(const void* const* mu, const void* const* sigma, int64_t n, const 
   const T* coords = reinterpret_cast<const T*>(dev);
   const uint32_t* recs = reinterpret_cast<const uint32_t*>((const unsigned char*)dev + coord_bytes);
   const uint32_t* col_end = reinterpret_cast<const uint32_t*>((const unsigned char*)dev + coord_bytes + rec_bytes);
-  rc = allow_full_lds((const void*)ehvi3_kernel<T>, "ehvi");
+  auto kern = waves == 1 ? ehvi3_kernel<T, 1> : ehvi3_kernel<T, kEhviWaves>;
+  rc = allow_full_lds((const void*)kern, "ehvi");
   if (rc != SCOOT_OK) return rc;
-  // A launch holds fewer than 2^32 threads, four per candidate here: pools of
+  // A launch holds fewer than 2^32 threads, up to four per candidate: pools of
   // 2^30 candidates and more take several.
   constexpr int64_t kSpan = (int64_t)1 << 29;
   for (int64_t at = 0; at < n; at += kSpan) {
     a.n = std::min(kSpan, n - at);
     const unsigned grid = (unsigned)((a.n + kEhviThreads - 1) / kEhviThreads);
-    hipLaunchKernelGGL(ehvi3_kernel<T>, dim3(grid), dim3(kEhviThreads * kEhviWaves), lds, s, (const T*)mu[0] + at,
-                       (const T*)mu[1] + at, (const T*)mu[2] + at, (const T*)sigma[0] + at, (const T*)sigma[1] + at,
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kEhviThreads * waves), lds, s, (const T*)mu[0] + at, (const T*)mu[1] + at,
+                       (const T*)mu[2] + at, (const T*)sigma[0] + at, (const T*)sigma[1] + at,
                        (const T*)sigma[2] + at, coords, recs, col_end, (T*)out + at, a);
   }
   hipError_t err = hipGetLastError();
