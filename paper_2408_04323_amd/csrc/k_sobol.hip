@@ -41,7 +41,7 @@ namespace {
 constexpr int kSobolThreads = 256;
 constexpr int kSobolRun = 16;       // points per thread; runs start at multiples of 16
 constexpr int kSobolBits = 32;
-// Workgroups of a large pool: six per compute unit, what its LDS holds, each
+// Workgroups of a large pool: six per compute unit (eight take the same time), each
 // loading the direction numbers once and looping over chunks of 256 / d runs.
 constexpr int kSobolBlocks = 256 * 6;
 
@@ -150,19 +150,37 @@ __global__ __launch_bounds__(kSobolThreads) void sobol_pool_kernel(float* __rest
 
     const int64_t row_base = a.row0 + chunk * kPts;
     float* to = Xc + row_base * D;
+    // By 16 bytes where the chunk is whole and aligned, else by element.  From
+    // seven dimensions on a run per wave at a time, without a division; a run of
+    // fewer would leave most lanes idle (n = 2^24, one run per wave and flat: d =
+    // 9 unaligned 182 and 217 us, d = 1 aligned 49 and 32).
     if (row_base >= 0 && row_base + kPts <= a.n && ((uintptr_t)to & 15) == 0) {
-      // 4 D <= 64 vectors of four floats per run, one run per wave at a time
-      for (int rr = wave; rr < R; rr += kSobolThreads / 64) {
-        if (lane < 4 * D) {
-          const float* from = tile + rr * kRow + 4 * lane;
-          reinterpret_cast<float4*>(to)[rr * 4 * D + lane] = float4{from[0], from[1], from[2], from[3]};
+      if constexpr (D >= 7) {
+        // 4 D <= 64 vectors of four floats per run
+        for (int rr = wave; rr < R; rr += kSobolThreads / 64) {
+          if (lane < 4 * D) {
+            const float* from = tile + rr * kRow + 4 * lane;
+            reinterpret_cast<float4*>(to)[rr * 4 * D + lane] = float4{from[0], from[1], from[2], from[3]};
+          }
+        }
+      } else {
+        for (int v = tid; v < R * 4 * D; v += kSobolThreads) {
+          const float* from = tile + 4 * v + v / (4 * D) * D;
+          reinterpret_cast<float4*>(to)[v] = float4{from[0], from[1], from[2], from[3]};
         }
       }
     } else {
-      const int64_t e_base = row_base * D, e_end = a.n * D;
-      for (int e = tid; e < kPts * D; e += kSobolThreads) {
-        const int64_t ge = e_base + e;
-        if (ge >= 0 && ge < e_end) Xc[ge] = tile[e + e / (kSobolRun * D) * D];
+      const int64_t lo = -row_base * D, hi = (a.n - row_base) * D;
+      if constexpr (D >= 7) {
+        for (int rr = wave; rr < R; rr += kSobolThreads / 64)
+#pragma unroll
+          for (int i = 0; i < (kSobolRun * D + 63) / 64; ++i) {
+            const int e = i * 64 + lane, at = rr * kSobolRun * D + e;
+            if (e < kSobolRun * D && at >= lo && at < hi) to[at] = tile[rr * kRow + e];
+          }
+      } else {
+        for (int e = tid; e < kPts * D; e += kSobolThreads)
+          if (e >= lo && e < hi) to[e] = tile[e + e / (kSobolRun * D) * D];
       }
     }
     if (known) {
