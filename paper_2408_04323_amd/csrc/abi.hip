@@ -150,10 +150,7 @@ GPDevice describe(const FitHost& f, const double* warp_a, const double* warp_b, 
   g.tau2 = f.tau2;
   g.c = f.c;
   g.s2_exp = f.s2_exp;
-  for (int k = 0; k < SCOOT_MAX_DIM; ++k) {
-    g.scale64[k] = k < f.d ? f.scale[k] : 0.0;
-    g.scale32[k] = (float)g.scale64[k];
-  }
+  for (int k = 0; k < SCOOT_MAX_DIM; ++k) g.scale64[k] = k < f.d ? f.scale[k] : 0.0;
   for (int i = 0; i < 3; ++i) {
     g.coef64[i] = f.coef[i];
     g.coef32[i] = (float)std::ldexp(f.coef[i], -2 * g.s2_exp);

@@ -27,9 +27,9 @@ constexpr double kPadCoord = 1.0e4;    // scaled coordinate of padding rows: k(x
 #define SCOOT_HOST_DEVICE
 #endif
 
-// Waves per workgroup of the posterior: more than 9 granules of K*
-// (72 KiB of LDS per 64-candidate tile) leave room for one workgroup per CU,
-// so it gets 8 waves; otherwise two 4-wave workgroups share a CU.
+// Waves per workgroup of the fp64 posterior: more than 9 row blocks of K* (72
+// KiB of LDS per tile of 32 candidates) leave room for one workgroup per CU, so
+// it gets 8 waves; otherwise two 4-wave workgroups share a CU.
 inline int posterior_waves(int nb) { return nb > 9 ? 8 : 4; }
 
 // Units (32 rows x 16 columns) of the fp32 posterior's stream of L^-1: at
@@ -40,8 +40,7 @@ inline int post_units(int nj, int nb32) {
   return u;
 }
 
-// Which 16-row blocks of V each wave of the posterior owns (both
-// precisions).  Row block I costs I + 1 blocks of the triangle.  Plan entry p
+// Which 16-row blocks of V each wave of the fp64 posterior owns.  Row block I costs I + 1 blocks of the triangle.  Plan entry p
 // goes to wave p of a 4-wave workgroup; with 8 waves the two entries p and
 // p + 4 share a SIMD and its matrix unit.  So the rows are first split into
 // four sets of (nearly) equal cost, one per SIMD, by a depth-first search for
@@ -326,7 +325,6 @@ struct GPDevice {
                               // fp64: m_pad x kXsStride scaled rows, alpha_i in column d when d < kXsStride
   const double* alpha = nullptr;  // m_pad
   const float* alpha32 = nullptr; // m_pad, float copy of alpha times 4^s2_exp
-  float scale32[SCOOT_MAX_DIM];
   double scale64[SCOOT_MAX_DIM];
   // fp32, s2_exp as in FitHost: covariances are held divided by 4^s2_exp and
   // L^-1 multiplied by 2^s2_exp, so that neither overflows, nor do the

@@ -6,17 +6,13 @@
 //   sigma[c] = sqrt(max(0, s2 - sum_i V[i, c]^2))   (Eq. 5, latent f)
 //   ei[c]    = G(best + xi)   optional fused EI epilogue (Eq. 8)
 //
-// One workgroup owns a tile of candidates (64 in fp32, 32 in fp64) and runs
-// three phases:
-//   1. generate: every wave computes K* for a share of the observation rows,
-//      for all candidates of the tile, straight into LDS in the B-operand
-//      order of the MFMA instruction; alpha is folded in on the way (mu);
-//   2. multiply: every wave takes whole row blocks I of V (a per-SIMD row plan
-//      keeps the triangular work balanced), accumulates sum_{J<=I} Linv[I,J] K*[J]
-//      on the matrix cores (A from the packed L^-1 in L2, B from LDS), and
-//      keeps only the squared norms of its rows;
-//   3. reduce: partial norms and means of all waves are summed per candidate.
-// K* and V never touch HBM.  L^-1 is shared by every workgroup (L2-resident).
+// One workgroup owns a tile of candidates at a time.  K* is made on chip and
+// goes into LDS in the B-operand order of the matrix instruction, alpha folded
+// in on the way (mu); the waves share the row blocks of V and keep only the
+// squared norms of their rows.  In fp32 the observation blocks are the outer loop
+// and K* of the next one is made beside the product of this one; in fp64 a tile
+// goes through generation, product and reduction in turn.  K* and V never touch
+// HBM.  L^-1 is shared by every workgroup (L2-resident).
 //
 // Covariance with folded constants: with per-dimension scale
 // w_k = sqrt5 * log2(e) / l_k, u = sqrt(sum_k (w_k (x_k - X_ik))^2) equals
@@ -70,12 +66,16 @@ __device__ inline double partial_expectation_d(double c, double mu, double sd) {
 // with L^-1 = a1 + a2 + a3 (split on the host, from double) and K* = b1 + b2 +
 // b3 (split in registers) a product is the six terms a1 b1, a1 b2, a2 b1,
 // a2 b2, a1 b3, a3 b1, accumulated in float, smallest first; the three terms
-// left out are below 2^-25 of the product.  Measured against 64 bits: sigma no
-// further off than with fp32 MFMA chains.  Why: six bf16 instructions take
+// left out are below 2^-25 of the product.  Error against 64 bits, 2-norm over
+// the pool and root mean square over data sets, with fp32 MFMA chains and now:
+// m = 32 (200 sets) mu 2.4e-7 and 2.2e-7, sigma 4.0e-8 and 3.6e-8; m = 256 (40)
+// 3.7e-7 and 3.1e-7, 5.3e-8 and 4.7e-8; m = 512 (24) 4.8e-7 and 4.0e-7, 5.0e-8 and
+// 4.3e-8: the instruction rounds a sum of 16 products once or twice, to
+// nearest, the fp32 one after every product.  Why: six bf16 instructions take
 // 6/16 of the fp32 instruction's time, and while the fp32 matrix instruction
 // and the vector ALU exclude each other, a bf16 one leaves the vector ALU free
-// for about 19 of its 32 cycles (measured), so the K* generation is woven
-// into the product, four vector instructions or so after each matrix one.
+// for about 19 of its 32 cycles (measured), which the K* generation of this
+// wave and of the others on its SIMD can use.
 //
 // Loop order: observation blocks j of 16 outermost, and inside the row blocks
 // P >= j / 2, their accumulators (two 32 x 32 tiles of 16 registers each)
@@ -442,8 +442,14 @@ __global__ __launch_bounds__(RS * 64, WPS) void posterior_f32_kernel(
 // K*[16J + 4s + l/16][16ct + l%16]; K* is stored as (J, ct, s/2, lane)
 // double2, component s%2.  Accumulator register r of lane l holds row
 // l/16 + 4r, column l%16 of its tile (only column sums of squares are taken,
-// so the row order does not matter here).  Same three phases and persistent
-// loop as the fp32 kernel.
+// so the row order does not matter here).  A persistent workgroup takes every
+// tile through three phases:
+//   1. generate: every wave computes K* for a share of the observation rows, for
+//      all candidates of the tile;
+//   2. multiply: every wave takes whole row blocks I of V (a per-SIMD row plan
+//      keeps the triangular work balanced), sum_{J<=I} Linv[I,J] K*[J] with A
+//      from the packed L^-1 in L2 and B from LDS;
+//   3. reduce: partial norms and means of all waves are summed per candidate.
 // ---------------------------------------------------------------------------
 struct Post64 {
   int64_t n;
@@ -489,8 +495,8 @@ __device__ inline void mfma_block16_at(int J, d4_t& l0, d4_t& l1, const d2_t (&a
   else mfma_block16<false>(l0, l1, a, b);
 }
 
-// One tile's pass over the wave's blocks; the same schedule as wave_tile16f
-// (one block of read-ahead, the A stream wrapping to the next tile).
+// One tile's pass over the wave's blocks: one block of read-ahead, the A stream
+// wrapping to the next tile.
 __device__ inline void wave_tile16(const d2_t* __restrict__ ap, const d2_t* ks, uint64_t lo, uint64_t hi, int count,
                                    int lane, d2_t (&ax)[2], double& sq0, double& sq1) {
   d4_t l0 = __builtin_nondeterministic_value(l0), l1 = l0;
@@ -562,7 +568,8 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void posterior_f64_kernel(
   // 16-byte loads per observation row: the D coordinates and, below 16, alpha
   constexpr int kRowVec = D < kXsStride ? (D + 1 + 1) / 2 : kXsStride / 2;
 
-  // plan entry of this wave, paired per SIMD as in the fp32 kernel
+  // Plan entry of this wave: of eight, the two of a SIMD take entries p and p + 4,
+  // which the plan balances; by wave number if they did not land two to a SIMD.
   int p = wave;
   if constexpr (WAVES == 8) {
     int* on_simd = reinterpret_cast<int*>(mu_red + WAVES * 2 * 32);  // [4]
@@ -604,7 +611,7 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void posterior_f64_kernel(
       for (int q = 0; q < D; ++q) xr[q] = Xc[min(next * 32 + cl, a.n - 1) * D + q];
     }
 
-    __builtin_amdgcn_s_setprio(2);  // K* at a raised priority, as in the fp32 kernel
+    __builtin_amdgcn_s_setprio(2);  // where a CU's waves are in different phases, generation is served first
     // ---- phase 1: group G = 4J + 2 s2 + kk covers rows
     // 16J + 8 s2 + 4t + 2kk + h = 4G - 2kk + h + 4t (t = 0, 1) of block J;
     // WAVES is even, so kk = wave & 1 for all of a wave's groups and each
