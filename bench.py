@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_FP32_MFMA_TFLOPS = 157.3
+PEAK_BF16_MFMA_TFLOPS = 2500.0
 PEAK_FP64_MFMA_TFLOPS = 78.6
 PEAK_HBM_GBPS = 8000.0
 
@@ -224,22 +224,28 @@ def main():
         kernels[name] = {"ms_per_call": ms, "bytes_per_candidate": hbm[name], "achieved_GBps": gbs,
                          "hbm_peak_GBps": PEAK_HBM_GBPS, "hbm_frac": gbs / PEAK_HBM_GBPS}
     kernels["note"] = ("one library call each, host-side argument work included; these kernels are bound by "
-                       "VALU issue (EHVI), LDS latency (forest) and launch latency (top-q) rather than HBM, so "
+                       "VALU issue (EHVI), LDS reads (forest) and launch latency (top-q) rather than HBM, so "
                        "hbm_frac is small by design; the VALU and LDS counters are in profiles/")
 
-    # Algorithmic work of the fused posterior per candidate and objective: the
-    # triangular product (m^2 flops) and K* with the mean (m (3d + 10) flops;
-    # the m square roots and m exponentials are not counted).  The peak is the
-    # rate of the precision that the results have: 157.3 TFLOP/s in fp32, 78.6
-    # in fp64, for the matrix instructions and the vector ALU alike.  The fp32
-    # kernel's product runs as six bf16 products of exact three-part splits
-    # (fp32 results at fp32 accuracy), so its share of the fp32 peak could
-    # exceed one.
+    # The roofline is that of the unit the posterior's product runs on.  fp32:
+    # the triangular product (m^2 flops per candidate and objective) is six
+    # bf16 products of exact three-part splits, so 6 m^2 flops against the dense
+    # bf16 peak.  fp64: product, K* and mean, m^2 + m (3d + 10) flops (the m square
+    # roots and m exponentials are not counted), all on the datapath that the
+    # fp64 matrix instructions and the vector ALU share, against its peak.
     flops_trsm = m * m
     flops_per_unit = flops_trsm + m * (3 * w["d"] + 10)
-    peak = PEAK_FP64_MFMA_TFLOPS if args.dtype == "f64" else PEAK_FP32_MFMA_TFLOPS
-    achieved = flops_per_unit * n / (post_ms * 1e-3) / 1e12
-    achieved_trsm = flops_trsm * n / (post_ms * 1e-3) / 1e12
+    if args.dtype == "f64":
+        counted, peak = flops_per_unit, PEAK_FP64_MFMA_TFLOPS
+        unit_text = (f"m^2 + m(3d+10) = {counted} flops per candidate per objective (triangular product + K* and "
+                     f"mean), {n} candidates per launch")
+    else:
+        counted, peak = 6 * flops_trsm, PEAK_BF16_MFMA_TFLOPS
+        unit_text = (f"6 m^2 = {counted} bf16 flops per candidate per objective (the triangular product as six part "
+                     f"products; K* and the mean, on the fp64 matrix unit and the vector ALU, not counted), {n} "
+                     "candidates per launch")
+    rate = lambda flops: flops * n / (post_ms * 1e-3) / 1e12  # noqa: E731
+    achieved = rate(counted)
     out = {
         "metric": METRIC if (args.config == 3 and args.kernel == "matern52" and not args.warp
                              and args.dtype == "f32") else
@@ -277,9 +283,11 @@ def main():
             "unit": "TFLOP/s",
             "frac": achieved / peak,
             "traffic": posterior_traffic(args),
-            "algorithmic_unit": f"m^2 + m(3d+10) = {flops_per_unit} flops per candidate per objective "
-                                f"(triangular product + K* and mean), {n} candidates per launch",
-            "frac_triangular_product_only": achieved_trsm / peak,
+            "algorithmic_unit": unit_text,
+            "frac_triangular_product_only": rate(flops_trsm if args.dtype == "f64" else counted) / peak,
+            # the same launch in flops of the results' precision
+            "algorithmic_tflops": rate(flops_per_unit),
+            "algorithmic_tflops_triangular_product_only": rate(flops_trsm),
         },
     }
     if not args.no_cpu_baseline:
