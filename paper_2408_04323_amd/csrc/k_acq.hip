@@ -404,12 +404,17 @@ int launch_ehvi_topq(const void* const* mu, const void* const* sigma, int p, int
   // One chunk of 64 per wave up to 512 workgroups (larger pools loop), and at
   // most kSelMaxKeys2 keys for stage 2.  Workgroups of sixteen waves, or of
   // eight where a compute unit would go without one, as long as stage 2, one
-  // workgroup that reads every list, is not given more than 4096 keys for it.
+  // workgroup that reads every list, is not given more than 4096 keys for it,
+  // nor its second wave and a second level (1024 keys to a wave: n = 10,000, q =
+  // 64 109 -> 119 us in fp32, 268 -> 307 in fp64; where it has them anyway smaller
+  // workgroups still pay, n = 30,000 140 -> 121).
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   const int64_t most = std::min<int64_t>(512, kSelMaxKeys2 / q);
-  const int threads = (n + 1023) / 1024 < cus && (n + 511) / 512 * q <= 4096 ? 512 : 1024;
+  const int64_t keys = (n + 1023) / 1024 * q, keys_small = (n + 511) / 512 * q;
+  const bool small = (n + 1023) / 1024 < cus && keys_small <= 4096 && (keys_small <= 1024 || keys > 1024);
+  const int threads = small ? 512 : 1024;
   const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n + threads - 1) / threads, most));
   const size_t ksz = dt == SCOOT_F32 ? sizeof(Key64) : sizeof(Key128);
   const size_t kbytes = ((size_t)blocks * q * ksz + 255) / 256 * 256;

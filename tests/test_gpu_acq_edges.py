@@ -90,3 +90,10 @@ def test_ehvi_three_objectives_few_columns(m, dtype):
         # three factors good to about eight eps of themselves (the float partial
         # expectation to 4e-7), whose differences telescope over at most m + 1 columns
         assert np.max(np.abs(got - want)) <= 24 * eps * (m + 3) * np.max(want)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n,q", [(8192, 64), (8193, 64), (16385, 64), (50000, 12), (130561, 4), (131073, 4)])
+def test_selection_beside_ehvi_many_keys(n, q, dtype):
+    """Either side of 1024 keys for the second stage in workgroups of eight and of sixteen waves."""
+    test_selection_beside_ehvi(n, q, dtype)
